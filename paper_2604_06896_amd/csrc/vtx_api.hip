@@ -337,12 +337,13 @@ int relax_impl(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_r
         const int cur = k & 1;
         launch_relax_iter(t->d, t->w, mode, bufs[cur], bufs[cur ^ 1], cur, raw(p), ra, cs);
     });
-    if (ra.t1_enable) {
+    const LoopCtl &h = t->w.ctl_host[0];
+    // (a loop without an exchange, and without an error, left the topology)
+    if (ra.t1_enable && (rc || h.n_t1 > 0 || h.t1_overflow)) {
         const int rt = vtx::tissue_topology_changed(t, s);
         if (!rc) rc = rt;
     }
     if (rc) return rc;
-    const LoopCtl &h = t->w.ctl_host[0];
     if (h.result_buf == 1) HIPCHK(hipMemcpyAsync(X, t->w.xbuf, pos_bytes(t, mode),
                                                  hipMemcpyDeviceToDevice, s));
     // energy (and nudge energy) at the returned positions
@@ -377,6 +378,7 @@ const Workspace &tissue_ws(vtx_tissue t) { return t->w; }
 int64_t tissue_size(vtx_tissue t) { return t->n_vert; }
 int64_t tissue_cells(vtx_tissue t) { return t->n_cell; }
 double *tissue_ep_buf(vtx_tissue t) { return t->ep_buf; }
+const TileTables &tissue_tiles(vtx_tissue t) { return t->tiles; }
 int set_error(int code, const char *msg) { return fail(code, "%s", msg); }
 int tissue_topology_changed(vtx_tissue t, hipStream_t s) {
     launch_tile_build(t->d, t->tiles, s);
@@ -653,9 +655,9 @@ int vtx_t1(vtx_tissue t, int32_t mode, void *X, const vtx_params *p, double l_mi
     if (rc) return rc;
     launch_t1(t->d, t->w, mode, X, raw(p), l_min, l_new, s);
     if ((rc = check_launch("vtx_t1"))) return rc;
-    if ((rc = vtx::tissue_topology_changed(t, s))) return rc;
     if ((rc = read_ctl(t, 1, s))) return rc;
     const LoopCtl h = t->w.ctl_host[1];
+    if ((h.n_t1 > 0 || h.t1_overflow) && (rc = vtx::tissue_topology_changed(t, s))) return rc;
     if (n_swap) *n_swap = h.n_t1;
     if (n_stretch) *n_stretch = h.n_stretch;
     LoopCtl z2{};  // the evaluation control block must never stay `done`

@@ -144,6 +144,12 @@ struct TileTables {
     int4 *fstar;        // [n_vert]
     int32_t *fe;        // [2][n_vert]
 };
+// One tissue of a launch that rebuilds the tables of many.
+struct TileJob {
+    DevTissue t;
+    TileTables tt;
+    int32_t tile0;      // first block of the tissue
+};
 __host__ __device__ inline int64_t n_tiles_for(int64_t n_vert) {
     return (n_vert + kTileV - 1) / kTileV;
 }

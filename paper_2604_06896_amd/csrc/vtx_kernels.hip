@@ -304,17 +304,34 @@ __device__ __forceinline__ int lower_bound_lds(const int32_t *a, int n, int32_t 
 // neighbours as local references, and the halo of outside vertices they
 // reach.  Tiles whose halo or rows overflow the fixed slots are marked for
 // the global path.
-__global__ __launch_bounds__(kTileV) void k_tile_build(DevTissue t, TileTables tt) {
+//
+// The build is a chain of latencies (three sorts in LDS and the loads they
+// wait for), so the rows are read from global memory once, eight lanes a
+// row, and every later look at them is in LDS; only vertices outside the
+// tile are sorted (about 350 candidates of 1800 corner references, none for
+// a tissue of one tile).
+__device__ __forceinline__ int pow2_at_least(int n) {
+    int p = 1;
+    while (p < n) p <<= 1;
+    return p;
+}
+
+__device__ __forceinline__ void tile_build(const DevTissue &t, const TileTables &tt, int tile) {
     constexpr int NK = 4096;  // 3 kTileV neighbours + kCornerCap corners, padded
     static_assert(3 * kTileV + kCornerCap <= NK, "halo candidate buffer");
     __shared__ int32_t keys[NK];
-    __shared__ int32_t uniq[kTileCap];  // distinct cells by id
-    __shared__ int32_t ord[kTileCap];   // the same cells by side count (then id)
-    __shared__ int32_t perm[kTileCap];  // position in ord of uniq[i]
-    __shared__ int32_t oimg[kTileCap];  // ord[r] has a corner with a nonzero image
+    __shared__ int32_t row[kCornerCap];  // corner rows in the order of uniq
+    __shared__ int32_t uniq[kTileCap];   // distinct cells by id
+    __shared__ int32_t urb[kTileCap];    // their rows in global memory
+    __shared__ int32_t ulen[kTileCap];   // their side counts
+    __shared__ int32_t ust[kTileCap];    // their rows in `row`
+    __shared__ int32_t ord[kTileCap];    // cells by side count: i of uniq, bit 30: image
+    __shared__ int32_t perm[kTileCap];   // position in ord of uniq[i]
+    __shared__ int32_t cst[kTileCap];    // row start of the cells in the order of ord
     __shared__ int32_t halo[kHaloCap];
     __shared__ int32_t scan[kTileV];
-    const int tile = blockIdx.x, tid = threadIdx.x;
+    __shared__ int s_cand;
+    const int tid = threadIdx.x;
     const int nv = t.n_vert;
     const int lo = tile * kTileV;
     const int hi = min(nv, lo + kTileV);
@@ -331,86 +348,104 @@ __global__ __launch_bounds__(kTileV) void k_tile_build(DevTissue t, TileTables t
     // (1) the distinct cells around the tile's vertices
     for (int k = 0; k < 3; ++k) keys[3 * tid + k] = c[k];
     keys[3 * kTileV + tid] = INT_MAX;
+    if (tid == 0) s_cand = 0;
     __syncthreads();
     block_bitonic(keys, 4 * kTileV);
     const int nu = block_unique<4>(keys, uniq, kTileCap, scan);  // <= 3 kTileV
-    // (1b) cells ordered by (crosses the box, side count), so that the lanes
-    // of a wave walk rows of equal length and most waves need no images
-    for (int i = tid; i < 4 * kTileV; i += kTileV) {
+    // (1b) their rows, staged in LDS; exclusive scan of the side counts of
+    // cells 3 tid .. 3 tid + 2
+    auto row_starts = [&](auto len_of_cell, int32_t *out) -> int {
+        int len[3], sum = 0;
+        for (int j = 0; j < 3; ++j) {
+            const int i = 3 * tid + j;
+            len[j] = i < nu ? len_of_cell(i) : 0;
+            sum += len[j];
+        }
+        scan[tid] = sum;
+        __syncthreads();
+        for (int off = 1; off < kTileV; off <<= 1) {
+            const int add = tid >= off ? scan[tid - off] : 0;
+            __syncthreads();
+            scan[tid] += add;
+            __syncthreads();
+        }
+        int at = scan[tid] - sum;
+        for (int j = 0; j < 3; ++j) {
+            if (3 * tid + j < nu) out[3 * tid + j] = at;
+            at += len[j];
+        }
+        const int total = scan[kTileV - 1];
+        __syncthreads();
+        return total;
+    };
+    for (int i = tid; i < nu; i += kTileV) {
+        urb[i] = t.row_ptr[uniq[i]];
+        ulen[i] = t.nsides[uniq[i]];
+    }
+    __syncthreads();
+    const int ncorner = row_starts([&](int i) { return ulen[i]; }, ust);
+    bool fallback = ncorner > kCornerCap;
+    if (!fallback)
+        for (int q = tid; q < 8 * nu; q += kTileV) {
+            const int i = q >> 3;
+            for (int k = q & 7; k < ulen[i]; k += 8) row[ust[i] + k] = t.corner[urb[i] + k];
+        }
+    __syncthreads();
+    // (2) cells ordered by (crosses the box, side count), so that the lanes
+    // of a wave walk rows of equal length and most waves need no images (a
+    // tile on the global path does not look at the image flags)
+    const int nu2 = pow2_at_least(nu);
+    for (int i = tid; i < nu2; i += kTileV) {
         int key = INT_MAX;
         if (i < nu) {
-            const int cc = uniq[i];
-            const int ns = t.nsides[cc], rb = t.row_ptr[cc];
             int img = 0;
-            for (int k = 0; k < ns; ++k)
-                img |= ((uint32_t)t.corner[rb + k] >> kIdBits) != kZeroImage ? 1 : 0;
-            key = (((img << 10) | min(ns, 1023)) << 10) | i;
+            if (!fallback)
+                for (int k = 0; k < ulen[i]; ++k)
+                    img |= ((uint32_t)row[ust[i] + k] >> kIdBits) != kZeroImage ? 1 : 0;
+            key = (((img << 10) | min(ulen[i], 1023)) << 10) | i;
         }
         keys[i] = key;
     }
     __syncthreads();
-    block_bitonic(keys, 4 * kTileV);
+    block_bitonic(keys, nu2);
     for (int r = tid; r < nu; r += kTileV) {
         const int i = keys[r] & 1023;
-        ord[r] = uniq[i];
+        ord[r] = i | (((keys[r] >> 20) & 1) << 30);
         perm[i] = r;
-        oimg[r] = (keys[r] >> 20) & 1;
     }
     __syncthreads();
-    // (2) row starts: exclusive scan of the rows' lengths, cells 3 tid .. 3 tid + 2
-    int len[3], cid[3];
-    int sum = 0;
-    for (int j = 0; j < 3; ++j) {
-        const int i = 3 * tid + j;
-        cid[j] = i < nu ? ord[i] : -1;
-        len[j] = i < nu ? t.nsides[cid[j]] : 0;
-        sum += len[j];
-    }
-    scan[tid] = sum;
-    __syncthreads();
-    for (int off = 1; off < kTileV; off <<= 1) {
-        const int add = tid >= off ? scan[tid - off] : 0;
-        __syncthreads();
-        scan[tid] += add;
-        __syncthreads();
-    }
-    const int ncorner = scan[kTileV - 1];
-    int start[3];
-    start[0] = scan[tid] - sum;
-    start[1] = start[0] + len[0];
-    start[2] = start[1] + len[1];
-    bool fallback = ncorner > kCornerCap;
+    constexpr int kOrd = 1023;
+    row_starts([&](int r) { return ulen[ord[r] & kOrd]; }, cst);
     // (3) the halo: neighbours and corners outside [lo, hi)
     int nh = 0;
     if (!fallback) {
+        auto add = [&](int32_t wk) {
+            const int id = id_of(wk);
+            if (id < lo || id >= hi) keys[atomicAdd(&s_cand, 1)] = id;
+        };
+        if (live)
+            for (int k = 0; k < 3; ++k) add(w[k]);
+        for (int q = tid; q < ncorner; q += kTileV) add(row[q]);
         __syncthreads();
-        for (int i = tid; i < NK; i += kTileV) keys[i] = INT_MAX;
-        __syncthreads();
-        for (int k = 0; k < 3; ++k) {
-            const int id = id_of(w[k]);
-            keys[3 * tid + k] = live && (id < lo || id >= hi) ? id : INT_MAX;
+        const int cand = s_cand;
+        if (cand > 0) {
+            const int n2 = pow2_at_least(cand), pad = cand <= 4 * kTileV ? 4 * kTileV : NK;
+            for (int i = cand + tid; i < pad; i += kTileV) keys[i] = INT_MAX;
+            __syncthreads();
+            block_bitonic(keys, n2);
+            nh = cand <= 4 * kTileV ? block_unique<4>(keys, halo, kHaloCap, scan)
+                                    : block_unique<NK / kTileV>(keys, halo, kHaloCap, scan);
         }
-        for (int j = 0; j < 3; ++j) {
-            if (cid[j] < 0) continue;
-            const int rb = t.row_ptr[cid[j]];
-            for (int k = 0; k < len[j]; ++k) {
-                const int id = id_of(t.corner[rb + k]);
-                keys[3 * kTileV + start[j] + k] = id < lo || id >= hi ? id : INT_MAX;
-            }
-        }
-        __syncthreads();
-        block_bitonic(keys, NK);
-        nh = block_unique<NK / kTileV>(keys, halo, kHaloCap, scan);
         fallback = nh > kHaloCap;
     }
     // (4) the tables
     int32_t *dst = tt.cells + (int64_t)tile * kTileCap;
-    for (int j = 0; j < 3; ++j) {
-        if (cid[j] < 0) continue;
-        const int v0 = id_of(t.corner[t.row_ptr[cid[j]]]);
-        uint32_t e = (uint32_t)cid[j] | (oimg[3 * tid + j] ? kCellImage : 0u);
+    for (int r = tid; r < nu; r += kTileV) {
+        const int i = ord[r] & kOrd;
+        const int v0 = id_of(ncorner > kCornerCap ? t.corner[urb[i]] : row[ust[i]]);
+        uint32_t e = (uint32_t)uniq[i] | ((ord[r] >> 30) & 1 ? kCellImage : 0u);
         if (v0 / kTileV == tile) e |= kCellOwner;
-        dst[3 * tid + j] = (int32_t)e;
+        dst[r] = (int32_t)e;
     }
     auto local_of = [&](int32_t wk) -> int {
         const int id = id_of(wk);
@@ -420,13 +455,12 @@ __global__ __launch_bounds__(kTileV) void k_tile_build(DevTissue t, TileTables t
         for (int i = tid; i < nh; i += kTileV) tt.halo[(int64_t)tile * kHaloCap + i] = halo[i];
         uint16_t *cs = tt.cstart + (int64_t)tile * kCstartPad;
         uint16_t *co = tt.corners + (int64_t)tile * kCornerCap;
-        for (int j = 0; j < 3; ++j) {
-            if (cid[j] < 0) continue;
-            cs[3 * tid + j] = (uint16_t)start[j];
-            const int rb = t.row_ptr[cid[j]];
-            for (int k = 0; k < len[j]; ++k) {
-                const int32_t wk = t.corner[rb + k];
-                co[start[j] + k] = (uint16_t)pack_local(local_of(wk), wk);
+        for (int r = tid; r < nu; r += kTileV) cs[r] = (uint16_t)cst[r];
+        for (int q = tid; q < 8 * nu; q += kTileV) {
+            const int r = q >> 3, i = ord[r] & kOrd;
+            for (int k = q & 7; k < ulen[i]; k += 8) {
+                const int32_t wk = row[ust[i] + k];
+                co[cst[r] + k] = (uint16_t)pack_local(local_of(wk), wk);
             }
         }
         if (tid == 0) cs[nu] = (uint16_t)ncorner;
@@ -446,6 +480,21 @@ __global__ __launch_bounds__(kTileV) void k_tile_build(DevTissue t, TileTables t
         tt.fe[v] = t.star[star_edge_at(nv, 1, v)];
         tt.fe[(int64_t)nv + v] = t.star[star_edge_at(nv, 2, v)];
     }
+}
+
+__global__ __launch_bounds__(kTileV) void k_tile_build(DevTissue t, TileTables tt) {
+    tile_build(t, tt, blockIdx.x);
+}
+
+// The tiles of many tissues in one launch: block b builds tile b - tile0 of
+// tissue job_of[b].  Tissues whose relaxation made no exchange (and did not
+// fail) keep their topology, and their blocks leave at once.
+__global__ __launch_bounds__(kTileV) void k_tile_build_many(const TileJob *__restrict__ jobs,
+                                                            const int32_t *__restrict__ job_of,
+                                                            const vtx_relax_result *res) {
+    const int j = job_of[blockIdx.x];
+    if (res[j].n_t1 == 0 && res[j].status >= 0) return;
+    tile_build(jobs[j].t, jobs[j].tt, (int)blockIdx.x - jobs[j].tile0);
 }
 
 // Energy and forces in one launch.  Each block takes one vertex tile: it
@@ -1257,6 +1306,12 @@ void launch_eval_fused(const DevTissue &t, const Workspace &w, const TileTables 
 void launch_tile_build(const DevTissue &t, const TileTables &tt, hipStream_t s) {
     const int64_t g = n_tiles_for(t.n_vert);
     if (g > 0) hipLaunchKernelGGL(k_tile_build, dim3((unsigned)g), dim3(kTileV), 0, s, t, tt);
+}
+
+void launch_tile_build_many(const TileJob *jobs, const int32_t *job_of, int n_tiles,
+                            const vtx_relax_result *res, hipStream_t s) {
+    hipLaunchKernelGGL(k_tile_build_many, dim3((unsigned)n_tiles), dim3(kTileV), 0, s, jobs,
+                       job_of, res);
 }
 
 void launch_eval(const DevTissue &t, const Workspace &w, int mode, const void *X,
