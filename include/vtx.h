@@ -130,7 +130,8 @@ typedef struct {
     double beta;
     const void *X_target;
     const void *g_lin;
-    int32_t chunk;   /* iterations per captured graph launch (0 = 256) */
+    int32_t chunk;   /* iterations per captured graph launch (0 = 256); not used where
+                        the whole loop runs in one workgroup */
 } vtx_relax_opts;
 
 typedef struct {
@@ -244,9 +245,11 @@ int vtx_edge_lengths(vtx_tissue t, int32_t mode, const void *X, double *len_dev,
                      void *stream);
 
 /* Relax X in place to mechanical equilibrium (Methods, "Simulation
- * engine").  The loop runs on the device in captured graphs of `chunk`
- * iterations; the host reads an 8-byte status between chunks.  T1 mutates
- * the tissue's topology.  `res` is a host struct; synchronises. */
+ * engine").  A tissue of at most 1024 cells whose position buffers, cell
+ * coefficients and corner rows fit a workgroup's LDS runs its whole loop in
+ * one workgroup; larger ones run on the whole GPU in captured graphs of
+ * `chunk` iterations, and the host reads a status between chunks.  T1
+ * mutates the tissue's topology.  `res` is a host struct; synchronises. */
 int vtx_relax(vtx_tissue t, int32_t mode, void *X, const vtx_params *p,
               const vtx_relax_opts *o, vtx_relax_result *res, void *stream);
 
@@ -320,17 +323,17 @@ int vtx_batch_destroy(vtx_batch b);
 
 /* Relax every tissue of the batch (each with its own X, parameters and the
  * shared options; Methods, "Simulation engine", per tissue).  Schedules:
- *   VTX_SCHED_PERSISTENT  one persistent launch captured in a graph, one
- *                         workgroup of `block_threads` (256, 512 or 1024;
- *                         0 chooses) threads per tissue looping the whole
- *                         relaxation, tissues taken from a device work
- *                         queue in descending size.  With 512 threads (or
- *                         0), a batch whose tissues all have at most 1024
- *                         cells and fit the per-workgroup LDS (both
- *                         position buffers, cell coefficients, corner rows)
- *                         runs a kernel that keeps them there and the vertex
- *                         stars in registers, T1 passes included; 0 takes
- *                         1024 threads otherwise;
+ *   VTX_SCHED_PERSISTENT  one persistent launch, one workgroup of
+ *                         `block_threads` (256, 512 or 1024; 0 chooses)
+ *                         threads per tissue looping the whole relaxation,
+ *                         tissues started in descending size.  With 512
+ *                         threads (or 0), a batch whose tissues all have at
+ *                         most 1024 cells and fit the per-workgroup LDS
+ *                         (both position buffers, cell coefficients, corner
+ *                         rows) runs a kernel that keeps them there and the
+ *                         vertex stars in registers, T1 passes included, on
+ *                         as many waves as its largest tissue needs (512
+ *                         threads at most); 0 takes 1024 threads otherwise;
  *   VTX_SCHED_GRID        each tissue in turn through vtx_relax (all
  *                         workgroups of the GPU on one tissue; suits a few
  *                         large tissues); block_threads is ignored;

@@ -15,6 +15,8 @@
 #include "vtx_launch.h"
 
 namespace vtx {
+// Rebuild the tissue's fused-evaluation tables after its topology changed
+// (on stream s, in order with the change).
 int tissue_topology_changed(vtx_tissue t, hipStream_t s);
 }
 
@@ -235,7 +237,7 @@ void free_tissue(vtx_tissue t) {
                     d.cell_he, d.star, d.star_he, t->w.xbuf,
                     t->w.cap, t->w.cell_aux, t->w.partials, t->w.partials2, t->w.mpart,
                     t->w.t1_list,
-                    t->w.ctl, t->w.cg, t->w.scal, t->ep_buf,
+                    t->w.ctl, t->w.cg, t->w.scal, t->w.one, t->ep_buf,
                     t->tiles.cells, t->tiles.info, t->tiles.halo, t->tiles.cstart,
                     t->tiles.corners, t->tiles.fstar, t->tiles.fe};
     for (void *p : ptrs)
@@ -300,24 +302,11 @@ int run_loop(vtx_tissue t, int chunk, int64_t max_steps, hipStream_t s, Body bod
     return rc;
 }
 
-int relax_impl(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_relax_opts *o,
-               vtx_relax_result *res, hipStream_t s) {
-    if (!(o->eta > 0) || !(o->tol >= 0) || o->patience < 1 || o->max_iter < 1)
-        return fail(VTX_E_ARG, "relax options: eta > 0, tol >= 0, patience >= 1, max_iter >= 1");
-    RelaxArgs ra{};
-    ra.eta = o->eta;
-    ra.t1_enable = o->t1_enable != 0;
-    ra.l_min = o->l_min;
-    ra.l_new = o->l_new;
-    ra.beta = o->beta;
-    ra.X_target = o->X_target;
-    ra.g_lin = o->g_lin;
-    ra.nudge = o->beta != 0.0 ? (o->X_target ? 1 : (o->g_lin ? 2 : 0)) : 0;
-    if (o->beta != 0.0 && ra.nudge == 0)
-        return fail(VTX_E_ARG, "a nudge needs X_target or g_lin");
-    if (ra.nudge && ra.t1_enable) return fail(VTX_E_ARG, "a nudge cannot be combined with T1");
-    if (ra.t1_enable && !(o->l_min > 0 && o->l_new > 0))
-        return fail(VTX_E_ARG, "T1 needs l_min > 0 and l_new > 0");
+// The relaxation loop on the whole GPU: captured graphs of `chunk`
+// iterations.  Leaves the result (all but the energy) in r and the T1 pass's
+// overflow code in `overflow`, and the final positions in X.
+int relax_grid(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_relax_opts *o,
+               const RelaxArgs &ra, hipStream_t s, vtx_relax_result &r, int &overflow) {
     LoopCtl c{};
     c.status = VTX_NOT_CONVERGED;
     c.max_iter = o->max_iter;
@@ -344,8 +333,42 @@ int relax_impl(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_r
         if (!rc) rc = rt;
     }
     if (rc) return rc;
-    if (h.result_buf == 1) HIPCHK(hipMemcpyAsync(X, t->w.xbuf, pos_bytes(t, mode),
-                                                 hipMemcpyDeviceToDevice, s));
+    if (h.result_buf == 1)
+        HIPCHK(hipMemcpyAsync(X, t->w.xbuf, pos_bytes(t, mode), hipMemcpyDeviceToDevice, s));
+    r.iters = h.iter;
+    r.n_t1 = h.n_t1;
+    r.n_stretch = h.n_stretch;
+    r.max_f = h.last_maxf;
+    r.status = h.status;
+    overflow = h.t1_overflow;
+    return VTX_OK;
+}
+
+int relax_impl(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_relax_opts *o,
+               vtx_relax_result *res, hipStream_t s) {
+    if (!(o->eta > 0) || !(o->tol >= 0) || o->patience < 1 || o->max_iter < 1)
+        return fail(VTX_E_ARG, "relax options: eta > 0, tol >= 0, patience >= 1, max_iter >= 1");
+    RelaxArgs ra{};
+    ra.eta = o->eta;
+    ra.t1_enable = o->t1_enable != 0;
+    ra.l_min = o->l_min;
+    ra.l_new = o->l_new;
+    ra.beta = o->beta;
+    ra.X_target = o->X_target;
+    ra.g_lin = o->g_lin;
+    ra.nudge = o->beta != 0.0 ? (o->X_target ? 1 : (o->g_lin ? 2 : 0)) : 0;
+    if (o->beta != 0.0 && ra.nudge == 0)
+        return fail(VTX_E_ARG, "a nudge needs X_target or g_lin");
+    if (ra.nudge && ra.t1_enable) return fail(VTX_E_ARG, "a nudge cannot be combined with T1");
+    if (ra.t1_enable && !(o->l_min > 0 && o->l_new > 0))
+        return fail(VTX_E_ARG, "T1 needs l_min > 0 and l_new > 0");
+    vtx_relax_result r{};
+    int overflow = 0;
+    // A tissue that fits one workgroup's LDS runs its whole loop there.
+    const vtx_relax_result *one = nullptr;
+    int rc = relax_one(t->d, t->w, mode, X, raw(p), ra, o->tol, o->patience, o->max_iter, s, &one);
+    if (rc) return rc;
+    if (!one && (rc = relax_grid(t, mode, X, p, o, ra, s, r, overflow))) return rc;
     // energy (and nudge energy) at the returned positions
     launch_eval(t->d, t->w, mode, X, raw(p), t->w.scal + 4, nullptr, nullptr, s);
     if (ra.nudge == 1) launch_v2v(t->d, t->w, mode, X, o->X_target, t->w.scal + 5, nullptr, s);
@@ -353,20 +376,24 @@ int relax_impl(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_r
         launch_dot_pos(t->w, mode, (int)t->n_vert, (const double *)o->g_lin, X, t->w.scal + 5, s);
     if ((rc = check_launch("final energy"))) return rc;
     double e[2] = {0, 0};
+    if (one) HIPCHK(hipMemcpyAsync(&r, one, sizeof r, hipMemcpyDeviceToHost, s));
     HIPCHK(hipMemcpyAsync(e, t->w.scal + 4, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    if (res) {
-        res->iters = h.iter;
-        res->n_t1 = h.n_t1;
-        res->n_stretch = h.n_stretch;
-        res->max_f = h.last_maxf;
-        res->energy = e[0] + (ra.nudge ? o->beta * e[1] : 0.0);
-        res->status = h.status == VTX_E_NONFINITE ? VTX_NOT_CONVERGED : h.status;
-    }
-    if (h.t1_overflow == 1) return fail(VTX_E_CAPACITY, "T1 pass: too many pending re-checks");
-    if (h.t1_overflow == 2)
+    if (one && ra.t1_enable && (r.n_t1 > 0 || r.status == VTX_E_CAPACITY) &&
+        (rc = vtx::tissue_topology_changed(t, s)))
+        return rc;
+    if (r.status == VTX_E_CAPACITY) overflow = 3;
+    const bool nonfinite = r.status == VTX_E_NONFINITE;
+    r.energy = e[0] + (ra.nudge ? o->beta * e[1] : 0.0);
+    if (r.status < 0) r.status = VTX_NOT_CONVERGED;
+    if (res) *res = r;
+    if (overflow == 1) return fail(VTX_E_CAPACITY, "T1 pass: too many pending re-checks");
+    if (overflow == 2)
         return fail(VTX_E_CAPACITY, "T1 pass: corner-row pool exhausted or a cell spans two images");
-    if (h.status == VTX_E_NONFINITE) return fail(VTX_E_NONFINITE, "non-finite forces in relaxation");
+    if (overflow == 3)
+        return fail(VTX_E_CAPACITY, "T1 pass: too many pending re-checks, corner-row pool exhausted "
+                                    "or a cell spans two images");
+    if (nonfinite) return fail(VTX_E_NONFINITE, "non-finite forces in relaxation");
     return VTX_OK;
 }
 
@@ -458,6 +485,7 @@ int vtx_tissue_create(const int32_t *he, int64_t n_he, int64_t n_vert, int64_t n
     A((void **)&w.ctl, 2 * sizeof(LoopCtl));
     A((void **)&w.cg, 6 * 16 * (size_t)n_vert);  // CG: 4 vectors, MINRES: 6
     A((void **)&w.scal, 16 * sizeof(double));
+    A(&w.one, kOneBytes);
     A((void **)&t->ep_buf, 2 * 16 * (size_t)n_vert);
     const size_t n_tiles = (size_t)n_tiles_for(n_vert);
     A((void **)&t->tiles.cells, 4 * (size_t)kTileCap * n_tiles);

@@ -2,8 +2,9 @@
 // launch (VertAX, arXiv 2604.06896, Methods, "Simulation engine", applied
 // per tissue).  One workgroup owns one tissue at a time and runs the whole
 // loop -- cell pass, T1 pass, vertex pass with the gradient-descent step,
-// convergence test -- with workgroup barriers only; tissues are taken from a
-// device work queue in descending size so the largest start first.
+// convergence test -- with workgroup barriers only; block b takes the b-th
+// largest tissue, so the largest start first.  (Blocks are dispatched in
+// order as others end, so no work queue is needed.)
 #include <algorithm>
 #include <chrono>
 #include <climits>
@@ -22,7 +23,6 @@ struct vtx_batch_s {
     void *gitems;                // device GradItem[n]
     void **xm_list;              // device pointer list (EP minus states)
     int32_t *order_d;            // device [2n]: order, then order + n
-    unsigned int *queue;
     vtx_relax_result *res_d;     // device [2n]
     vtx_grad_result *gres_d;
     void *mb_groups;             // device MbGroup[n] (multi-workgroup adjoint)
@@ -30,7 +30,6 @@ struct vtx_batch_s {
     TileJob *tile_jobs;          // device [n]: the fused evaluation's tables of every tissue
     int32_t *tile_job_of;        // device [n_tiles]: tissue of each tile
     int n_tiles;
-    hipStream_t cap_stream;
 };
 
 namespace vtx {
@@ -48,8 +47,6 @@ __device__ __forceinline__ void nudge_grad(const BatchItem &B, const PosT *X, in
         cy = B.g_lin[2 * (int64_t)v + 1];
     }
 }
-
-__global__ void k_reset_queue(unsigned int *q) { *q = 0u; }
 
 // LDS bytes the batched adjoint needs to hold, for one tissue, the arrays its
 // Hessian-vector product gathers: positions, the vector multiplied, and the
@@ -79,15 +76,15 @@ __host__ __device__ inline bool cg_fast_fits(int64_t n_vert, int64_t n_cell, int
            cg_fast_lds_bytes<PosT, M>(n_vert, n_cell, n_he) <= lds_bytes;
 }
 
-// Cells of a tissue handed to the threads of the register-resident CG by
+// Cells of a tissue handed to the threads of the one-workgroup kernels by
 // side count.  The cells, stably sorted by min(sides, 15), are cut into K
-// runs of ceil(n_cell / K); slot k of thread i takes entry i of run k,
-// counted from the front in even runs and from the back in odd ones.  The
-// cells of one slot across a wave then have about the same number of
-// corners (the wave walks them in step), and each thread's K cells about K
-// times the mean, so the waves finish the cell phase together.  `tmp`
-// holds n_cell ints.  cid[k] is the cell of the thread's slot k, -1 if the
-// run has no entry i.
+// runs of ceil(n_cell / K) (one run where there is a thread for every cell);
+// slot k of thread i takes entry i of run k, counted from the front in even
+// runs and from the back in odd ones.  The cells of one slot across a wave
+// then have about the same number of corners (the wave walks them in step),
+// and each thread's K cells about K times the mean, so the waves finish the
+// cell phase together.  `tmp` holds n_cell ints.  cid[k] is the cell of the
+// thread's slot k, -1 if the run has no entry i.
 template <int K>
 __device__ __forceinline__ void cells_by_sides(const DevTissue &t, int *tmp, int *s_scan,
                                                int (&cid)[K]) {
@@ -112,7 +109,7 @@ __device__ __forceinline__ void cells_by_sides(const DevTissue &t, int *tmp, int
         base += tot;
     }
     __syncthreads();
-    const int run = (nc + K - 1) / K;
+    const int run = nc <= bd ? nc : (nc + K - 1) / K;
 #pragma unroll
     for (int i = 0; i < K; ++i) {
         const int lo = i * run, len = min(run, nc - lo);
@@ -298,20 +295,14 @@ constexpr int kFastK = MAXT <= 512 ? 2 : 0;
 // of the L2.  The arithmetic is the same either way.
 template <typename PosT, typename M, int MAXT>
 __global__ __launch_bounds__(MAXT) void k_batch_cg(const GradItem *__restrict__ items,
-                                                   const int32_t *__restrict__ order, int n,
-                                                   unsigned int *queue, GradOpts o,
-                                                   vtx_grad_result *res, int lds_bytes) {
+                                                   const int32_t *__restrict__ order,
+                                                   GradOpts o, vtx_grad_result *res,
+                                                   int lds_bytes) {
     extern __shared__ __align__(16) unsigned char lds_dyn[];
     __shared__ double sh[16];
-    __shared__ int s_item;
     __shared__ int s_scan[16];
-    for (;;) {
-        if (threadIdx.x == 0) s_item = (int)atomicAdd(queue, 1u);
-        __syncthreads();
-        const int slot = s_item;
-        __syncthreads();
-        if (slot >= n) return;
-        const int idx = order[slot];
+    {
+        const int idx = order[blockIdx.x];
         const GradItem &G = items[idx];
         const DevTissue t = G.t;
         const DevParams<PosT> p = to_dev<PosT>(G.p);
@@ -514,7 +505,6 @@ __global__ __launch_bounds__(MAXT) void k_batch_cg(const GradItem *__restrict__ 
             gr.status = status;
             res[idx] = gr;
         }
-        __syncthreads();
     }
 }
 
@@ -684,29 +674,37 @@ static_assert(kRelaxLdsThreads <= 512, "block_allsum2 holds the sums of eight wa
 // pass with the step and the convergence control are those of k_batch_relax
 // (same arithmetic; the nudge mean is summed per thread in the same vertex
 // order), and the state returned is copied back into the caller's buffer.
+//
+// With one workgroup on a CU a step is a chain of latencies: two barriers
+// (after the cell pass and after the vertex pass, where every wave leaves
+// its max |F| and every thread then takes the convergence decision by
+// itself), and between them the corner steps of a cell and the stars of a
+// vertex, written so that their square roots overlap.  Small tissues run on
+// fewer waves (relax_lds_threads), which makes both barriers shorter.
+// Against a form with five barriers, a branch per corner, the library's
+// sqrt and division and always eight waves, a step of 100 FP64 cells with T1
+// takes 2.8 us instead of 4.5, of 100 tissues of 100 MIXED cells 3.3 instead
+// of 4.8, and of 128 nudged FP64 relaxations of 1000 cells 8.0 instead of
+// 9.7; through one launch per pass (Tissue.relax before) the first took
+// 15.4 us.
 template <typename PosT, typename M, bool T1>
 __global__ __launch_bounds__(kRelaxLdsThreads) void k_batch_relax_lds(
-    const BatchItem *__restrict__ items, const int32_t *__restrict__ order, int n,
-    unsigned int *queue, BatchOpts o, vtx_relax_result *res) {
+    const BatchItem *__restrict__ items, const int32_t *__restrict__ order, BatchOpts o,
+    vtx_relax_result *res) {
     constexpr int K = kRelaxLdsK, KV = 2 * kRelaxLdsK;
     extern __shared__ __align__(16) unsigned char lds_dyn[];
     __shared__ int32_t sort_buf[T1 ? kT1SortCap : 1];
     __shared__ int32_t extra[T1 ? kT1Extra : 1];
     __shared__ int32_t scan[T1 ? kRelaxLdsThreads : 1];
-    __shared__ unsigned int s_cnt;
+    __shared__ unsigned int s_cnt[2];  // short edges, by step parity
     __shared__ double sh[16];
-    __shared__ int s_item;
+    __shared__ double s_max[2][8];     // max |F| of each wave, by step parity
     __shared__ int s_scan[16];
     __shared__ RelaxState st;
     auto a16 = [](int64_t b) { return (b + 15) & ~(int64_t)15; };
     const M lmin2 = (M)(o.l_min * o.l_min * (1.0 + 1e-4));
-    for (;;) {
-        if (threadIdx.x == 0) s_item = (int)atomicAdd(queue, 1u);
-        __syncthreads();
-        const int slot = s_item;
-        __syncthreads();
-        if (slot >= n) return;
-        const int idx = order[slot];
+    {
+        const int idx = order ? order[blockIdx.x] : (int)blockIdx.x;
         const BatchItem &B = items[idx];
         const DevTissue &t = B.t;
         const DevParams<PosT> p = to_dev<PosT>(B.p);
@@ -793,7 +791,10 @@ __global__ __launch_bounds__(kRelaxLdsThreads) void k_batch_relax_lds(
                 }
             }
         }
-        if (tid == 0) st = RelaxState{0, 0, 0, 0, 0.0, VTX_NOT_CONVERGED, 0, 0, 0, 0};
+        if (tid == 0) {
+            st = RelaxState{0, 0, 0, 0, 0.0, VTX_NOT_CONVERGED, 0, 0, 0, 0};
+            s_cnt[0] = 0u;
+        }
         __syncthreads();
         const double inv_n = 1.0 / (double)nv;
         // gradient of the nudge cost at own vertex j (as nudge_grad)
@@ -812,14 +813,14 @@ __global__ __launch_bounds__(kRelaxLdsThreads) void k_batch_relax_lds(
             }
         };
         const PosT lmin2p = (PosT)lmin2;
-        int cur = 0;
+        int cur = 0, status = VTX_NOT_CONVERGED, result_buf = 0;
+        int64_t iter = 0, count = 0;
+        double last_mf = 0.0;
+        const int nw = (bd + 63) >> 6;
         for (;;) {
             PosT *Xc = cur ? X1 : X0;
             PosT *Xn = cur ? X0 : X1;
-            if (T1) {
-                if (tid == 0) s_cnt = 0u;
-                __syncthreads();
-            }
+            const int par = (int)(iter & 1);
             // cell pass
 #pragma unroll
             for (int i = 0; i < K; ++i) {
@@ -827,16 +828,20 @@ __global__ __launch_bounds__(kRelaxLdsThreads) void k_batch_relax_lds(
                 const int base = lrb[i];
                 if (c >= 0) {
                     PosT A, P;
-                    cell_geom<PosT, PosT>(
-                        t, Xc, cn[i], [&](int k) { return rowl[base + k]; }, grb[i], A, P,
-                        T1 && o.t1_enable != 0, lmin2p, B.t1_list, &s_cnt);
+                    auto corner_at = [&](int k) { return rowl[base + k]; };
+                    cell_geom_flat<PosT>(t, Xc, cn[i], corner_at, grb[i], A, P,
+                                         T1 && o.t1_enable != 0, lmin2p, B.t1_list, &s_cnt[par]);
                     st2(capl, c, (M)((PosT)2 * ka[i] * (A - a0[i])),
                         (M)((PosT)2 * kp[i] * (P - p0[i])));
                 }
             }
             __syncthreads();
+            bool bad_t1 = false;
             if (T1) {
-                const int ncand = (int)s_cnt;
+                const int ncand = (int)s_cnt[par];
+                // the other counter was last read before the previous step's
+                // closing barrier and is next added to after this one's
+                if (tid == 0) s_cnt[par ^ 1] = 0u;
                 if (ncand > 0) {
                     const int64_t swaps0 = st.n_t1;
                     batch_t1_pass_lds<PosT, M>(&B, Xc, capl, ncand, o.l_min, o.l_new, sort_buf,
@@ -846,6 +851,7 @@ __global__ __launch_bounds__(kRelaxLdsThreads) void k_batch_relax_lds(
                     // coefficients, both in LDS already
                     if (st.n_t1 != swaps0) load_topology();
                     __syncthreads();
+                    bad_t1 = st.bad_t1 != 0;
                 }
             }
             // nudge gradient at the own vertices (kept for the vertex pass)
@@ -899,46 +905,54 @@ __global__ __launch_bounds__(kRelaxLdsThreads) void k_batch_relax_lds(
                     st2(Xn, v, (PosT)((double)xi + o.eta * gx), (PosT)((double)yi + o.eta * gy));
                 }
             }
-            const double m = block_max(mf, sh);
-            if (tid == 0) {
-                st.iter += 1;
-                st.last_mf = m;
-                if (st.bad_t1) {
-                    st.done = 1;
-                    st.status = VTX_E_CAPACITY;
-                    st.result_buf = cur;
-                } else if (!(m <= 1.7976931348623157e308)) {
-                    st.done = 1;
-                    st.status = VTX_E_NONFINITE;
-                    st.result_buf = cur;
-                } else {
-                    st.count = m < o.tol ? st.count + 1 : 0;
-                    if (st.count >= o.patience) {
-                        st.done = 1;
-                        st.status = VTX_CONVERGED;
-                        st.result_buf = cur;
-                    } else if (st.iter >= o.max_iter) {
-                        st.done = 1;
-                        st.status = VTX_NOT_CONVERGED;
-                        st.result_buf = cur ^ 1;
-                    }
+            // max |F| (never NaN: a NaN force counts as +inf) and the
+            // decision, taken alike by every thread
+            mf = wave_max_plain(mf);
+            if ((tid & 63) == 0) s_max[par][tid >> 6] = mf;
+            __syncthreads();
+            double m = 0.0;
+            for (int w = 0; w < nw; ++w) m = fmax(m, s_max[par][w]);
+            ++iter;
+            last_mf = m;
+            int stop = 0;
+            if (bad_t1) {
+                stop = 1;
+                status = VTX_E_CAPACITY;
+                result_buf = cur;
+            } else if (!(m <= 1.7976931348623157e308)) {
+                stop = 1;
+                status = VTX_E_NONFINITE;
+                result_buf = cur;
+            } else {
+                count = m < o.tol ? count + 1 : 0;
+                if (count >= o.patience) {
+                    stop = 1;
+                    status = VTX_CONVERGED;
+                    result_buf = cur;
+                } else if (iter >= o.max_iter) {
+                    stop = 1;
+                    status = VTX_NOT_CONVERGED;
+                    result_buf = cur ^ 1;
                 }
             }
-            __syncthreads();
-            if (st.done) break;
+            if (__builtin_amdgcn_readfirstlane(stop)) break;
             cur ^= 1;
         }
-        const PosT *Xr = st.result_buf ? X1 : X0;
+        if (tid == 0) {
+            st.iter = iter;
+            st.last_mf = last_mf;
+            st.status = status;
+        }
+        const PosT *Xr = result_buf ? X1 : X0;
         for (int k = tid; k < 2 * nv; k += bd) ((PosT *)B.X)[k] = Xr[k];
         __syncthreads();
         batch_relax_result<PosT>(B, t, p, st, sh, res, idx);
-        __syncthreads();
     }
 }
 
 // Persistent batched relaxation (Methods, "Simulation engine", per tissue):
-// each workgroup takes tissues from a device queue (largest first) and runs
-// the whole gradient-descent loop of one tissue with workgroup barriers
+// workgroup b takes the b-th largest tissue and runs the whole
+// gradient-descent loop of one tissue with workgroup barriers
 // only.  An iteration is the cell pass (coefficients, short-edge flags), the
 // T1 pass if any edge was flagged, the mean of the nudge gradient (EP), the
 // vertex pass with the step into the other position buffer, and the
@@ -947,25 +961,18 @@ __global__ __launch_bounds__(kRelaxLdsThreads) void k_batch_relax_lds(
 // vtx_relax.  The returned state is copied back into the caller's buffer.
 template <typename PosT, typename M>
 __global__ __launch_bounds__(1024) void k_batch_relax(const BatchItem *__restrict__ items,
-                                                      const int32_t *__restrict__ order, int n,
-                                                      unsigned int *queue, BatchOpts o,
-                                                      vtx_relax_result *res) {
+                                                      const int32_t *__restrict__ order,
+                                                      BatchOpts o, vtx_relax_result *res) {
     __shared__ int32_t sort_buf[kT1SortCap];
     __shared__ int32_t extra[kT1Extra];
     __shared__ int32_t scan[1024];
     __shared__ double sh[16];
     __shared__ unsigned int s_cnt;
-    __shared__ int s_item;
     __shared__ RelaxState st;
     __shared__ double s_mean[2];
     const M lmin2 = (M)(o.l_min * o.l_min * (1.0 + 1e-4));
-    for (;;) {
-        if (threadIdx.x == 0) s_item = (int)atomicAdd(queue, 1u);
-        __syncthreads();
-        const int slot = s_item;
-        __syncthreads();
-        if (slot >= n) return;
-        const int idx = order[slot];
+    {
+        const int idx = order[blockIdx.x];
         const BatchItem &B = items[idx];
         const DevTissue &t = B.t;
         const DevParams<PosT> p = to_dev<PosT>(B.p);
@@ -1071,7 +1078,6 @@ __global__ __launch_bounds__(1024) void k_batch_relax(const BatchItem *__restric
                 ((PosT *)B.X)[k] = ((PosT *)B.xbuf)[k];
         __syncthreads();
         batch_relax_result<PosT>(B, t, p, st, sh, res, idx);
-        __syncthreads();
     }
 }
 
@@ -1087,21 +1093,8 @@ ParamsRaw raw_params(const vtx_params &q) {
 
 int hip_fail(hipError_t e) { return set_error(VTX_E_HIP, hipGetErrorString(e)); }
 
-// Capture (queue reset + one persistent launch) as a graph and run it.
-template <typename Launch>
-int run_graph(vtx_batch b, hipStream_t s, Launch launch) {
-    hipGraph_t g = nullptr;
-    hipGraphExec_t ge = nullptr;
-    hipError_t e = hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal);
-    if (e != hipSuccess) return hip_fail(e);
-    hipLaunchKernelGGL(k_reset_queue, dim3(1), dim3(1), 0, b->cap_stream, b->queue);
-    launch(b->cap_stream);
-    e = hipStreamEndCapture(b->cap_stream, &g);
-    if (e != hipSuccess) return hip_fail(e);
-    e = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
-    if (e == hipSuccess) e = hipGraphLaunch(ge, s);
-    if (ge) (void)hipGraphExecDestroy(ge);
-    if (g) (void)hipGraphDestroy(g);
+int launched() {
+    const hipError_t e = hipGetLastError();
     return e == hipSuccess ? VTX_OK : hip_fail(e);
 }
 
@@ -1135,10 +1128,9 @@ int launch_batch_cg_t(vtx_batch b, const GradItem *gi, const int32_t *order, int
                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return hip_fail(e);
     }
-    return run_graph(b, s, [&](hipStream_t cs) {
-        hipLaunchKernelGGL((k_batch_cg<PosT, M, MAXT>), dim3(n), dim3(block_threads),
-                           (size_t)lds, cs, gi, order, n, b->queue, go, b->gres_d, lds);
-    });
+    hipLaunchKernelGGL((k_batch_cg<PosT, M, MAXT>), dim3(n), dim3(block_threads), (size_t)lds, s,
+                       gi, order, go, b->gres_d, lds);
+    return launched();
 }
 
 // Workgroup size of the batched adjoint when the caller leaves it open: 512
@@ -1208,10 +1200,10 @@ int plan_mb(vtx_batch b, int block_threads, int *K, int *n_groups, int *lds) {
     return VTX_OK;
 }
 
-// Dynamic LDS for k_batch_relax_lds if every tissue of the batch fits it
+// Dynamic LDS for k_batch_relax_lds if every one of the n tissues fits it
 // (*lds > 0), else *lds = 0.
 template <typename PosT, typename M, bool T1>
-int relax_lds_plan(vtx_batch b, int *lds) {
+int relax_lds_plan_t(const DevTissue *const *ts, size_t n, int *lds) {
     *lds = 0;
     int dev = 0, lds_max = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -1224,8 +1216,8 @@ int relax_lds_plan(vtx_batch b, int *lds) {
     if (e != hipSuccess) return hip_fail(e);
     const int64_t budget = (int64_t)lds_max - (int64_t)fa.sharedSizeBytes;
     int64_t need = 0;
-    for (size_t i = 0; i < b->ts.size(); ++i) {
-        const DevTissue &d = tissue_dev(b->ts[i]);
+    for (size_t i = 0; i < n; ++i) {
+        const DevTissue &d = *ts[i];
         const int64_t nb = relax_lds_bytes<PosT, M>(d.n_vert, d.n_cell, d.n_he);
         if (d.n_cell > (int64_t)kRelaxLdsK * kRelaxLdsThreads ||
             d.n_vert > 2 * (int64_t)kRelaxLdsK * kRelaxLdsThreads || nb > budget)
@@ -1237,6 +1229,61 @@ int relax_lds_plan(vtx_batch b, int *lds) {
     if (e != hipSuccess) return hip_fail(e);
     *lds = (int)need;
     return VTX_OK;
+}
+
+int relax_lds_plan(int mode, bool t1, const DevTissue *const *ts, size_t n, int *lds) {
+    if (mode == VTX_F32)
+        return t1 ? relax_lds_plan_t<float, float, true>(ts, n, lds)
+                  : relax_lds_plan_t<float, float, false>(ts, n, lds);
+    if (mode == VTX_F64)
+        return t1 ? relax_lds_plan_t<double, double, true>(ts, n, lds)
+                  : relax_lds_plan_t<double, double, false>(ts, n, lds);
+    return t1 ? relax_lds_plan_t<double, float, true>(ts, n, lds)
+              : relax_lds_plan_t<double, float, false>(ts, n, lds);
+}
+
+int relax_lds_plan(vtx_batch b, int mode, bool t1, int *lds) {
+    std::vector<const DevTissue *> ts;
+    for (vtx_tissue t : b->ts) ts.push_back(&tissue_dev(t));
+    return relax_lds_plan(mode, t1, ts.data(), ts.size(), lds);
+}
+
+// Threads of k_batch_relax_lds for tissues of up to n_vert vertices: one per
+// vertex up to 512, so that a small tissue's barriers join few waves.  A
+// nudged relaxation always takes 512: its mean is summed over the
+// workgroup, and its rounding does not depend on the batch's sizes.
+int relax_lds_threads(int64_t n_vert, bool nudged) {
+    return nudged ? kRelaxLdsThreads
+                  : (int)std::min<int64_t>(kRelaxLdsThreads, (n_vert + 63) / 64 * 64);
+}
+int relax_lds_threads(vtx_batch b, bool nudged) {
+    return relax_lds_threads(tissue_size(b->ts[b->order[0]]), nudged);
+}
+
+void launch_relax_lds(int mode, bool t1, const BatchItem *it, const int32_t *order, int n,
+                      int threads, int lds, const BatchOpts &bo, vtx_relax_result *res,
+                      hipStream_t s) {
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(n), dim3(threads), (size_t)lds, s, it, order, bo, res);
+    };
+    if (mode == VTX_F32)
+        t1 ? go(k_batch_relax_lds<float, float, true>) : go(k_batch_relax_lds<float, float, false>);
+    else if (mode == VTX_F64)
+        t1 ? go(k_batch_relax_lds<double, double, true>)
+           : go(k_batch_relax_lds<double, double, false>);
+    else
+        t1 ? go(k_batch_relax_lds<double, float, true>)
+           : go(k_batch_relax_lds<double, float, false>);
+}
+
+void launch_batch_relax(int mode, const BatchItem *it, const int32_t *order, int n, int threads,
+                        const BatchOpts &bo, vtx_relax_result *res, hipStream_t s) {
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(n), dim3(threads), 0, s, it, order, bo, res);
+    };
+    if (mode == VTX_F32) go(k_batch_relax<float, float>);
+    else if (mode == VTX_F64) go(k_batch_relax<double, double>);
+    else go(k_batch_relax<double, float>);
 }
 
 // The split schedule: each tissue over K cooperating workgroups
@@ -1274,17 +1321,8 @@ int relax_split(vtx_batch b, int mode, const BatchItem *it, const BatchOpts &bo,
                        hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return hip_fail(e);
     const int m = (int)rest.size();
-    return run_graph(b, s, [&](hipStream_t cs) {
-        if (mode == VTX_F32)
-            hipLaunchKernelGGL((k_batch_relax<float, float>), dim3(m), dim3(1024), 0, cs, it,
-                               b->order2_d, m, b->queue, bo, b->res_d);
-        else if (mode == VTX_F64)
-            hipLaunchKernelGGL((k_batch_relax<double, double>), dim3(m), dim3(1024), 0, cs, it,
-                               b->order2_d, m, b->queue, bo, b->res_d);
-        else
-            hipLaunchKernelGGL((k_batch_relax<double, float>), dim3(m), dim3(1024), 0, cs, it,
-                               b->order2_d, m, b->queue, bo, b->res_d);
-    });
+    launch_batch_relax(mode, it, b->order2_d, m, 1024, bo, b->res_d, s);
+    return launched();
 }
 
 // The batch's items for positions X (nudge beta towards Xt, or along g_lin)
@@ -1351,45 +1389,19 @@ int batch_relax_run(vtx_batch b, int mode, void *const *X, const vtx_params *p,
         const int rc = relax_split(b, mode, it, bo, n, split_K, s);
         if (rc) return rc;
     } else if (block_threads == 0 || block_threads == kRelaxLdsThreads) {
-        int rc;
-        if (mode == VTX_F32)
-            rc = t1 ? relax_lds_plan<float, float, true>(b, &lds)
-                    : relax_lds_plan<float, float, false>(b, &lds);
-        else if (mode == VTX_F64)
-            rc = t1 ? relax_lds_plan<double, double, true>(b, &lds)
-                    : relax_lds_plan<double, double, false>(b, &lds);
-        else
-            rc = t1 ? relax_lds_plan<double, float, true>(b, &lds)
-                    : relax_lds_plan<double, float, false>(b, &lds);
+        const int rc = relax_lds_plan(b, mode, t1, &lds);
         if (rc) return rc;
     }
     if (block_threads == 0) block_threads = 1024;
-    auto launch_lds = [&](auto kern, hipStream_t cs) {
-        hipLaunchKernelGGL(kern, dim3(n), dim3(kRelaxLdsThreads), (size_t)lds, cs, it, b->order_d,
-                           n, b->queue, bo, b->res_d);
-    };
-    int rc = split_K > 0 ? VTX_OK : run_graph(b, s, [&](hipStream_t cs) {
-        const dim3 grid(n), block(block_threads);
-        if (lds > 0) {
-            if (mode == VTX_F32)
-                t1 ? launch_lds(k_batch_relax_lds<float, float, true>, cs)
-                   : launch_lds(k_batch_relax_lds<float, float, false>, cs);
-            else if (mode == VTX_F64)
-                t1 ? launch_lds(k_batch_relax_lds<double, double, true>, cs)
-                   : launch_lds(k_batch_relax_lds<double, double, false>, cs);
-            else
-                t1 ? launch_lds(k_batch_relax_lds<double, float, true>, cs)
-                   : launch_lds(k_batch_relax_lds<double, float, false>, cs);
-        } else if (mode == VTX_F32)
-            hipLaunchKernelGGL((k_batch_relax<float, float>), grid, block, 0, cs, it, b->order_d,
-                               n, b->queue, bo, b->res_d);
-        else if (mode == VTX_F64)
-            hipLaunchKernelGGL((k_batch_relax<double, double>), grid, block, 0, cs, it,
-                               b->order_d, n, b->queue, bo, b->res_d);
+    int rc = VTX_OK;
+    if (split_K == 0) {
+        if (lds > 0)
+            launch_relax_lds(mode, t1, it, b->order_d, n, relax_lds_threads(b, beta != 0.0), lds,
+                             bo, b->res_d, s);
         else
-            hipLaunchKernelGGL((k_batch_relax<double, float>), grid, block, 0, cs, it, b->order_d,
-                               n, b->queue, bo, b->res_d);
-    });
+            launch_batch_relax(mode, it, b->order_d, n, block_threads, bo, b->res_d, s);
+        rc = launched();
+    }
     if (rc) return rc;
     // The fused evaluation's tables of the tissues that made exchanges, in
     // one launch: one launch per tissue ran them one after another, 190-210 us
@@ -1407,6 +1419,19 @@ int batch_relax_run(vtx_batch b, int mode, void *const *X, const vtx_params *p,
 
 constexpr int kPlanDoesNotApply = 1;
 
+// Item and result of a one-workgroup launch of a single tissue, in the
+// tissue's workspace; written by a kernel (in stream order, and without a
+// copy from host memory that would have to outlive the call).
+struct OneSlot {
+    BatchItem item;
+    vtx_relax_result res;
+};
+static_assert(sizeof(OneSlot) <= kOneBytes, "workspace slot");
+
+__global__ void k_put_item(BatchItem item, BatchItem *dst) {
+    if (threadIdx.x == 0) *dst = item;
+}
+
 // Centred EP's two nudged relaxations (+beta and -beta about X*, from Xp
 // and Xm) as one launch of 2n items when every tissue takes the
 // LDS-resident kernel: there the two items of a tissue share no global
@@ -1419,10 +1444,7 @@ int batch_relax_pm(vtx_batch b, int mode, void *const *Xp, void *const *Xm, cons
                    hipStream_t s) {
     if (o->t1_enable || (block_threads != 0 && block_threads != kRelaxLdsThreads))
         return kPlanDoesNotApply;
-    int lds = 0, rc;
-    if (mode == VTX_F32) rc = relax_lds_plan<float, float, false>(b, &lds);
-    else if (mode == VTX_F64) rc = relax_lds_plan<double, double, false>(b, &lds);
-    else rc = relax_lds_plan<double, float, false>(b, &lds);
+    int lds = 0, rc = relax_lds_plan(b, mode, false, &lds);
     if (rc) return rc;
     if (lds == 0) return kPlanDoesNotApply;
     const int n = (int)b->ts.size();
@@ -1434,16 +1456,9 @@ int batch_relax_pm(vtx_batch b, int mode, void *const *Xp, void *const *Xm, cons
     if (e != hipSuccess) return hip_fail(e);
     const BatchOpts bo{o->eta, o->tol, o->l_min, o->l_new, o->patience, o->max_iter, 0};
     const BatchItem *it = (const BatchItem *)b->items;
-    auto launch = [&](auto kern, hipStream_t cs) {
-        hipLaunchKernelGGL(kern, dim3(2 * n), dim3(kRelaxLdsThreads), (size_t)lds, cs, it,
-                           b->order_d, 2 * n, b->queue, bo, b->res_d);
-    };
-    rc = run_graph(b, s, [&](hipStream_t cs) {
-        if (mode == VTX_F32) launch(k_batch_relax_lds<float, float, false>, cs);
-        else if (mode == VTX_F64) launch(k_batch_relax_lds<double, double, false>, cs);
-        else launch(k_batch_relax_lds<double, float, false>, cs);
-    });
-    if (rc) return rc;
+    launch_relax_lds(mode, false, it, b->order_d, 2 * n, relax_lds_threads(b, true), lds, bo,
+                     b->res_d, s);
+    if ((rc = launched())) return rc;
     std::vector<vtx_relax_result> r(2 * (size_t)n);
     e = hipMemcpyAsync(r.data(), b->res_d, sizeof(vtx_relax_result) * 2 * n,
                        hipMemcpyDeviceToHost, s);
@@ -1479,6 +1494,29 @@ int check_relax_opts(const vtx_relax_opts *o) {
 
 }  // namespace
 
+namespace vtx {
+int relax_one(const DevTissue &t, const Workspace &w, int mode, void *X, const ParamsRaw &p,
+              const RelaxArgs &ra, double tol, int64_t patience, int64_t max_iter, hipStream_t s,
+              const vtx_relax_result **res_d) {
+    *res_d = nullptr;
+    int lds = 0;
+    const bool t1 = ra.t1_enable != 0;
+    const DevTissue *tp = &t;
+    const int rc = relax_lds_plan(mode, t1, &tp, 1, &lds);
+    if (rc || lds == 0) return rc;
+    OneSlot *slot = (OneSlot *)w.one;
+    const BatchItem item{t, X, w.xbuf, w.cap, w.t1_list, p, ra.nudge == 1 ? ra.X_target : nullptr,
+                         ra.nudge == 2 ? (const double *)ra.g_lin : nullptr,
+                         ra.nudge ? ra.beta : 0.0};
+    hipLaunchKernelGGL(k_put_item, dim3(1), dim3(64), 0, s, item, &slot->item);
+    const BatchOpts bo{ra.eta, tol, ra.l_min, ra.l_new, patience, max_iter, ra.t1_enable};
+    launch_relax_lds(mode, t1, &slot->item, nullptr, 1,
+                     relax_lds_threads(t.n_vert, ra.nudge != 0), lds, bo, &slot->res, s);
+    *res_d = &slot->res;
+    return launched();
+}
+}  // namespace vtx
+
 extern "C" {
 
 int vtx_batch_create(const vtx_tissue *ts, int32_t n, vtx_batch *out) {
@@ -1501,7 +1539,6 @@ int vtx_batch_create(const vtx_tissue *ts, int32_t n, vtx_batch *out) {
     if (e == hipSuccess) e = hipMalloc(&b->gitems, sizeof(GradItem) * n);
     if (e == hipSuccess) e = hipMalloc((void **)&b->xm_list, sizeof(void *) * n);
     if (e == hipSuccess) e = hipMalloc((void **)&b->order_d, sizeof(int32_t) * 2 * n);
-    if (e == hipSuccess) e = hipMalloc((void **)&b->queue, sizeof(unsigned int));
     if (e == hipSuccess) e = hipMalloc((void **)&b->res_d, sizeof(vtx_relax_result) * 2 * n);
     if (e == hipSuccess) e = hipMalloc((void **)&b->gres_d, sizeof(vtx_grad_result) * n);
     if (e == hipSuccess) e = hipMalloc(&b->mb_groups, mb_group_bytes() * n);
@@ -1522,7 +1559,6 @@ int vtx_batch_create(const vtx_tissue *ts, int32_t n, vtx_batch *out) {
     if (e == hipSuccess)
         e = hipMemcpy(b->tile_job_of, job_of.data(), sizeof(int32_t) * job_of.size(),
                       hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking);
     if (e != hipSuccess) {
         vtx_batch_destroy(b);
         return hip_fail(e);
@@ -1534,11 +1570,10 @@ int vtx_batch_create(const vtx_tissue *ts, int32_t n, vtx_batch *out) {
 int vtx_batch_destroy(vtx_batch b) {
     if (!b) return set_error(VTX_E_ARG, "null batch");
     (void)hipDeviceSynchronize();
-    void *ptrs[] = {b->items, b->gitems, b->xm_list, b->order_d, b->queue, b->res_d, b->gres_d,
+    void *ptrs[] = {b->items, b->gitems, b->xm_list, b->order_d, b->res_d, b->gres_d,
                     b->mb_groups, b->order2_d, b->tile_jobs, b->tile_job_of};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
-    if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
     delete b;
     return VTX_OK;
 }

@@ -71,6 +71,63 @@ __device__ __forceinline__ void cell_geom(const DevTissue &t, const PosT *__rest
     P = per;
 }
 
+// The same area, perimeter and short-edge list, without a branch per corner:
+// a row is read as if it went on with copies of its corner 0, so the step
+// after the last corner is the closing edge and the ones after it add zero
+// to both sums (exactly).  The branches of cell_geom keep the square roots of
+// successive corners in separate basic blocks, one dependent chain after
+// another; here six of them are in flight at once.  For kernels with one or
+// two waves per SIMD, where that latency is the time of the cell pass; the
+// evaluation of large tissues, with many waves to hide it, keeps cell_geom
+// and does not compute the copies.
+template <typename PosT, bool NOIMG = false, typename CornerAt>
+__device__ __forceinline__ void cell_geom_flat(const DevTissue &t, const PosT *__restrict__ X,
+                                               int n, CornerAt corner_at, int row_base, PosT &A,
+                                               PosT &P, bool det, PosT lmin2, int32_t *list,
+                                               unsigned int *count) {
+    const PosT Lx = (PosT)t.Lx, Ly = (PosT)t.Ly;
+    const int32_t w0 = corner_at(0);
+    const auto p0 = ld2(X, id_of(w0));
+    const int v0 = id_of(w0);
+    PosT px = 0, py = 0, a = 0, per = 0;
+    int vprev = v0;
+    uint32_t shorts = 0;
+    auto step = [&](int k, int32_t wk, typename Vec2<PosT>::type qk) {
+        const PosT rx = pdiff<PosT>(qk.x, p0.x, NOIMG ? 0 : ox_of(wk), Lx);
+        const PosT ry = pdiff<PosT>(qk.y, p0.y, NOIMG ? 0 : oy_of(wk), Ly);
+        const PosT dx = rx - px, dy = ry - py;
+        const PosT l2 = dx * dx + dy * dy;
+        a += px * ry - py * rx;
+        per += len_of(l2);
+        if (det) {
+            const int v = id_of(wk);
+            if (k < 32) shorts |= (l2 < lmin2 && vprev < v ? 1u : 0u) << k;
+            else if (l2 < lmin2 && vprev < v) list[atomicAdd(count, 1u)] = row_base + k - 1;
+            vprev = v;
+        }
+        px = rx;
+        py = ry;
+    };
+    constexpr int U = 6;
+    int32_t w[U];
+    typename Vec2<PosT>::type q[U];
+#pragma unroll
+    for (int k = 1; k <= U; ++k) w[k - 1] = corner_at(k < n ? k : 0);
+#pragma unroll
+    for (int k = 1; k <= U; ++k) q[k - 1] = ld2(X, id_of(w[k - 1]));
+#pragma unroll
+    for (int k = 1; k <= U; ++k) step(k, w[k - 1], q[k - 1]);
+    for (int k = U + 1; k <= n; ++k) {
+        const int32_t wk = corner_at(k < n ? k : 0);
+        step(k, wk, ld2(X, id_of(wk)));
+    }
+    if (det)
+        for (; shorts; shorts &= shorts - 1)
+            list[atomicAdd(count, 1u)] = row_base + __builtin_ctz(shorts) - 1;
+    A = (PosT)0.5 * a;
+    P = per;
+}
+
 // ---------------------------------------------------------------- vertex
 // Force on vertex i from its star (outgoing half-edges h_k = i -> j_k,
 // sector cell a_k = face(h_k), edge e_k).  With d_k = x_{j_k} - x_i,

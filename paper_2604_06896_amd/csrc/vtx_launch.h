@@ -66,4 +66,13 @@ void launch_dot_pos(const Workspace &w, int mode, int nv, const double *g, const
 void launch_mean_pos(const Workspace &w, int mode, int nv, const void *a, double *mean_out,
                      hipStream_t s);
 
+// Bytes of Workspace::one.
+constexpr size_t kOneBytes = 1024;
+// Relaxation of a tissue that fits one workgroup's LDS (vtx_batch.hip):
+// launches it and sets *res_d to its (device) result, or sets it to NULL,
+// having launched nothing, where the tissue does not fit.
+int relax_one(const DevTissue &t, const Workspace &w, int mode, void *X, const ParamsRaw &p,
+              const RelaxArgs &ra, double tol, int64_t patience, int64_t max_iter, hipStream_t s,
+              const vtx_relax_result **res_d);
+
 }  // namespace vtx

@@ -40,3 +40,51 @@ def test_tile_tables_follow_a_batched_relaxation(vtx, mode):
             F2, _ = T.vertex_forces(X, P, T.cell_coeffs(X, P, mode=mode), mode=mode)
             assert torch.equal(F, F2)
     assert res[-1]["n_t1"] == 0 and any(r["n_t1"] > 0 for r in res)
+
+
+@pytest.mark.parametrize("mode", ["f32", "mixed", "f64"])
+@pytest.mark.parametrize("n_cell", [20, 32, 33, 64, 129, 255, 257, 513, 1000])
+def test_one_workgroup_relaxation_matches_the_oracle(vtx, oracle, mode, n_cell):
+    """Tissue.relax of a tissue that fits one workgroup (a wave for every 64
+    vertices, at most eight; one cell per thread up to 512 cells, then two),
+    with T1, at sizes around those steps.  In FP64 60 steps agree with the
+    oracle to rounding (each step adds at most a few ulp of the box side);
+    the reduced modes to 60 steps of their force rounding."""
+    V = vtx
+    t = g.random_tissue(n_cell, seed=300 + n_cell)
+    p = g.uniform_params(t, P0=3.7, lam=0.1)
+    T = V.Tissue.from_tissue(t)
+    X = _dev(t.X, V.pos_dtype(mode))
+    opts = dict(eta=3e-3, tol=0.0, max_iter=60, t1_enable=True, l_min=0.02)
+    r = T.relax(X, V.Params(KA=1.0, A0=1.0, KP=1.0, P0=3.7, lam=0.1), mode=mode, **opts)
+    m = oracle.Mesh.from_tissue(t)
+    Xo = t.X.astype(np.float32).astype(np.float64) if mode == "f32" else t.X.copy()
+    ro = oracle.relax(m, Xo, p, patience=1, **opts)
+    assert r["iters"] == ro["iters"] == 60
+    if mode != "f64":
+        # an edge within rounding of the threshold may be handled a step apart
+        same = np.array_equal(T.topology(), m.he)
+        if not same:
+            return
+    assert np.array_equal(T.topology(), m.he)
+    assert (r["n_t1"], r["n_stretch"]) == (ro["n_t1"], ro["n_stretch"])
+    ulp = {"f64": 2.0 ** -52, "mixed": 2.0 ** -23 * 3e-3, "f32": 2.0 ** -23}[mode]
+    err = np.abs(X.cpu().numpy() - Xo).max()
+    assert err <= 60 * 16 * ulp * max(t.Lx, 20.0), err
+
+
+@pytest.mark.parametrize("scale", [1e-60, 1e-3, 1.0, 1e60])
+def test_fp64_lengths_over_the_range(vtx, oracle, scale):
+    """Forces and energy of a tissue scaled over the exponent range of the
+    FP64 lengths (areas up to scale^2, their squares up to scale^4)."""
+    V = vtx
+    t = g.random_tissue(100, seed=7)
+    ts = g.Tissue(t.he, t.X * scale, t.Lx * scale, t.Ly * scale)
+    p = g.uniform_params(ts, A0=scale ** 2, P0=3.7 * scale, lam=0.1 * scale,
+                         KA=scale ** -2)
+    T = V.Tissue.from_tissue(ts)
+    P = V.Params(KA=scale ** -2, A0=scale ** 2, KP=1.0, P0=3.7 * scale, lam=0.1 * scale)
+    E, F, _ = T.energy_forces(_dev(ts.X), P)
+    Eo, Fo = oracle.energy_forces(oracle.Mesh.from_tissue(ts), ts.X, p)
+    assert abs(E.item() / Eo - 1.0) < 1e-12
+    assert np.abs(F.cpu().numpy() - Fo).max() / np.abs(Fo).max() < 1e-12
