@@ -274,7 +274,9 @@ int vtx_hvp(vtx_tissue t, int32_t mode, const void *X, const vtx_params *p, cons
  *     CG stops with VTX_CG_NEG_CURVATURE if H is not positive definite.
  *   ADJOINT_MINRES: the same with MINRES (Paige-Saunders; the paper's
  *     solver, Methods, ID), which needs H symmetric only; cg_tol bounds the
- *     recursive residual |P b - H mu| / |P b|.
+ *     recursive residual |P b - H mu| / |P b|.  With either solver an FP64
+ *     tissue of at most 1024 cells is solved by one workgroup, others by
+ *     launches on the whole GPU.
  *   EP_CENTRED: relaxes E + (beta/2) C and E - (beta/2) C from X_star and
  *     returns (dE/dtheta(X+) - dE/dtheta(X-)) / beta, where C is the v2v
  *     cost to X_target when given (device, element type of X) and the
@@ -382,8 +384,11 @@ int vtx_batch_autotune(vtx_batch b, int32_t mode, void *const *X, const vtx_para
  * keeps them there, and with workgroups of at most 512 threads a CG solve of
  * a tissue with at most two cells and four vertices per thread also keeps
  * its corner rows in LDS and its stars, solution and residual in registers
- * (same arithmetic in every form).  0 takes 512 threads when every tissue
- * has that form, else 1024.  EP_CENTRED / EP_FORWARD: batched nudged
+ * (same arithmetic in every form).  An FP64 batch whose tissues all have at
+ * most 1024 cells, with block_threads 512 or 0, runs either solver in a
+ * kernel that also keeps the geometry of the Hessian-vector product (its
+ * sums are rounded in another order).  Otherwise 0 takes 512 threads when
+ * every tissue has the form above, else 1024.  EP_CENTRED / EP_FORWARD: batched nudged
  * relaxations (vtx_batch_relax with a per-tissue nudge, workgroups of
  * `block_threads`; 0 takes the LDS-resident relaxation of vtx_batch_relax
  * when every tissue fits it, else 1024 threads) and one estimate launch.

@@ -711,18 +711,27 @@ int vtx_v2v(vtx_tissue t, int32_t mode, const void *X, const void *X_target, dou
 }
 
 // Solves H x = P b at X (H restricted to the zero-mean subspace) by CG or
-// MINRES on the device, x left projected in the first workspace vector.
+// MINRES on the device, x left projected in the first workspace vector, then
+// contracts it with the mixed derivatives of theta into g unless g is NULL.
 static int solve_hessian(vtx_tissue t, int mode, const void *X, const vtx_params *p,
-                         const double *b, bool minres, double tol, int64_t max_iter,
-                         hipStream_t s, vtx_grad_result *r) {
+                         const double *b, bool minres, double tol, int64_t max_iter, int theta,
+                         double *g, hipStream_t s, vtx_grad_result *r) {
     const int nv = (int)t->n_vert;
+    // an FP64 tissue that fits one workgroup's LDS is solved there
+    const vtx_grad_result *one = nullptr;
+    int rc = solve_one(t->d, t->w, mode, X, raw(p), b, minres, tol, max_iter, theta, g, s, &one);
+    if (rc) return rc;
+    if (one) {
+        HIPCHK(hipMemcpyAsync(r, one, sizeof *r, hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
+        return VTX_OK;
+    }
     launch_cell_coeffs(t->d, t->w, mode, X, raw(p), s);
     LoopCtl c{};
     c.status = VTX_CG_MAXITER;
     c.tol = tol;
     c.max_iter = max_iter;
     c.solver = minres ? 1 : 0;
-    int rc;
     if ((rc = reset_ctl(t, 0, c, s))) return rc;
     if (minres) launch_minres_init(t->w, nv, b, s);
     else launch_cg_init(t->w, nv, b, s);
@@ -737,6 +746,7 @@ static int solve_hessian(vtx_tissue t, int mode, const void *X, const vtx_params
     }
     const LoopCtl &h = t->w.ctl_host[0];
     launch_project(t->w, nv, t->w.cg, s);
+    if (g) launch_contract(t->d, mode, X, raw(p), theta, t->w.cg, g, s);
     r->cg_iters = h.cg_iter;
     r->cg_rel_res = h.rel_res;
     r->status = h.status;
@@ -757,10 +767,8 @@ int vtx_param_grad(vtx_tissue t, int32_t mode, const void *X_star, const vtx_par
         if (!dC_dX) return fail(VTX_E_ARG, "the adjoint needs dC_dX");
         if (!(o->cg_tol > 0) || o->cg_max_iter < 1) return fail(VTX_E_ARG, "bad Krylov options");
         if ((rc = solve_hessian(t, mode, X_star, p, dC_dX, o->method == VTX_GRAD_ADJOINT_MINRES,
-                                o->cg_tol, o->cg_max_iter, s, &r)))
+                                o->cg_tol, o->cg_max_iter, o->theta, dC_dtheta, s, &r)))
             return rc;
-        launch_contract(t->d, mode, X_star, raw(p), o->theta, t->w.cg, dC_dtheta, s);
-        if ((rc = check_launch("adjoint contraction"))) return rc;
         HIPCHK(hipStreamSynchronize(s));
     } else if (o->method == VTX_GRAD_EP_CENTRED || o->method == VTX_GRAD_EP_FORWARD) {
         const bool centred = o->method == VTX_GRAD_EP_CENTRED;
@@ -806,7 +814,7 @@ int vtx_param_sens(vtx_tissue t, int32_t mode, const void *X_star, const vtx_par
     launch_sens_rhs(t->d, t->w, X_star, raw(p), o->theta, d, rhs, s);
     vtx_grad_result r{};
     int rc = solve_hessian(t, mode, X_star, p, rhs, o->method == VTX_GRAD_ADJOINT_MINRES,
-                           o->cg_tol, o->cg_max_iter, s, &r);
+                           o->cg_tol, o->cg_max_iter, o->theta, nullptr, s, &r);
     if (rc) return rc;
     launch_dot_pos(t->w, VTX_F64, nv, dC_dX, t->w.cg, dC_dd, s);
     if (dX_dd)

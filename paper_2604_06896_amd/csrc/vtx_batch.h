@@ -44,7 +44,7 @@ struct GradItem {
     double *cg;          // x, r, q, Aq: 4 x [n_vert][2]
     void *cap;
     void *aux;
-    double *g;           // output [n_edge] or [n_cell]
+    double *g;           // output [n_edge] or [n_cell] (NULL: the solution only)
 };
 
 struct GradOpts {

@@ -508,6 +508,375 @@ __global__ __launch_bounds__(MAXT) void k_batch_cg(const GradItem *__restrict__ 
     }
 }
 
+// ------------------------------------------- FP64 Krylov solve in one CU
+// Threads of k_solve_lds at most, and its vertices and cells per thread.
+constexpr int kSolveThreads = 512;
+constexpr int kSolveKV = 2048 / kSolveThreads;
+constexpr int kSolveK = kSolveKV / 2;
+constexpr int kSolveMaxVerts = kSolveKV * kSolveThreads;
+
+// LDS bytes of k_solve_lds: the vector multiplied, one pair per corner, and
+// one pair per cell.
+__host__ __device__ inline int64_t solve_lds_bytes(int64_t n_vert, int64_t n_cell, int64_t n_he) {
+    return 16 * (n_vert + n_he + n_cell);
+}
+
+// Sum over the workgroup, returned to every thread, with one barrier: `buf`
+// (16 doubles) must not be written again before another barrier of the
+// block.  The waves' sums are added in a fixed tree.
+__device__ __forceinline__ double solve_sum(double v, double *buf) {
+    v = wave_sum(v);
+    const int nw = (blockDim.x + 63) >> 6;
+    if ((threadIdx.x & 63) == 0) buf[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double a[kSolveThreads / 64];
+#pragma unroll
+    for (int w = 0; w < kSolveThreads / 64; ++w) a[w] = w < nw ? buf[w] : 0.0;
+#pragma unroll
+    for (int d = 1; d < kSolveThreads / 64; d *= 2)
+#pragma unroll
+        for (int w = 0; w + d < kSolveThreads / 64; w += 2 * d) a[w] += a[w + d];
+    return a[0];
+}
+
+// Solves H x = P b (CG or MINRES) for one FP64 tissue per workgroup, then the
+// contraction with the mixed derivatives, as k_batch_cg; for tissues of up
+// to 2048 vertices whose arrays fit the LDS.
+//
+// H stays fixed during the solve, so everything its product needs of the
+// positions is computed once and kept in the registers of the vertices'
+// threads: per star slot k the unit vector u_k of its edge, the length l_k,
+// tension over length, and half the pressure step.  The cell terms are
+// formed from the vertex side as well: with p_k = u_k . v_i and
+// c_k = l_k (u_k.y v_i.x - u_k.x v_i.y), vertex i adds (c_k - c_{k+1}) / 2 to
+// the area derivative and -(p_k + p_{k+1}) to the perimeter derivative of its
+// sector cell k.  A step writes these pairs to the cells' rows in LDS, adds
+// each row, and forms H v from the three sums and three neighbours of each
+// vertex:
+//   slots | rows -> (K_A dA, 2 K_P dP) | H v, v.Hv | x, r, r.r | v
+// with a barrier at each bar, about 70 FP64 operations per vertex where
+// recomputing the geometry took 290 with three roots (the corner geometry
+// from the cell side, 192 KB at 1000 cells, does not fit the LDS).  LDS
+// traffic is the larger half of what is left (430 KB a step at 1000 cells).
+// 64 tissues of 1000 cells to 1e-12: 9.63 -> 5.21 ms; one forward derivative
+// of 1000 cells, through four launches a step before: 15.4 -> 4.0 ms.  512
+// threads with four vertices each, not 1024 with two (7.0 and 6.0 ms: more
+// spills at 128 registers, and longer barriers); guards per vertex, not
+// clamped vertices without branches (5.5 and 4.6 ms).
+template <bool MINRES>
+__global__ __launch_bounds__(kSolveThreads) void k_solve_lds(const GradItem *__restrict__ items,
+                                                             const int32_t *__restrict__ order,
+                                                             GradOpts o, vtx_grad_result *res) {
+    constexpr int K = kSolveK, KV = kSolveKV;
+    extern __shared__ __align__(16) unsigned char lds_dyn[];
+    __shared__ double sh_a[16], sh_b[16];
+    __shared__ int s_scan[16];
+    const int idx = order ? order[blockIdx.x] : (int)blockIdx.x;
+    const GradItem &G = items[idx];
+    const DevTissue &t = G.t;
+    const DevParams<double> p = to_dev<double>(G.p);
+    const double *X = (const double *)G.X;
+    const int tid = threadIdx.x, bd = blockDim.x, nv = t.n_vert, nc = t.n_cell;
+    double2 *ql = (double2 *)lds_dyn;
+    double2 *slot = ql + nv;
+    double2 *aux = slot + t.n_he;
+    auto at = [&](const double2 *base, uint32_t byte) {
+        return *(const double2 *)((const unsigned char *)base + byte);
+    };
+    // the thread's cells: their rows' places in `slot`, (cA, cP) at X* into aux
+    int cid[K], cn[K], lrb[K];
+    double ka[K], kp[K];
+    cells_by_sides<K>(t, reinterpret_cast<int *>(ql), s_scan, cid);
+    int32_t *pos = reinterpret_cast<int32_t *>(slot);  // place of each half-edge's corner
+    int rows = 0;
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+        const int c = cid[i];
+        cn[i] = c >= 0 ? t.nsides[c] : 0;
+        int tot;
+        lrb[i] = rows + block_exclusive_scan(cn[i], s_scan, tot);
+        rows += tot;
+        ka[i] = kp[i] = 0.0;
+        if (c >= 0) {
+            const int rb = t.row_ptr[c];
+            for (int k = 0; k < cn[i]; ++k) pos[t.corner_he[rb + k]] = lrb[i] + k;
+            double A, P;
+            cell_geom_flat<double>(
+                t, X, cn[i], [&](int k) { return t.corner[rb + k]; }, rb, A, P, false, 0.0,
+                nullptr, nullptr);
+            ka[i] = 0.5 * p.ka(c);  // of c_k - c_{k+1}, halved again across an edge
+            kp[i] = 2.0 * p.kp(c);
+            aux[c] = double2{2.0 * p.ka(c) * (A - p.a0(c)), kp[i] * (P - p.p0(c))};
+        }
+    }
+    __syncthreads();
+    double ux[KV][3], uy[KV][3], ln[KV][3], ti[KV][3], dC[KV][3];
+    uint32_t adr[KV][3];   // byte offsets: neighbour in ql, cell in aux (high half)
+    uint32_t sl01[KV], sl2[KV];
+    double bx[KV], by[KV];
+    double sx = 0.0, sy = 0.0;
+#pragma unroll
+    for (int j = 0; j < KV; ++j) {
+        const int v = tid + j * bd;
+        sl01[j] = sl2[j] = 0u;
+        bx[j] = by[j] = 0.0;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            ux[j][k] = uy[j][k] = ln[j][k] = ti[j][k] = dC[j][k] = 0.0;
+            adr[j][k] = 0u;
+        }
+        if (v < nv) {
+            StarLoad<double, double> L;
+            star_ids<double, double>(t, X, v, L);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                L.q[k] = ld2(X, id_of(L.w[k]));
+                L.cc[k] = aux[L.c[k]];
+                L.lam[k] = p.lm(L.e[k]);
+            }
+            Star<double, double> s;
+            double xi, yi;
+            star_math<double, double>(t, L, s, xi, yi);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const int km = (k + 2) % 3;
+                ux[j][k] = s.ux[k];
+                uy[j][k] = s.uy[k];
+                ln[j][k] = s.l[k];
+                ti[j][k] = (s.lam[k] + s.cP[k] + s.cP[km]) * s.inv[k];
+                dC[j][k] = 0.5 * (s.cA[k] - s.cA[km]);
+                adr[j][k] = ((uint32_t)s.nb[k] << 4) | ((uint32_t)L.c[k] << 20);
+            }
+            sl01[j] = (uint32_t)pos[t.star_he[v]] | (uint32_t)pos[t.star_he[nv + v]] << 16;
+            sl2[j] = (uint32_t)pos[t.star_he[2 * nv + v]];
+            bx[j] = G.b[2 * (int64_t)v];
+            by[j] = G.b[2 * (int64_t)v + 1];
+            sx += bx[j];
+            sy += by[j];
+        }
+    }
+    const double mbx = solve_sum(sx, sh_a) / (double)nv;
+    const double mby = solve_sum(sy, sh_b) / (double)nv;  // its barrier frees pos and aux
+    // r = P b
+    double rr = 0.0;
+#pragma unroll
+    for (int j = 0; j < KV; ++j)
+        if (tid + j * bd < nv) {
+            bx[j] -= mbx;
+            by[j] -= mby;
+            rr += bx[j] * bx[j] + by[j] * by[j];
+        }
+    rr = solve_sum(rr, sh_a);
+    const double rr0 = rr;
+#pragma unroll
+    for (int j = 0; j < KV; ++j)
+        if (tid + j * bd < nv) ql[tid + j * bd] = double2{bx[j], by[j]};
+    // H q with q in `ql` (its barriers publish the own values, written
+    // before); returns the thread's part of q . H q
+    auto hess = [&](double (&hx)[KV], double (&hy)[KV]) {
+#pragma unroll
+        for (int j = 0; j < KV; ++j) {
+            const int v = tid + j * bd;
+            if (v < nv) {
+                const double2 q = ql[v];
+                double pk[3], ck[3];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    pk[k] = fma(ux[j][k], q.x, uy[j][k] * q.y);
+                    ck[k] = ln[j][k] * fma(uy[j][k], q.x, -ux[j][k] * q.y);
+                }
+                slot[sl01[j] & 0xffffu] = double2{ck[0] - ck[1], pk[0] + pk[1]};
+                slot[sl01[j] >> 16] = double2{ck[1] - ck[2], pk[1] + pk[2]};
+                slot[sl2[j]] = double2{ck[2] - ck[0], pk[2] + pk[0]};
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+            if (cid[i] >= 0) {
+                const double2 *row = slot + lrb[i];
+                double a = 0.0, b = 0.0;
+#pragma unroll
+                for (int k = 0; k < 6; ++k) {  // six entries in flight at once
+                    const double2 s = row[k < cn[i] ? k : 0];
+                    a += k < cn[i] ? s.x : 0.0;
+                    b += k < cn[i] ? s.y : 0.0;
+                }
+                for (int k = 6; k < cn[i]; ++k) {
+                    a += row[k].x;
+                    b += row[k].y;
+                }
+                aux[cid[i]] = double2{ka[i] * a, kp[i] * b};
+            }
+        __syncthreads();
+        double d = 0.0;
+#pragma unroll
+        for (int j = 0; j < KV; ++j) {
+            hx[j] = hy[j] = 0.0;
+            const int v = tid + j * bd;
+            if (v < nv) {
+                const double2 qi = ql[v];
+                double2 g[3], q[3];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    q[k] = at(ql, adr[j][k] & 0xffffu);
+                    g[k] = at(aux, adr[j][k] >> 16);
+                }
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const int km = (k + 2) % 3;
+                    const double vx = q[k].x - qi.x, vy = q[k].y - qi.y;
+                    // g.y holds minus 2 K_P dP
+                    const double s = fma(ti[j][k], fma(vx, ux[j][k], vy * uy[j][k]),
+                                         g[k].y + g[km].y);
+                    const double a = (g[k].x - g[km].x) * ln[j][k];
+                    hx[j] = fma(dC[j][k], vy,
+                                fma(a, uy[j][k], fma(ux[j][k], s, fma(-ti[j][k], vx, hx[j]))));
+                    hy[j] = fma(-dC[j][k], vx,
+                                fma(-a, ux[j][k], fma(uy[j][k], s, fma(-ti[j][k], vy, hy[j]))));
+                }
+                d = fma(qi.x, hx[j], fma(qi.y, hy[j], d));
+            }
+        }
+        return d;
+    };
+    // The solution (and MINRES's search directions) are touched once a step,
+    // by their own thread, off the step's chain: they stay in global memory.
+    double2 *xg = (double2 *)G.cg;
+    for (int v = tid; v < nv; v += bd) xg[v] = double2{0.0, 0.0};
+    int status = rr0 > 0.0 ? VTX_CG_MAXITER : VTX_CONVERGED;
+    int64_t it = 0;
+    double rel_res = 0.0;
+    double hx[KV], hy[KV];
+    if (!MINRES) {
+        const double stop = o.tol * sqrt(rr0);
+        while (status == VTX_CG_MAXITER && it < o.max_iter) {
+            if (__builtin_amdgcn_readfirstlane(sqrt(rr) <= stop ? 1 : 0)) {
+                status = VTX_CONVERGED;
+                break;
+            }
+            const double pAp = solve_sum(hess(hx, hy), sh_a);
+            if (__builtin_amdgcn_readfirstlane(pAp > 0.0 ? 0 : 1)) {
+                status = VTX_CG_NEG_CURVATURE;
+                break;
+            }
+            const double al = rr / pAp;
+            double rn = 0.0;
+#pragma unroll
+            for (int j = 0; j < KV; ++j) {
+                bx[j] = fma(-al, hx[j], bx[j]);
+                by[j] = fma(-al, hy[j], by[j]);
+                rn = fma(bx[j], bx[j], fma(by[j], by[j], rn));
+            }
+            rn = solve_sum(rn, sh_b);
+            const double be = rn / rr;
+            rr = rn;
+            ++it;
+#pragma unroll
+            for (int j = 0; j < KV; ++j) {
+                const int v = tid + j * bd;
+                if (v < nv) {
+                    const double2 q = ql[v], x = xg[v];
+                    xg[v] = double2{fma(al, q.x, x.x), fma(al, q.y, x.y)};
+                    ql[v] = double2{fma(be, q.x, bx[j]), fma(be, q.y, by[j])};
+                }
+            }
+        }
+        if (status == VTX_CG_MAXITER && sqrt(rr) <= stop) status = VTX_CONVERGED;
+        rel_res = rr0 > 0.0 ? sqrt(rr / rr0) : 0.0;
+    } else {
+        // the recurrences of k_batch_cg; `ql` holds the current Lanczos
+        // vector, bx, by the previous one
+        double2 *w1 = xg + nv, *w2 = w1 + nv;
+        const double beta1 = sqrt(rr0), inv1 = beta1 > 0.0 ? 1.0 / beta1 : 0.0;
+#pragma unroll
+        for (int j = 0; j < KV; ++j) {
+            const int v = tid + j * bd;
+            if (v < nv) {
+                ql[v] = double2{bx[j] * inv1, by[j] * inv1};
+                w1[v] = w2[v] = double2{0.0, 0.0};
+            }
+            bx[j] = by[j] = 0.0;
+        }
+        double beta = 0.0, c1 = 1.0, s1 = 0.0, c2 = 1.0, s2 = 0.0, phibar = beta1;
+        while (status == VTX_CG_MAXITER && it < o.max_iter) {
+            const double alpha = solve_sum(hess(hx, hy), sh_a);
+            double zz = 0.0;
+#pragma unroll
+            for (int j = 0; j < KV; ++j) {
+                const int v = tid + j * bd;
+                if (v < nv) {
+                    const double2 q = ql[v];
+                    hx[j] -= alpha * q.x + beta * bx[j];
+                    hy[j] -= alpha * q.y + beta * by[j];
+                    bx[j] = q.x;
+                    by[j] = q.y;
+                }
+                zz = fma(hx[j], hx[j], fma(hy[j], hy[j], zz));
+            }
+            const double beta_next = sqrt(solve_sum(zz, sh_b));
+            const double eps = s2 * beta, dbar = c2 * beta;
+            const double delta = c1 * dbar + s1 * alpha;
+            const double gbar = -s1 * dbar + c1 * alpha;
+            const double gamma = sqrt(gbar * gbar + beta_next * beta_next);
+            ++it;
+            if (!(gamma > 0.0)) {
+                status = fabs(phibar) <= o.tol * beta1 ? VTX_CONVERGED : VTX_CG_MAXITER;
+                break;
+            }
+            const double c = gbar / gamma, s = beta_next / gamma;
+            const double tau = c * phibar, ig = 1.0 / gamma;
+            const double ib = beta_next > 0.0 ? 1.0 / beta_next : 0.0;
+            phibar = -s * phibar;
+#pragma unroll
+            for (int j = 0; j < KV; ++j) {
+                const int v = tid + j * bd;
+                if (v < nv) {
+                    const double2 a = w1[v], b = w2[v], x = xg[v];
+                    const double wx = (bx[j] - delta * a.x - eps * b.x) * ig;
+                    const double wy = (by[j] - delta * a.y - eps * b.y) * ig;
+                    xg[v] = double2{fma(tau, wx, x.x), fma(tau, wy, x.y)};
+                    w2[v] = a;
+                    w1[v] = double2{wx, wy};
+                    ql[v] = double2{hx[j] * ib, hy[j] * ib};
+                }
+            }
+            c2 = c1;
+            s2 = s1;
+            c1 = c;
+            s1 = s;
+            beta = beta_next;
+            if (fabs(phibar) <= o.tol * beta1) status = VTX_CONVERGED;
+            else if (!(beta_next > 0.0)) break;
+        }
+        rel_res = beta1 > 0.0 ? fabs(phibar) / beta1 : 0.0;
+    }
+    // project the solution to zero mean
+    __syncthreads();  // a step that ended the loop early may still read sh_a
+    sx = sy = 0.0;
+    for (int v = tid; v < nv; v += bd) {
+        sx += xg[v].x;
+        sy += xg[v].y;
+    }
+    const double mxx = solve_sum(sx, sh_a) / (double)nv;
+    const double mxy = solve_sum(sy, sh_b) / (double)nv;
+    for (int v = tid; v < nv; v += bd) xg[v] = double2{xg[v].x - mxx, xg[v].y - mxy};
+    if (tid == 0) {
+        vtx_grad_result gr{};
+        gr.cg_iters = it;
+        gr.cg_rel_res = rel_res;
+        gr.status = status;
+        res[idx] = gr;
+    }
+    if (!G.g) return;
+    __syncthreads();
+    if (o.theta == VTX_THETA_LAMBDA)
+        for (int e = tid; e < t.n_edge; e += bd)
+            G.g[e] = contract_lambda_one<double>(t, X, G.cg, e);
+    else
+        for (int c = tid; c < nc; c += bd) G.g[c] = contract_p0_one<double>(t, X, p, G.cg, c);
+}
+
 // EP estimate from two states, one workgroup per tissue: the states nudged
 // by +beta/2 and -beta/2 (centred EP) or the state nudged by beta and X*
 // itself (first-order EP); either way the difference of the parameter
@@ -1153,9 +1522,58 @@ int auto_cg_threads(vtx_batch b, const GradOpts &go, int *out) {
     return VTX_OK;
 }
 
+// Dynamic LDS of k_solve_lds if every one of the n tissues fits it (*lds > 0),
+// else *lds = 0.
+int solve_lds_plan(const DevTissue *const *ts, size_t n, bool minres, int *lds) {
+    *lds = 0;
+    int dev = 0, lds_max = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess)
+        e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+    if (e != hipSuccess) return hip_fail(e);
+    int64_t need = 0;
+    for (size_t i = 0; i < n; ++i) {
+        const DevTissue &d = *ts[i];
+        const int64_t nb = solve_lds_bytes(d.n_vert, d.n_cell, d.n_he);
+        if (d.n_vert > kSolveMaxVerts || d.n_cell > kSolveK * kSolveThreads ||
+            nb > (int64_t)lds_max - 1024)  // the kernel's static LDS stays below
+            return VTX_OK;
+        need = std::max(need, nb);
+    }
+    const void *kern = minres ? reinterpret_cast<const void *>(&k_solve_lds<true>)
+                              : reinterpret_cast<const void *>(&k_solve_lds<false>);
+    e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)need);
+    if (e != hipSuccess) return hip_fail(e);
+    *lds = (int)need;
+    return VTX_OK;
+}
+
+// One workgroup per tissue, of a thread per vertex up to kSolveThreads.
+int launch_solve_lds(const GradItem *gi, const int32_t *order, int n, int64_t nv_max, int lds,
+                     const GradOpts &go, vtx_grad_result *res, hipStream_t s) {
+    const dim3 threads((unsigned)std::min<int64_t>(kSolveThreads, (nv_max + 63) / 64 * 64));
+    if (go.minres)
+        hipLaunchKernelGGL(k_solve_lds<true>, dim3(n), threads, (size_t)lds, s, gi, order, go, res);
+    else
+        hipLaunchKernelGGL(k_solve_lds<false>, dim3(n), threads, (size_t)lds, s, gi, order, go,
+                           res);
+    return launched();
+}
+
 template <typename PosT, typename M>
 int launch_batch_cg(vtx_batch b, const GradItem *gi, const int32_t *order, int n,
                     const GradOpts &go, int block_threads, hipStream_t s) {
+    if (sizeof(M) == sizeof(double) && (block_threads == 0 || block_threads == 512)) {
+        // FP64 tissues that all fit keep the geometry of the whole solve
+        std::vector<const DevTissue *> ts;
+        for (vtx_tissue t : b->ts) ts.push_back(&tissue_dev(t));
+        int lds = 0;
+        const int rc = solve_lds_plan(ts.data(), ts.size(), go.minres != 0, &lds);
+        if (rc) return rc;
+        if (lds > 0)
+            return launch_solve_lds(gi, order, n, tissue_size(b->ts[b->order[0]]), lds, go,
+                                    b->gres_d, s);
+    }
     if (block_threads == 0) {
         const int rc = auto_cg_threads<PosT, M>(b, go, &block_threads);
         if (rc) return rc;
@@ -1425,10 +1843,13 @@ constexpr int kPlanDoesNotApply = 1;
 struct OneSlot {
     BatchItem item;
     vtx_relax_result res;
+    GradItem gitem;
+    vtx_grad_result gres;
 };
 static_assert(sizeof(OneSlot) <= kOneBytes, "workspace slot");
 
-__global__ void k_put_item(BatchItem item, BatchItem *dst) {
+template <typename Item>
+__global__ void k_put_item(Item item, Item *dst) {
     if (threadIdx.x == 0) *dst = item;
 }
 
@@ -1508,12 +1929,29 @@ int relax_one(const DevTissue &t, const Workspace &w, int mode, void *X, const P
     const BatchItem item{t, X, w.xbuf, w.cap, w.t1_list, p, ra.nudge == 1 ? ra.X_target : nullptr,
                          ra.nudge == 2 ? (const double *)ra.g_lin : nullptr,
                          ra.nudge ? ra.beta : 0.0};
-    hipLaunchKernelGGL(k_put_item, dim3(1), dim3(64), 0, s, item, &slot->item);
+    hipLaunchKernelGGL(k_put_item<BatchItem>, dim3(1), dim3(64), 0, s, item, &slot->item);
     const BatchOpts bo{ra.eta, tol, ra.l_min, ra.l_new, patience, max_iter, ra.t1_enable};
     launch_relax_lds(mode, t1, &slot->item, nullptr, 1,
                      relax_lds_threads(t.n_vert, ra.nudge != 0), lds, bo, &slot->res, s);
     *res_d = &slot->res;
     return launched();
+}
+
+int solve_one(const DevTissue &t, const Workspace &w, int mode, const void *X, const ParamsRaw &p,
+              const double *rhs, bool minres, double tol, int64_t max_iter, int theta, double *g,
+              hipStream_t s, const vtx_grad_result **res_d) {
+    *res_d = nullptr;
+    if (mode != VTX_F64) return VTX_OK;
+    int lds = 0;
+    const DevTissue *tp = &t;
+    const int rc = solve_lds_plan(&tp, 1, minres, &lds);
+    if (rc || lds == 0) return rc;
+    OneSlot *slot = (OneSlot *)w.one;
+    const GradItem item{t, X, p, rhs, w.cg, w.cap, w.cell_aux, g};
+    hipLaunchKernelGGL(k_put_item<GradItem>, dim3(1), dim3(64), 0, s, item, &slot->gitem);
+    *res_d = &slot->gres;
+    return launch_solve_lds(&slot->gitem, nullptr, 1, t.n_vert, lds,
+                            GradOpts{tol, max_iter, theta, minres ? 1 : 0}, &slot->gres, s);
 }
 }  // namespace vtx
 

@@ -74,5 +74,11 @@ constexpr size_t kOneBytes = 1024;
 int relax_one(const DevTissue &t, const Workspace &w, int mode, void *X, const ParamsRaw &p,
               const RelaxArgs &ra, double tol, int64_t patience, int64_t max_iter, hipStream_t s,
               const vtx_relax_result **res_d);
+// H x = P rhs of an FP64 tissue that fits one workgroup (vtx_batch.hip), x in
+// w.cg, then the contraction with the mixed derivatives into g unless it is
+// NULL; *res_d as above.
+int solve_one(const DevTissue &t, const Workspace &w, int mode, const void *X, const ParamsRaw &p,
+              const double *rhs, bool minres, double tol, int64_t max_iter, int theta, double *g,
+              hipStream_t s, const vtx_grad_result **res_d);
 
 }  // namespace vtx

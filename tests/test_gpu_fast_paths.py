@@ -88,3 +88,41 @@ def test_fp64_lengths_over_the_range(vtx, oracle, scale):
     Eo, Fo = oracle.energy_forces(oracle.Mesh.from_tissue(ts), ts.X, p)
     assert abs(E.item() / Eo - 1.0) < 1e-12
     assert np.abs(F.cpu().numpy() - Fo).max() / np.abs(Fo).max() < 1e-12
+
+
+@pytest.mark.parametrize("method", ["adjoint", "adjoint_minres"])
+@pytest.mark.parametrize("theta", ["lambda", "P0"])
+@pytest.mark.parametrize("n_cell", [20, 32, 33, 129, 256, 257, 512, 513, 1000, 1024, 1025])
+def test_one_workgroup_solve_matches_the_oracle(vtx, oracle, n_cell, theta, method):
+    """Gradients of single FP64 tissues at the steps of the one-workgroup
+    solve (a wave for every 64 vertices, at most eight; one cell per thread up
+    to 512, then two; beyond 1024 cells the whole GPU), on random tilings
+    (3- to 12-sided cells) under tensions that make H positive definite.
+    Both solvers stop at a residual of 1e-12, so gradients agree to that
+    times the condition number (below 1e5 here)."""
+    V = vtx
+    t = g.random_tissue(n_cell, seed=900 + n_cell)
+    rng = np.random.default_rng(n_cell)
+    p = g.uniform_params(t, KA=0.02, P0=0.5, lam=1.0)
+    p.lam = rng.uniform(0.9, 1.1, t.n_edge)
+    b = rng.normal(size=(t.n_vert, 2))
+    T = V.Tissue.from_tissue(t)
+    P = V.Params(KA=0.02, A0=1.0, KP=1.0, P0=0.5, lam=_dev(p.lam))
+    got, info = T.param_grad(_dev(t.X), P, dC_dX=_dev(b), theta=theta, method=method,
+                             cg_tol=1e-12)
+    ref, info_o = oracle.adjoint_grad(oracle.Mesh.from_tissue(t), t.X, p, b, theta=theta,
+                                      tol=1e-12)
+    assert info["status"] == V.CONVERGED and info_o["status"] == 0
+    assert info["cg_rel_res"] <= 1e-12
+    err = np.abs(got.cpu().numpy() - ref).max() / np.abs(ref).max()
+    assert err < 1e-7, err
+    # a batch of the tissue and a smaller one takes the same kernel
+    if n_cell == 513:
+        t2 = g.random_tissue(40, seed=5)
+        T2 = V.Tissue.from_tissue(t2)
+        P2 = V.Params(KA=0.02, P0=0.5, lam=1.0)
+        outs, _ = V.Batch([T2, T]).param_grad([_dev(t2.X), _dev(t.X)], [P2, P],
+                                              dC_dX=[_dev(np.ones((80, 2))), _dev(b)],
+                                              theta=theta, method=method, cg_tol=1e-12)
+        assert torch.equal(outs[1], got)
+        assert float(outs[0].abs().max()) == 0.0  # a constant cost gradient has no zero-mean part
