@@ -89,6 +89,11 @@ ParamsRaw raw(const vtx_params *p) {
     return r;
 }
 
+// Largest tissue of the one-launch relaxation step, and its launches per
+// captured graph.
+constexpr int64_t kStepMaxVerts = 131072;
+constexpr int kStepChunk = 252;
+
 // Host copy of the staged layouts.
 struct Staged {
     std::vector<int32_t> he_edge, edge_he, row_ptr, row_cap, corner, corner_he, nsides, cell_he;
@@ -237,12 +242,14 @@ void free_tissue(vtx_tissue t) {
                     d.cell_he, d.star, d.star_he, t->w.xbuf,
                     t->w.cap, t->w.cell_aux, t->w.partials, t->w.partials2, t->w.mpart,
                     t->w.t1_list,
-                    t->w.ctl, t->w.cg, t->w.scal, t->w.one, t->ep_buf,
+                    t->w.ctl, t->w.cg, t->w.scal, t->w.one, t->w.step, t->w.step_part,
+                    t->ep_buf,
                     t->tiles.cells, t->tiles.info, t->tiles.halo, t->tiles.cstart,
                     t->tiles.corners, t->tiles.fstar, t->tiles.fe};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (t->w.ctl_host) (void)hipHostFree(t->w.ctl_host);
+    if (t->w.step_host) (void)hipHostFree(t->w.step_host);
     if (t->w.cap_stream) (void)hipStreamDestroy(t->w.cap_stream);
     delete t;
 }
@@ -262,14 +269,20 @@ int read_ctl(vtx_tissue t, int which, hipStream_t s) {
     return VTX_OK;
 }
 
+hipError_t fetch_ctl(vtx_tissue t, hipStream_t s) {
+    return hipMemcpyAsync(t->w.ctl_host, t->w.ctl, sizeof(LoopCtl), hipMemcpyDeviceToHost, s);
+}
+
 size_t pos_bytes(vtx_tissue t, int mode) {
     return (size_t)t->n_vert * 2 * (mode == VTX_F32 ? sizeof(float) : sizeof(double));
 }
 
 // Device loop driver: capture `chunk` steps of `body` once, replay until the
-// control block reports done.
-template <typename Body>
-int run_loop(vtx_tissue t, int chunk, int64_t max_steps, hipStream_t s, Body body) {
+// control block (copied by `read` into host memory, then asked by `done`)
+// reports done.
+template <typename Body, typename Read, typename Done>
+int run_loop(vtx_tissue t, int chunk, int64_t max_steps, hipStream_t s, Body body, Read read,
+             Done done) {
     hipGraph_t g = nullptr;
     hipGraphExec_t ge = nullptr;
     HIPCHK(hipStreamBeginCapture(t->w.cap_stream, hipStreamCaptureModeThreadLocal));
@@ -284,14 +297,13 @@ int run_loop(vtx_tissue t, int chunk, int64_t max_steps, hipStream_t s, Body bod
     int rc = VTX_OK;
     for (int64_t done_steps = 0;; done_steps += chunk) {
         hipError_t e = hipGraphLaunch(ge, s);
-        if (e == hipSuccess) e = hipMemcpyAsync(t->w.ctl_host, t->w.ctl, sizeof(LoopCtl),
-                                                hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = read();
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) {
             rc = fail(VTX_E_HIP, "device loop: %s", hipGetErrorString(e));
             break;
         }
-        if (t->w.ctl_host[0].done) break;
+        if (done()) break;
         if (done_steps + chunk >= max_steps + 2 * (int64_t)chunk) {
             rc = fail(VTX_E_HIP, "device loop did not report completion");
             break;
@@ -302,11 +314,52 @@ int run_loop(vtx_tissue t, int chunk, int64_t max_steps, hipStream_t s, Body bod
     return rc;
 }
 
+// The loop of one-launch steps (k_relax_step): no nudge, tissues of up to
+// kStepMaxVerts vertices.
+int relax_steps(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_relax_opts *o,
+                const RelaxArgs &ra, hipStream_t s, vtx_relax_result &r, int &overflow) {
+    StepCtl &h = *t->w.step_host;
+    h = StepCtl{};
+    h.s[0].status = VTX_NOT_CONVERGED;
+    HIPCHK(hipMemcpyAsync(t->w.step, &h, sizeof h, hipMemcpyHostToDevice, s));
+    HIPCHK(hipStreamSynchronize(s));
+    // (a multiple of 6: every replay starts at launch index 0 mod 2 and mod 3)
+    const int chunk = ((o->chunk > 0 ? o->chunk : kStepChunk) + 5) / 6 * 6;
+    // an iteration with a T1 pass takes three launches
+    const int64_t most = ra.t1_enable ? 3 * std::min(o->max_iter, INT64_MAX / 4) : o->max_iter;
+    int rc = run_loop(
+        t, chunk, most + 1, s,
+        [&](int k, hipStream_t cs) {
+            launch_relax_step(t->d, t->w, mode, X, t->w.xbuf, raw(p), ra, o->tol, o->patience,
+                              o->max_iter, k, cs);
+        },
+        [&]() { return hipMemcpyAsync(&h, t->w.step, sizeof h, hipMemcpyDeviceToHost, s); },
+        [&]() { return h.s[0].done != 0; });
+    const StepState &f = h.s[0];
+    // (a loop without an exchange, and without an error, left the topology)
+    if (ra.t1_enable && (rc || f.n_t1 > 0 || f.t1_overflow)) {
+        const int rt = vtx::tissue_topology_changed(t, s);
+        if (!rc) rc = rt;
+    }
+    if (rc) return rc;
+    if (f.result_buf == 1)
+        HIPCHK(hipMemcpyAsync(X, t->w.xbuf, pos_bytes(t, mode), hipMemcpyDeviceToDevice, s));
+    r.iters = f.iter;
+    r.n_t1 = f.n_t1;
+    r.n_stretch = f.n_stretch;
+    r.max_f = f.last_maxf;
+    r.status = f.status;
+    overflow = f.t1_overflow;
+    return VTX_OK;
+}
+
 // The relaxation loop on the whole GPU: captured graphs of `chunk`
 // iterations.  Leaves the result (all but the energy) in r and the T1 pass's
 // overflow code in `overflow`, and the final positions in X.
 int relax_grid(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_relax_opts *o,
                const RelaxArgs &ra, hipStream_t s, vtx_relax_result &r, int &overflow) {
+    if (!ra.nudge && t->n_vert <= kStepMaxVerts)
+        return relax_steps(t, mode, X, p, o, ra, s, r, overflow);
     LoopCtl c{};
     c.status = VTX_NOT_CONVERGED;
     c.max_iter = o->max_iter;
@@ -325,7 +378,7 @@ int relax_grid(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_r
     rc = run_loop(t, chunk, o->max_iter, s, [&](int k, hipStream_t cs) {
         const int cur = k & 1;
         launch_relax_iter(t->d, t->w, mode, bufs[cur], bufs[cur ^ 1], cur, raw(p), ra, cs);
-    });
+    }, [&]() { return fetch_ctl(t, s); }, [&]() { return t->w.ctl_host[0].done != 0; });
     const LoopCtl &h = t->w.ctl_host[0];
     // (a loop without an exchange, and without an error, left the topology)
     if (ra.t1_enable && (rc || h.n_t1 > 0 || h.t1_overflow)) {
@@ -486,6 +539,9 @@ int vtx_tissue_create(const int32_t *he, int64_t n_he, int64_t n_vert, int64_t n
     A((void **)&w.cg, 6 * 16 * (size_t)n_vert);  // CG: 4 vectors, MINRES: 6
     A((void **)&w.scal, 16 * sizeof(double));
     A(&w.one, kOneBytes);
+    A((void **)&w.step, sizeof(StepCtl));
+    A((void **)&w.step_part,
+      2 * sizeof(double) * (size_t)((4 * std::min(n_vert, kStepMaxVerts) + kBlock - 1) / kBlock));
     A((void **)&t->ep_buf, 2 * 16 * (size_t)n_vert);
     const size_t n_tiles = (size_t)n_tiles_for(n_vert);
     A((void **)&t->tiles.cells, 4 * (size_t)kTileCap * n_tiles);
@@ -496,6 +552,7 @@ int vtx_tissue_create(const int32_t *he, int64_t n_he, int64_t n_vert, int64_t n
     A((void **)&t->tiles.fstar, 16 * (size_t)n_vert);
     A((void **)&t->tiles.fe, 8 * (size_t)n_vert);
     if (e == hipSuccess) e = hipHostMalloc((void **)&w.ctl_host, 2 * sizeof(LoopCtl), 0);
+    if (e == hipSuccess) e = hipHostMalloc((void **)&w.step_host, sizeof(StepCtl), 0);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&w.cap_stream, hipStreamNonBlocking);
     if (e == hipSuccess) {
         LoopCtl z{};
@@ -741,7 +798,7 @@ static int solve_hessian(vtx_tissue t, int mode, const void *X, const vtx_params
         rc = run_loop(t, 32, max_iter, s, [&](int, hipStream_t cs) {
             if (minres) launch_minres_iter(t->d, t->w, mode, X, raw(p), cs);
             else launch_cg_iter(t->d, t->w, mode, X, raw(p), cs);
-        });
+        }, [&]() { return fetch_ctl(t, s); }, [&]() { return t->w.ctl_host[0].done != 0; });
         if (rc) return rc;
     }
     const LoopCtl &h = t->w.ctl_host[0];

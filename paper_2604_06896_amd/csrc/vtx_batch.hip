@@ -601,9 +601,9 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_lds(const GradItem *__r
             const int rb = t.row_ptr[c];
             for (int k = 0; k < cn[i]; ++k) pos[t.corner_he[rb + k]] = lrb[i] + k;
             double A, P;
-            cell_geom_flat<double>(
-                t, X, cn[i], [&](int k) { return t.corner[rb + k]; }, rb, A, P, false, 0.0,
-                nullptr, nullptr);
+            auto corner_at = [&](int k) { return t.corner[rb + (k < cn[i] ? k : 0)]; };
+            cell_geom_flat<double>(t, X, cn[i], corner_at, corner_at, rb, A, P, false, 0.0,
+                                   nullptr, nullptr);
             ka[i] = 0.5 * p.ka(c);  // of c_k - c_{k+1}, halved again across an edge
             kp[i] = 2.0 * p.kp(c);
             aux[c] = double2{2.0 * p.ka(c) * (A - p.a0(c)), kp[i] * (P - p.p0(c))};
@@ -1197,8 +1197,8 @@ __global__ __launch_bounds__(kRelaxLdsThreads) void k_batch_relax_lds(
                 const int base = lrb[i];
                 if (c >= 0) {
                     PosT A, P;
-                    auto corner_at = [&](int k) { return rowl[base + k]; };
-                    cell_geom_flat<PosT>(t, Xc, cn[i], corner_at, grb[i], A, P,
+                    auto corner_at = [&](int k) { return rowl[base + (k < cn[i] ? k : 0)]; };
+                    cell_geom_flat<PosT>(t, Xc, cn[i], corner_at, corner_at, grb[i], A, P,
                                          T1 && o.t1_enable != 0, lmin2p, B.t1_list, &s_cnt[par]);
                     st2(capl, c, (M)((PosT)2 * ka[i] * (A - a0[i])),
                         (M)((PosT)2 * kp[i] * (P - p0[i])));

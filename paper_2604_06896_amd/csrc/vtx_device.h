@@ -80,13 +80,15 @@ __device__ __forceinline__ void cell_geom(const DevTissue &t, const PosT *__rest
 // two waves per SIMD, where that latency is the time of the cell pass; the
 // evaluation of large tissues, with many waves to hide it, keeps cell_geom
 // and does not compute the copies.
-template <typename PosT, bool NOIMG = false, typename CornerAt>
+// `head(k)` returns corner k for a constant k <= 6, `tail(k)` for any k > 6;
+// both return corner 0 for k >= n.
+template <typename PosT, bool NOIMG = false, typename Head, typename Tail>
 __device__ __forceinline__ void cell_geom_flat(const DevTissue &t, const PosT *__restrict__ X,
-                                               int n, CornerAt corner_at, int row_base, PosT &A,
+                                               int n, Head head, Tail tail, int row_base, PosT &A,
                                                PosT &P, bool det, PosT lmin2, int32_t *list,
                                                unsigned int *count) {
     const PosT Lx = (PosT)t.Lx, Ly = (PosT)t.Ly;
-    const int32_t w0 = corner_at(0);
+    const int32_t w0 = head(0);
     const auto p0 = ld2(X, id_of(w0));
     const int v0 = id_of(w0);
     PosT px = 0, py = 0, a = 0, per = 0;
@@ -112,13 +114,13 @@ __device__ __forceinline__ void cell_geom_flat(const DevTissue &t, const PosT *_
     int32_t w[U];
     typename Vec2<PosT>::type q[U];
 #pragma unroll
-    for (int k = 1; k <= U; ++k) w[k - 1] = corner_at(k < n ? k : 0);
+    for (int k = 1; k <= U; ++k) w[k - 1] = head(k);
 #pragma unroll
     for (int k = 1; k <= U; ++k) q[k - 1] = ld2(X, id_of(w[k - 1]));
 #pragma unroll
     for (int k = 1; k <= U; ++k) step(k, w[k - 1], q[k - 1]);
     for (int k = U + 1; k <= n; ++k) {
-        const int32_t wk = corner_at(k < n ? k : 0);
+        const int32_t wk = tail(k);
         step(k, wk, ld2(X, id_of(wk)));
     }
     if (det)

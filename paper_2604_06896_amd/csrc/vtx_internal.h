@@ -161,6 +161,21 @@ __host__ __device__ inline uint32_t pack_local(int32_t local, int32_t w) {
     return (uint32_t)local | (((uint32_t)w >> kIdBits) << 12);
 }
 
+// State of the one-launch relaxation step (k_relax_step) between launches.
+struct StepState {
+    int64_t iter, count, n_t1, n_stretch;
+    double last_maxf;
+    int32_t cur;         // buffer of the current positions
+    int32_t pending;     // the launch before computed a step from `cur`
+    int32_t det;         // ... and listed the short edges it saw
+    int32_t redo;        // the step takes its coefficients from `cap` (after a T1 pass)
+    int32_t done, status, result_buf, t1_overflow;
+};
+struct StepCtl {
+    StepState s[2];      // launch k reads s[k mod 2] and writes the other
+    uint32_t cnt[3];     // short edges: read k mod 3, add to the next, clear the one after
+};
+
 struct Workspace {
     void *xbuf;          // second position buffer (double [n_vert][2])
     double *cap;         // per-cell (cA, cP) in the arithmetic type, sized for double
@@ -173,6 +188,9 @@ struct Workspace {
     LoopCtl *ctl_host;   // pinned host mirror
     double *cg;          // CG vectors: x, r, p, Ap (double [4][n_vert][2])
     double *scal;        // device scalars
+    StepCtl *step;       // device
+    double *step_part;   // max |F| of each block of a step, [2][blocks]
+    StepCtl *step_host;  // pinned host mirror
     void *one;           // device: item and result of a one-workgroup launch (OneSlot)
     hipStream_t cap_stream;
 };

@@ -656,7 +656,7 @@ __global__ __launch_bounds__(kTileV) void k_eval_fused(DevTissue t, const PosT *
 
 // ---------------------------------------------------------------------- T1
 template <typename PosT, typename M>
-__global__ __launch_bounds__(kBlock) void k_t1(DevTissue t, PosT *X, DevParams<PosT> p, M *cap,
+__global__ __launch_bounds__(kBlock, 4) void k_t1(DevTissue t, PosT *X, DevParams<PosT> p, M *cap,
                                                LoopCtl *ctl, int32_t *list_g, double l_min,
                                                double l_new) {
     __shared__ int32_t buf[kT1SortCap];
@@ -695,6 +695,224 @@ __global__ __launch_bounds__(kBlock) void k_t1(DevTissue t, PosT *X, DevParams<P
             ctl->done = 1;
         }
     }
+}
+
+// ------------------------------------------------- one-launch relaxation step
+struct StepArgs {
+    double eta, tol, l_min, l_new;
+    int64_t patience, max_iter;
+    double *part;   // [2][gridDim.x] max |F| of each block
+    int k2, k3;     // launch index mod 2 and mod 3
+};
+
+// Lane k of a quad (quad_perm), for doubles and floats.
+template <int Ctrl>
+__device__ __forceinline__ double quad(double v) { return dpp_f64<Ctrl>(v); }
+template <int Ctrl>
+__device__ __forceinline__ float quad(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), Ctrl, 0xF, 0xF, false));
+}
+constexpr int kQuadPrev = 0x12 | (3 << 6);  // lanes 0, 1, 2 read 2, 0, 1
+constexpr int kQuad0 = 0x00, kQuad1 = 0x55, kQuad2 = 0xAA;
+
+// A gradient-descent iteration in one launch, for tissues too large for one
+// workgroup and small enough that the chip is idle most of a step.  Three of
+// the four lanes of a quad take the three star slots of a vertex: lane k
+// computes the coefficients of sector cell k from its corner row (so each
+// cell is computed by every vertex around it, six times as much arithmetic
+// as k_cell, on lanes that would have none), the edge k, and its term of the
+// force, and the quad adds the terms in slot order; the arithmetic is that of
+// k_cell and k_vertex, so the iterates are theirs bit for bit.  Detection of
+// short edges for T1 takes the star's edges.
+//
+// Nothing is reduced within the launch: the blocks leave their max |F|, and
+// every block of the next launch adds up the decision for itself (while it
+// waits for its rows): converged, go on from the new positions, or, if short
+// edges were listed, drop the step, let block 0 run the T1 pass on the old
+// positions, and take the step again in the launch after, from the
+// coefficients this launch stored and the pass changed.  Kernel boundaries
+// give the ordering that device-scope arrivals or k_finish gave before.
+// (Four waves per SIMD: the T1 pass, which one wave runs, would take all 512
+// registers and leave the step one wave per SIMD.)
+template <typename PosT, typename M, bool T1>
+__global__ __launch_bounds__(kBlock, 4) void k_relax_step(DevTissue t, PosT *X0, PosT *X1,
+                                                       DevParams<PosT> p, M *cap, StepCtl *ctl,
+                                                       int32_t *list, StepArgs a) {
+    __shared__ int32_t sort_buf[T1 ? kT1SortCap : 1];
+    __shared__ int32_t extra[T1 ? kT1Extra : 1];
+    __shared__ int32_t scan[T1 ? kBlock : 1];
+    __shared__ double sh[2 * (kBlock / 64)];
+    StepState S = ctl->s[a.k2];
+    if (S.done) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) ctl->s[a.k2 ^ 1] = S;
+        return;
+    }
+    const int tid = threadIdx.x, nv = t.n_vert;
+    const int gid = xcd_block() * kBlock + tid;
+    const int v = gid >> 2, k = gid & 3;
+    const bool live = v < nv && k < 3;
+    // topology (does not depend on the decision below)
+    int32_t wn = 0, c = 0, e = 0, rb = 0, n = 0;
+    constexpr int U = 7;
+    int32_t wc[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) wc[j] = 0;
+    if (live) {
+        wn = t.star[star_nb_at(nv, k, v)];
+        c = t.star[star_cell_at(nv, k, v)];
+        e = t.star[star_edge_at(nv, k, v)];
+        rb = t.row_ptr[c];
+        n = t.nsides[c];
+#pragma unroll
+        for (int j = 0; j < U; ++j) wc[j] = t.corner[rb + (j < n ? j : 0)];
+    }
+    // the launch before: its step stands, is dropped for a T1 pass, or ends
+    // the loop
+    const uint32_t ncand = T1 ? ctl->cnt[a.k3] : 0u;
+    bool pass = false;
+    if (S.pending) {
+        double m = 0.0;
+        const double *part = a.part + (int64_t)a.k2 * gridDim.x;
+        for (int i = tid; i < (int)gridDim.x; i += kBlock) m = fmax(m, part[i]);
+        m = wave_max_plain(m);
+        if ((tid & 63) == 0) sh[tid >> 6] = m;
+        __syncthreads();
+        m = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
+        if (T1 && S.det && ncand > 0) {
+            pass = true;
+        } else {
+            S.iter += 1;
+            S.last_maxf = m;
+            if (!(m <= 1.7976931348623157e308)) {
+                S.done = 1;
+                S.status = VTX_E_NONFINITE;
+                S.result_buf = S.cur;
+            } else {
+                S.count = m < a.tol ? S.count + 1 : 0;
+                if (S.count >= a.patience) {
+                    S.done = 1;
+                    S.status = VTX_CONVERGED;
+                    S.result_buf = S.cur;
+                } else if (S.iter >= a.max_iter) {
+                    S.done = 1;
+                    S.status = VTX_NOT_CONVERGED;
+                    S.result_buf = S.cur ^ 1;
+                }
+            }
+            S.cur ^= 1;
+            S.redo = 0;
+        }
+    }
+    if (pass) {  // T1 pass on the positions the dropped step started from
+        if (blockIdx.x != 0) return;
+        PosT *X = S.cur ? X1 : X0;
+        int np2 = 1;
+        while (np2 < (int)ncand) np2 <<= 1;
+        int32_t *arr = np2 <= kT1SortCap ? sort_buf : list;
+        for (int i = tid; i < np2; i += kBlock) arr[i] = i < (int)ncand ? list[i] : INT_MAX;
+        __syncthreads();
+        block_bitonic(arr, np2);
+        __shared__ int s_relocated;
+        if (tid < 64) {
+            const T1Counts r = t1_sequential<PosT, M>(t, X, p, cap, arr, (int)ncand, extra,
+                                                      a.l_min, a.l_new);
+            if (tid == 0) {
+                S.n_t1 += r.swaps;
+                S.n_stretch += r.stretches;
+                if (r.overflow) S.t1_overflow = r.overflow;
+                if (r.overflow == 2) S.done = 1;  // the host reports it
+                s_relocated = r.relocated;
+            }
+        }
+        __syncthreads();
+        int bad = 0;
+        if (s_relocated) bad = rebuild_rows_block(t, scan);
+        if (tid == 0) {
+            if (bad) {
+                S.t1_overflow = 2;
+                S.done = 1;
+            }
+            S.pending = 0;
+            S.redo = 1;
+            ctl->s[a.k2 ^ 1] = S;
+            ctl->cnt[(a.k3 + 2) % 3] = 0u;
+        }
+        return;
+    }
+    const bool det = T1 && !S.redo;
+    if (blockIdx.x == 0 && tid == 0) {
+        StepState N = S;
+        N.pending = 1;
+        N.det = det ? 1 : 0;
+        ctl->s[a.k2 ^ 1] = N;
+        ctl->cnt[(a.k3 + 2) % 3] = 0u;
+    }
+    if (S.done) return;
+    const PosT *X = S.cur ? X1 : X0;
+    PosT *out = S.cur ? X0 : X1;
+    double mf = 0.0;
+    M tx = 0, ty = 0;
+    typename Vec2<PosT>::type pi{};
+    typename Vec2<M>::type cc{};
+    M dx = 0, dy = 0, ux = 0, uy = 0, lam = 0;
+    if (live) {
+        const PosT Lx = (PosT)t.Lx, Ly = (PosT)t.Ly;
+        pi = ld2(X, v);
+        const auto qn = ld2(X, id_of(wn));
+        lam = (M)p.lm(e);
+        const PosT ex = pdiff<PosT>(qn.x, pi.x, ox_of(wn), Lx);
+        const PosT ey = pdiff<PosT>(qn.y, pi.y, oy_of(wn), Ly);
+        if (S.redo) {
+            cc = ld2((const M *)cap, c);
+        } else {
+            PosT A, P;
+            cell_geom_flat<PosT>(
+                t, X, n, [&](int j) { return wc[j]; },
+                [&](int j) { return j < n ? t.corner[rb + j] : wc[0]; }, rb, A, P, false, (PosT)0,
+                (int32_t *)nullptr, (unsigned int *)nullptr);
+            const PosT ka = p.ka(c), kp = p.kp(c);
+            const PosT da = A - p.a0(c), dp = P - p.p0(c);
+            cc.x = (M)((PosT)2 * ka * da);
+            cc.y = (M)((PosT)2 * kp * dp);
+            // one vertex of the cell (its corner 0) keeps them for a redo
+            if (T1 && id_of(wc[0]) == v) st2(cap, c, cc.x, cc.y);
+            // (the margin above l_min covers rounding; the pass tests exactly)
+            if (det && v < id_of(wn) &&
+                ex * ex + ey * ey < (PosT)(M)(a.l_min * a.l_min * (1.0 + 1e-4)))
+                list[atomicAdd(&ctl->cnt[(a.k3 + 1) % 3], 1u)] = e;
+        }
+        dx = (M)ex;
+        dy = (M)ey;
+        M l, inv;
+        len_inv(dx * dx + dy * dy, l, inv);
+        ux = dx * inv;
+        uy = dy * inv;
+    }
+    // star_force: lane k needs the coefficients of sector cell k - 1
+    const M cAm = quad<kQuadPrev>(cc.x), cPm = quad<kQuadPrev>(cc.y);
+    const M T = lam + cc.y + cPm;
+    const M dA = (M)0.5 * (cc.x - cAm);
+    tx = T * ux - dA * dy;
+    ty = T * uy + dA * dx;
+    M fx = 0, fy = 0;
+    fx += quad<kQuad0>(tx);
+    fy += quad<kQuad0>(ty);
+    fx += quad<kQuad1>(tx);
+    fy += quad<kQuad1>(ty);
+    fx += quad<kQuad2>(tx);
+    fy += quad<kQuad2>(ty);
+    if (live && k == 0) {
+        const double gx = fx, gy = fy;
+        mf = fmax(fabs(gx), fabs(gy));
+        if (!(gx == gx) || !(gy == gy)) mf = INFINITY;
+        st2(out, v, (PosT)((double)pi.x + a.eta * gx), (PosT)((double)pi.y + a.eta * gy));
+    }
+    mf = wave_max_plain(mf);
+    if ((tid & 63) == 0) sh[4 + (tid >> 6)] = mf;
+    __syncthreads();
+    if (tid == 0)
+        a.part[(int64_t)(a.k2 ^ 1) * gridDim.x + blockIdx.x] =
+            fmax(fmax(sh[4], sh[5]), fmax(sh[6], sh[7]));
 }
 
 // ------------------------------------------------------ scalar reductions
@@ -1396,6 +1614,32 @@ void launch_relax_iter(const DevTissue &t, const Workspace &w, int mode, void *X
     if (mode == VTX_F32) relax_iter_impl<float, float>(t, w, Xc, Xn, cur, p, ra, s);
     else if (mode == VTX_F64) relax_iter_impl<double, double>(t, w, Xc, Xn, cur, p, ra, s);
     else relax_iter_impl<double, float>(t, w, Xc, Xn, cur, p, ra, s);
+}
+
+template <typename PosT, typename M>
+static void relax_step_impl(const DevTissue &t, const Workspace &w, void *X0, void *X1,
+                            const ParamsRaw &pr, const RelaxArgs &ra, double tol,
+                            int64_t patience, int64_t max_iter, int k, hipStream_t s) {
+    const StepArgs a{ra.eta, tol, ra.l_min, ra.l_new, patience, max_iter, w.step_part, k % 2, k % 3};
+    const dim3 grid(blocks_for(4 * (int64_t)t.n_vert)), block(kBlock);
+    auto p = dev_params<PosT>(pr);
+    if (ra.t1_enable)
+        hipLaunchKernelGGL((k_relax_step<PosT, M, true>), grid, block, 0, s, t, (PosT *)X0,
+                           (PosT *)X1, p, (M *)w.cap, w.step, w.t1_list, a);
+    else
+        hipLaunchKernelGGL((k_relax_step<PosT, M, false>), grid, block, 0, s, t, (PosT *)X0,
+                           (PosT *)X1, p, (M *)w.cap, w.step, w.t1_list, a);
+}
+
+void launch_relax_step(const DevTissue &t, const Workspace &w, int mode, void *X0, void *X1,
+                       const ParamsRaw &p, const RelaxArgs &ra, double tol, int64_t patience,
+                       int64_t max_iter, int k, hipStream_t s) {
+    if (mode == VTX_F32)
+        relax_step_impl<float, float>(t, w, X0, X1, p, ra, tol, patience, max_iter, k, s);
+    else if (mode == VTX_F64)
+        relax_step_impl<double, double>(t, w, X0, X1, p, ra, tol, patience, max_iter, k, s);
+    else
+        relax_step_impl<double, float>(t, w, X0, X1, p, ra, tol, patience, max_iter, k, s);
 }
 
 template <typename PosT, typename M>

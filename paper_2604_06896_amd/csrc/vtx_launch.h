@@ -36,6 +36,11 @@ void launch_vertex_pass(const DevTissue &t, const Workspace &w, int mode, const 
                         hipStream_t s);
 void launch_relax_iter(const DevTissue &t, const Workspace &w, int mode, void *Xc, void *Xn,
                        int cur, const ParamsRaw &p, const RelaxArgs &ra, hipStream_t s);
+// Launch k of a captured chunk (whose length is a multiple of 6) of the
+// one-launch relaxation step; X0 is the caller's buffer, X1 the library's.
+void launch_relax_step(const DevTissue &t, const Workspace &w, int mode, void *X0, void *X1,
+                       const ParamsRaw &p, const RelaxArgs &ra, double tol, int64_t patience,
+                       int64_t max_iter, int k, hipStream_t s);
 void launch_t1(const DevTissue &t, const Workspace &w, int mode, void *X, const ParamsRaw &p,
                double l_min, double l_new, hipStream_t s);
 void launch_cell_coeffs(const DevTissue &t, const Workspace &w, int mode, const void *X,

@@ -126,3 +126,33 @@ def test_one_workgroup_solve_matches_the_oracle(vtx, oracle, n_cell, theta, meth
                                               theta=theta, method=method, cg_tol=1e-12)
         assert torch.equal(outs[1], got)
         assert float(outs[0].abs().max()) == 0.0  # a constant cost gradient has no zero-mean part
+
+
+@pytest.mark.parametrize("mode", ["f32", "mixed", "f64"])
+@pytest.mark.parametrize("t1", [True, False])
+@pytest.mark.parametrize("n_cell,chunk", [(1025, 0), (1500, 1), (2111, 17)])
+def test_one_launch_step_equals_the_batched_loop(vtx, mode, t1, n_cell, chunk):
+    """Tissue.relax beyond one workgroup takes one launch per iteration (three
+    with a T1 pass, whatever the length of the captured chunk): the iterates,
+    counts and topology are those of the batched loop bit for bit, at a fixed
+    number of steps and at a tolerance with patience."""
+    V = vtx
+    dt = V.pos_dtype(mode)
+    t = g.random_tissue(n_cell, seed=70 + n_cell)
+    rng = np.random.default_rng(n_cell)
+    P = V.Params(KA=1.0, A0=1.0, KP=1.0, P0=_dev(rng.uniform(3.6, 3.9, t.n_cell), dt),
+                 lam=_dev(rng.uniform(0.05, 0.15, t.n_edge), dt))
+    for kw in (dict(tol=0.0, max_iter=101), dict(tol=0.8, max_iter=400, patience=7)):
+        T1, T2 = V.Tissue.from_tissue(t), V.Tissue.from_tissue(t)
+        X1, X2 = _dev(t.X, dt), _dev(t.X, dt)
+        opts = dict(eta=3e-3, t1_enable=t1, l_min=0.02, **kw)
+        r1 = T1.relax(X1, P, mode=mode, chunk=chunk, **opts)
+        r2 = V.Batch([T2]).relax([X2], [P], mode=mode, block_threads=1024, **opts)[0]
+        keys = ("iters", "n_t1", "n_stretch", "status", "max_f")
+        assert [r1[k] for k in keys] == [r2[k] for k in keys]
+        assert torch.equal(X1, X2) and np.array_equal(T1.topology(), T2.topology())
+        assert not t1 or r1["n_t1"] > 0
+        # the tables of the fused evaluation follow
+        F = T1.energy_forces(X1, P, mode=mode)[1]
+        assert torch.equal(F, T1.vertex_forces(X1, P, T1.cell_coeffs(X1, P, mode=mode),
+                                               mode=mode)[0])
