@@ -287,20 +287,6 @@ __device__ __forceinline__ void cell_walk(const DevTissue &t, const PosT *X, int
     P = per;
 }
 
-__device__ __forceinline__ void star_refresh(const DevTissue &t, int v, int h0) {
-    const int nv = t.n_vert;
-    int h = h0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const int32_t *r = t.he + 8 * (int64_t)h;
-        t.star_he[k * nv + v] = h;
-        t.star[star_nb_at(nv, k, v)] = pack_id(r[HG], r[HOX], r[HOY]);
-        t.star[star_cell_at(nv, k, v)] = r[HF];
-        t.star[star_edge_at(nv, k, v)] = t.he_edge[h];
-        h = t.he[8 * (int64_t)t.he[8 * (int64_t)h + HP] + HT];  // twin(prev(h))
-    }
-}
-
 // ------------------------------------------------------------------- T1
 // One half-edge record loaded as two 16-byte vectors.
 struct HeRec {
@@ -317,58 +303,47 @@ __device__ __forceinline__ HeRec he_rec(const DevTissue &t, int h) {
 // optional edit of the corner sequence:
 //   edit 1: drop vertex va;
 //   edit 2: put vertex vb, at the image of va plus (sx, sy), right before va.
-// Coordinates are unwrapped x + W L; the first corner is the origin.  The
-// first kRowPre corners and their positions are loaded before any is used.
-constexpr int kRowPre = 12;
+// Coordinates are unwrapped x + W L; the first corner is the origin.  One
+// lane walks the row; the T1 pass uses it for rows longer than kRowLanes.
 template <typename PosT>
-__device__ __noinline__ void row_geom(const DevTissue &t, const PosT *X, int c,
-                                         const PosOverride<PosT> ov, int edit, int va, int vb,
+__device__ __forceinline__ void row_geom(const DevTissue &t, const PosT *X, int c,
+                                         const PosOverride<PosT> &ov, int edit, int va, int vb,
                                          int sx, int sy, double &A, double &P) {
     const int rb = t.row_ptr[c], n = t.nsides[c];
-    int32_t w[kRowPre];
-    double qx[kRowPre], qy[kRowPre];
-#pragma unroll
-    for (int k = 0; k < kRowPre; ++k) w[k] = t.corner[rb + (k < n ? k : 0)];
-#pragma unroll
-    for (int k = 0; k < kRowPre; ++k) ov.get(X, id_of(w[k]), qx[k], qy[k]);
     double x0 = 0.0, y0 = 0.0, px = 0.0, py = 0.0, a = 0.0, per = 0.0;
     bool first = true;
-    auto emit = [&](double x, double y, int wx, int wy) {
+    for (int k = 0, ins = 0; k < n;) {
+        const int32_t wk = t.corner[rb + k];
+        int v = id_of(wk), wx = ox_of(wk), wy = oy_of(wk);
+        if (edit == 1 && v == va) {
+            ++k;
+            continue;
+        }
+        if (edit == 2 && v == va && !ins) {  // vb first, then va on the next turn
+            ins = 1;
+            v = vb;
+            wx += sx;
+            wy += sy;
+        } else {
+            ++k;
+        }
+        double x, y;
+        ov.get(X, v, x, y);
         const double rx = x + wx * t.Lx, ry = y + wy * t.Ly;
         if (first) {
             x0 = rx;
             y0 = ry;
             first = false;
-            return;
+            continue;
         }
         const double ux = rx - x0, uy = ry - y0;
         const double dx = ux - px, dy = uy - py;
         a += px * uy - py * ux;
-        per += sqrt(dx * dx + dy * dy);
+        per += len_of(dx * dx + dy * dy);
         px = ux;
         py = uy;
-    };
-    auto corner = [&](int32_t wk, double x, double y) {
-        const int v = id_of(wk);
-        if (edit == 2 && v == va) {
-            double bx, by;
-            ov.get(X, vb, bx, by);
-            emit(bx, by, ox_of(wk) + sx, oy_of(wk) + sy);
-        }
-        if (edit == 1 && v == va) return;
-        emit(x, y, ox_of(wk), oy_of(wk));
-    };
-#pragma unroll
-    for (int k = 0; k < kRowPre; ++k)
-        if (k < n) corner(w[k], qx[k], qy[k]);
-    for (int k = kRowPre; k < n; ++k) {
-        const int32_t wk = t.corner[rb + k];
-        double x, y;
-        ov.get(X, id_of(wk), x, y);
-        corner(wk, x, y);
     }
-    const double dx = -px, dy = -py;  // closing edge back to the first corner
-    per += sqrt(dx * dx + dy * dy);
+    per += len_of(px * px + py * py);  // closing edge back to the first corner
     A = 0.5 * a;
     P = per;
 }
@@ -378,79 +353,6 @@ __device__ __forceinline__ double cell_energy(const DevParams<PosT> &p, int c, d
                                               double P) {
     const double da = A - (double)p.a0(c), dp = P - (double)p.p0(c);
     return (double)p.ka(c) * da * da + (double)p.kp(c) * dp * dp;
-}
-
-// Cell-term coefficients of one cell recomputed (FP64) after a T1 step.
-template <typename PosT, typename M>
-__device__ __forceinline__ void cell_refresh_cap(const DevTissue &t, const PosT *X,
-                                                 const DevParams<PosT> &p, M *cap, int c) {
-    PosOverride<PosT> none{-1, -1, 0, 0, 0, 0};
-    double A, P;
-    row_geom<PosT>(t, X, c, none, 0, -1, -1, 0, 0, A, P);
-    cap[2 * (int64_t)c] = (M)(2.0 * (double)p.ka(c) * (A - (double)p.a0(c)));
-    cap[2 * (int64_t)c + 1] = (M)(2.0 * (double)p.kp(c) * (P - (double)p.p0(c)));
-}
-
-// Length of the edge src -> tgt with image offset (ox, oy), overridden
-// positions allowed.
-template <typename PosT>
-__device__ __forceinline__ double ov_len(const DevTissue &t, const PosT *X,
-                                         const PosOverride<PosT> &ov, int s, int g, int ox,
-                                         int oy) {
-    double xs, ys, xg, yg;
-    ov.get(X, s, xs, ys);
-    ov.get(X, g, xg, yg);
-    const double dx = xg + ox * t.Lx - xs, dy = yg + oy * t.Ly - ys;
-    return sqrt(dx * dx + dy * dy);
-}
-
-// Neighbour exchange of the edge of half-edge h (i -> j in C1, its twin
-// j -> i in C2; C3 is the third cell at i, C4 the third cell at j).
-// Afterwards h bounds C4 and its twin bounds C3, the edge to c (next of h
-// in C1) moves from j to i and the edge to b (next of the twin in C2) from
-// i to j; the moved half-edges change image offset by the offset of h so
-// that every edge vector is kept.
-__device__ __forceinline__ void t1_patch(const DevTissue &t, int h) {
-    int32_t *he = t.he;
-    auto R = [&](int x) { return he + 8 * (int64_t)x; };
-    const int tw = R(h)[HT];
-    const int i = R(h)[HS], j = R(h)[HG];
-    const int p1 = R(h)[HP], n1 = R(h)[HN];
-    const int p2 = R(tw)[HP], n2 = R(tw)[HN];
-    const int tp1 = R(p1)[HT], tn1 = R(n1)[HT];
-    const int tp2 = R(p2)[HT], tn2 = R(n2)[HT];
-    const int C3 = R(tp1)[HF], C4 = R(tn1)[HF];
-    const int hox = R(h)[HOX], hoy = R(h)[HOY];
-    // C1: a->i -> i->c
-    R(p1)[HN] = n1;
-    R(n1)[HP] = p1;
-    R(n1)[HS] = i;
-    R(tn1)[HG] = i;
-    R(n1)[HOX] += hox;
-    R(n1)[HOY] += hoy;
-    R(tn1)[HOX] = -R(n1)[HOX];
-    R(tn1)[HOY] = -R(n1)[HOY];
-    // C2: d->j -> j->b
-    R(p2)[HN] = n2;
-    R(n2)[HP] = p2;
-    R(n2)[HS] = j;
-    R(tn2)[HG] = j;
-    R(n2)[HOX] -= hox;
-    R(n2)[HOY] -= hoy;
-    R(tn2)[HOX] = -R(n2)[HOX];
-    R(tn2)[HOY] = -R(n2)[HOY];
-    // C4: c->i -> i->j -> j->d
-    R(tn1)[HN] = h;
-    R(h)[HP] = tn1;
-    R(h)[HN] = tp2;
-    R(tp2)[HP] = h;
-    R(h)[HF] = C4;
-    // C3: b->j -> j->i -> i->a
-    R(tn2)[HN] = tw;
-    R(tw)[HP] = tn2;
-    R(tw)[HN] = tp1;
-    R(tp1)[HP] = tw;
-    R(tw)[HF] = C3;
 }
 
 // In-place edit of cell c's corner row after an exchange.
@@ -519,23 +421,69 @@ struct T1Counts {
     int overflow;   // 1: too many pending re-checks; 2: row edit failed
 };
 
+// Rows of up to this many corners are evaluated and edited by 16 lanes (an
+// exchange adds one corner, and the closing edge takes one more lane).
+constexpr int kRowLanes = 14;
+
+__device__ __forceinline__ int lane_int(int x, int lane) {
+    return __builtin_amdgcn_readlane(x, lane);
+}
+constexpr int kDppRowShl1 = 0x101;  // lane i of a row of 16 reads lane i + 1
+constexpr int kDppRowShr1 = 0x111;  // lane i of a row of 16 reads lane i - 1
+
+// Area and perimeter of four polygons, one per row of 16 lanes: lane s < m
+// holds corner s (unwrapped), m + 1 <= 16.  Valid in lane 0 of each row.  The
+// terms are added in corner order, as one lane walking the row adds them.
+__device__ __forceinline__ void quad_rows_geom(double rx, double ry, int s, int m, int m_max,
+                                               double &A, double &P) {
+    const int first = (threadIdx.x & 63) & 48;
+    const double x0 = __shfl(rx, first, 64), y0 = __shfl(ry, first, 64);
+    const double ux = s < m ? rx - x0 : 0.0, uy = s < m ? ry - y0 : 0.0;
+    // (lane 0 of a row has no lane before it and reads the 0 of `old`)
+    const double px = dpp_f64<kDppRowShr1>(ux), py = dpp_f64<kDppRowShr1>(uy);
+    const double dx = ux - px, dy = uy - py;
+    double cross = px * uy - py * ux;
+    double len = len_of(dx * dx + dy * dy);
+    double a = 0.0, per = 0.0;
+    for (int k = 1; k <= m_max; ++k) {
+        cross = dpp_f64<kDppRowShl1>(cross);
+        len = dpp_f64<kDppRowShl1>(len);
+        a += cross;
+        per += len;
+    }
+    A = 0.5 * a;
+    P = per;
+}
+
 // Sequential T1 pass over the ascending candidate list `list[0..n)` (edge
 // ids, sorted, may hold duplicates and INT_MAX padding), run by the 64
 // lanes of ONE wave with wave-uniform control flow.  Each candidate is
 // re-checked with the current positions; edges next to a processed edge
 // that become short are visited in turn as well, so the result equals
-// visiting every edge in ascending id order.  Both candidates are evaluated
-// on the four cells around the edge (lanes 0-7: stretch on cells C1..C4,
-// exchange on C1..C4, read from their corner rows with the exchange applied
-// as row edits) and the five edges at its ends; everything else is common
-// to both.  Lane 0 writes the result; the kept candidate's cell geometry
-// gives the new cell coefficients.  Not inlined: it must not raise the
-// register pressure of the loops around it.
+// visiting every edge in ascending id order.
+//
+// A candidate is a chain of dependent loads, so the pass is arranged to make
+// it short: the half-edge of the edge, then the stars of its ends i and j
+// (which name the other four half-edges, vertices, edges and cells around
+// the edge), then the four cells' rows, their corners and the positions,
+// each level loaded by as many lanes as it has entries.  With h: i -> j in
+// C1 and its twin in C2, the star of i holds h, twin(prev(h)) = i -> a (in
+// C3) and next(twin) = i -> b (in C2) counter-clockwise, the star of j holds
+// the twin, j -> d (in C4) and next(h) = j -> c (in C1).  Both outcomes are
+// evaluated on the rows C1..C4 (16 lanes each, the exchange as an edit of the
+// row) and the five edges at the ends (a lane each).  An exchange is then
+// stored from values in registers, the rows by their lanes: C1 drops j, C2
+// drops i, C3 gains j before i and C4 gains i before j, and the moved
+// half-edges change image offset by the offset of h so that every edge
+// vector is kept.  A walk by single lanes with a load per step (the form
+// before) took about 45 us per exchange and 15 us per stretch.
 template <typename PosT, typename M>
-__device__ __noinline__ T1Counts t1_sequential(const DevTissue &t, PosT *X, const DevParams<PosT> &p,
-                                               M *cap, const int32_t *list, int n, int32_t *extra,
-                                               double l_min, double l_new) {
-    const int lane = threadIdx.x & 63;
+__device__ __forceinline__ T1Counts t1_sequential(const DevTissue &t, PosT *X,
+                                                  const DevParams<PosT> &p, M *cap,
+                                                  const int32_t *list, int n, int32_t *extra,
+                                                  double l_min, double l_new) {
+    const int lane = threadIdx.x & 63, q = lane >> 4, s = lane & 15;
+    const int nv = t.n_vert;
     T1Counts out{0, 0, 0, 0, 0};
     int pos = 0, n_extra = 0;
     int last = -1;
@@ -549,6 +497,7 @@ __device__ __noinline__ T1Counts t1_sequential(const DevTissue &t, PosT *X, cons
         if (pos < n) e = list[pos];
         for (int a = 0; a < n_extra; ++a)
             if (extra[a] < e) e = extra[a];
+        e = __builtin_amdgcn_readfirstlane(e);
         if (e == 0x7fffffff) break;
         if (pos < n && list[pos] == e) ++pos;
         {   // drop e (and anything below it) from the pending set
@@ -561,106 +510,310 @@ __device__ __noinline__ T1Counts t1_sequential(const DevTissue &t, PosT *X, cons
         }
         last = e;
 
-        const int h = t.edge_he[e];
+        const int h = __builtin_amdgcn_readfirstlane(t.edge_he[e]);
         const HeRec rh = he_rec(t, h);
-        const int i = rh.src, j = rh.tgt;
+        const int i = __builtin_amdgcn_readfirstlane(rh.src);
+        const int j = __builtin_amdgcn_readfirstlane(rh.tgt);
+        const int tw = __builtin_amdgcn_readfirstlane(rh.twin);
+        const int p1 = __builtin_amdgcn_readfirstlane(rh.prev);
+        const int n1 = __builtin_amdgcn_readfirstlane(rh.next);
+        const int hox = __builtin_amdgcn_readfirstlane(rh.ox);
+        const int hoy = __builtin_amdgcn_readfirstlane(rh.oy);
+        // star slots: lanes 0-2 those of i, lanes 4-6 those of j
+        const int sl = (lane & 3) < 3 ? (lane & 3) : 0;
+        const int sv = (lane & 4) ? j : i;
+        const int32_t st_w = t.star[star_nb_at(nv, sl, sv)];
+        const int32_t st_c = t.star[star_cell_at(nv, sl, sv)];
+        const int32_t st_e = t.star[star_edge_at(nv, sl, sv)];
+        const int32_t st_h = t.star_he[sl * nv + sv];
+        const int p2_v = t.he[8 * (int64_t)tw + HP];
+        const int tn1_v = t.he[8 * (int64_t)n1 + HT];
         const double xi = (double)X[2 * (int64_t)i], yi = (double)X[2 * (int64_t)i + 1];
         const double xj = (double)X[2 * (int64_t)j], yj = (double)X[2 * (int64_t)j + 1];
-        const double dx = pdiff<double>(xj, xi, rh.ox, t.Lx), dy = pdiff<double>(yj, yi, rh.oy, t.Ly);
-        const double l = sqrt(dx * dx + dy * dy);
-        if (!(l < l_min)) continue;
+        const double dx = pdiff<double>(xj, xi, hox, t.Lx), dy = pdiff<double>(yj, yi, hoy, t.Ly);
+        const double l = len_of(dx * dx + dy * dy);
+        if (__builtin_amdgcn_readfirstlane(l < l_min ? 0 : 1)) continue;
         double ux = 1.0, uy = 0.0;
         if (l > 0.0) { ux = dx / l; uy = dy / l; }
         const double mx = xi + 0.5 * dx, my = yi + 0.5 * dy;
-        const double sxL = rh.ox * t.Lx, syL = rh.oy * t.Ly;
+        const double sxL = hox * t.Lx, syL = hoy * t.Ly;
         const PosOverride<PosT> S{i, j, mx - hl * ux, my - hl * uy, mx + hl * ux - sxL, my + hl * uy - syL};
         const double nx = -uy, ny = ux;
         const PosOverride<PosT> T{i, j, mx + hl * nx, my + hl * ny, mx - hl * nx - sxL, my - hl * ny - syL};
 
-        const int tw = rh.twin, p1 = rh.prev, n1 = rh.next;
-        const HeRec rt = he_rec(t, tw), rp1 = he_rec(t, p1), rn1 = he_rec(t, n1);
-        const int p2 = rt.prev, n2 = rt.next;
-        const HeRec rp2 = he_rec(t, p2), rn2 = he_rec(t, n2);
-        const int tp1 = rp1.twin, tn1 = rn1.twin, tn2 = rn2.twin;
-        const int C1 = rh.face, C2 = rt.face;
-        const int C3 = he_rec(t, tp1).face, C4 = he_rec(t, tn1).face;
-        const bool distinct = C1 != C2 && C1 != C3 && C1 != C4 && C2 != C3 && C2 != C4 && C3 != C4;
-        const bool admissible = distinct && t.nsides[C1] > 3 && t.nsides[C2] > 3;
+        // slots after that of h (at i) and of the twin (at j)
+        const uint64_t at_i = __builtin_amdgcn_ballot_w64(lane < 3 && st_h == h);
+        const uint64_t at_j = __builtin_amdgcn_ballot_w64(lane >= 4 && lane < 7 && st_h == tw);
+        const int s0 = at_i ? __builtin_ctzll(at_i) : 0, s4 = at_j ? __builtin_ctzll(at_j) - 4 : 0;
+        const int la = (s0 + 1) % 3, lb = (s0 + 2) % 3, ld = 4 + (s4 + 1) % 3, lc = 4 + (s4 + 2) % 3;
+        const int wa = lane_int(st_w, la), wb = lane_int(st_w, lb), wc = lane_int(st_w, lc),
+                  wd = lane_int(st_w, ld);
+        const int ea = lane_int(st_e, la), eb = lane_int(st_e, lb), ec = lane_int(st_e, lc),
+                  ed = lane_int(st_e, ld);
+        const int tp1 = lane_int(st_h, la), n2 = lane_int(st_h, lb), tp2 = lane_int(st_h, ld);
+        const int C1 = lane_int(st_c, s0), C2 = lane_int(st_c, 4 + s4), C3 = lane_int(st_c, la),
+                  C4 = lane_int(st_c, ld);
+        const int p2 = __builtin_amdgcn_readfirstlane(p2_v);
+        const int tn1 = __builtin_amdgcn_readfirstlane(tn1_v);
+        // half-edges the kept offsets refer to: a -> i, j -> c, d -> j, i -> b
+        const int p1x = -ox_of(wa), p1y = -oy_of(wa), n1x = ox_of(wc), n1y = oy_of(wc);
+        const int p2x = -ox_of(wd), p2y = -oy_of(wd), n2x = ox_of(wb), n2y = oy_of(wb);
+        const int va_ = id_of(wa), vb_ = id_of(wb), vc_ = id_of(wc), vd_ = id_of(wd);
 
-        // lanes 0..3: stretch geometry of C1..C4; lanes 4..7: exchange geometry
-        const int q = lane & 3;
+        // the cells: row q of lanes has C1..C4
         const int cq = q == 0 ? C1 : q == 1 ? C2 : q == 2 ? C3 : C4;
-        double A = 0.0, P = 0.0, Eq = 0.0;
-        if (lane < 4 || (lane < 8 && admissible)) {
-            // stretch: no row edit.  Exchange: C1 drops j, C2 drops i, C3
-            // gains j before i, C4 gains i before j.  One call site for both.
-            const bool ex = lane >= 4;
-            const int ed = !ex ? 0 : (q < 2 ? 1 : 2);
-            const int va = !ex ? -1 : ((q == 0 || q == 3) ? j : i);
-            const int vb = !ex ? -1 : (q == 2 ? j : (q == 3 ? i : -1));
-            const int sx = !ex ? 0 : (q == 2 ? rh.ox : (q == 3 ? -rh.ox : 0));
-            const int sy = !ex ? 0 : (q == 2 ? rh.oy : (q == 3 ? -rh.oy : 0));
-            row_geom<PosT>(t, X, cq, ex ? T : S, ed, va, vb, sx, sy, A, P);
-            Eq = cell_energy<PosT>(p, cq, A, P);
+        const int rb = t.row_ptr[cq], nq = t.nsides[cq], rc = t.row_cap[cq];
+        const double ka = (double)p.ka(cq), a0 = (double)p.a0(cq), kp = (double)p.kp(cq),
+                     p0 = (double)p.p0(cq);
+        const int tn2_v = t.he[8 * (int64_t)n2 + HT];
+        // stars of c (lanes 0-2) and b (lanes 4-6), which change neighbour
+        const int cv = (lane & 4) ? vb_ : vc_;
+        const int32_t cb_w = t.star[star_nb_at(nv, sl, cv)];
+        const int32_t cb_c = t.star[star_cell_at(nv, sl, cv)];
+        const int32_t cb_e = t.star[star_edge_at(nv, sl, cv)];
+        const int32_t cb_h = t.star_he[sl * nv + cv];
+        // (a, b, c and d are neither i nor j where C1..C4 are distinct)
+        // the five edges at i and j: lanes 0-4 for the stretch, 8-12 for the
+        // exchange (i -> c and j -> b replace j -> c and i -> b)
+        const int er = lane & 7;
+        const int ev = er == 1 ? va_ : er == 2 ? vc_ : er == 3 ? vd_ : vb_;
+        const int ee = er == 0 ? e : er == 1 ? ea : er == 2 ? ec : er == 3 ? ed : eb;
+        const double xf = (double)X[2 * (int64_t)ev], yf = (double)X[2 * (int64_t)ev + 1];
+        const double el = (double)p.lm(ee);
+
+        const bool distinct = C1 != C2 && C1 != C3 && C1 != C4 && C2 != C3 && C2 != C4 && C3 != C4;
+        const int nC1 = lane_int(nq, 0), nC2 = lane_int(nq, 16), nC3 = lane_int(nq, 32),
+                  nC4 = lane_int(nq, 48);
+        const bool admissible = distinct && nC1 > 3 && nC2 > 3;
+        const int n_max = max(max(nC1, nC2), max(nC3, nC4));
+        const bool wide = n_max <= kRowLanes;
+        // the exchange as an edit of row q: C1 drops j, C2 drops i, C3 gains j
+        // before i, C4 gains i before j
+        const int ed_q = q < 2 ? 1 : 2;
+        const int ev_a = (q == 0 || q == 3) ? j : i;
+        const int ev_b = q == 2 ? j : i;
+        const int esx = q == 2 ? hox : -hox, esy = q == 2 ? hoy : -hoy;
+
+        int32_t cw = 0, ch = 0, xw = 0, xh = 0;  // the lane's corner now and after the exchange
+        int xox = 0, xoy = 0, xm = 0;            // its image, and the corners after the exchange
+        bool ok = true;                          // the row holds the vertex to edit at
+        double AS = 0.0, PS = 0.0, AT = 0.0, PT = 0.0;
+        if (wide) {
+            const int at = rb + (s < nq ? s : 0);
+            cw = t.corner[at];
+            ch = t.corner_he[at];
+            const int v = id_of(cw);
+            double x = (double)X[2 * (int64_t)v], y = (double)X[2 * (int64_t)v + 1];
+            double xs = v == i ? S.xi : v == j ? S.xj : x, ys = v == i ? S.yi : v == j ? S.yj : y;
+            quad_rows_geom(xs + ox_of(cw) * t.Lx, ys + oy_of(cw) * t.Ly, s, nq, n_max, AS, PS);
+            if (admissible) {
+                const uint64_t hit = __builtin_amdgcn_ballot_w64(s < nq && v == ev_a);
+                const int hits = (int)((hit >> (16 * q)) & 0xffffu);
+                ok = hits != 0;
+                const int k = ok ? __builtin_ctz(hits) : 0;
+                // corner s of the edited row: one of the old row, or the new one
+                xm = ed_q == 1 ? nq - 1 : nq + 1;
+                const bool ins = ed_q == 2 && s == k;
+                const int from = (lane & 48) + (ed_q == 1 ? (s < k ? s : min(s + 1, 15))
+                                                          : (s <= k ? s : s - 1));
+                xw = __shfl(cw, from, 64);
+                xh = __shfl(ch, from, 64);
+                const double fx = __shfl(x, from, 64), fy = __shfl(y, from, 64);
+                const int xv = ins ? ev_b : id_of(xw);
+                xox = ox_of(xw) + (ins ? esx : 0);
+                xoy = oy_of(xw) + (ins ? esy : 0);
+                // the corner before a dropped vertex leaves by a new half-edge
+                const int kp_new = k > 0 ? k - 1 : nq - 2;
+                if (ed_q == 1 && s == kp_new) xh = q == 0 ? n1 : n2;
+                if (ins) xh = q == 2 ? tw : h;
+                xw = xv;  // the id; the image is added when it is stored
+                const double xt = xv == i ? T.xi : xv == j ? T.xj : fx;
+                const double yt = xv == i ? T.yi : xv == j ? T.yj : fy;
+                quad_rows_geom(xt + xox * t.Lx, yt + xoy * t.Ly, s, xm, n_max + 1, AT, PT);
+            }
+        } else if (s == 0) {
+            row_geom<PosT>(t, X, cq, S, 0, -1, -1, 0, 0, AS, PS);
+            if (admissible) row_geom<PosT>(t, X, cq, T, ed_q, ev_a, ev_b, esx, esy, AT, PT);
         }
         bool take_T = false;
         if (admissible) {
-            const double ES = ((__shfl(Eq, 0, 64) + __shfl(Eq, 1, 64)) + __shfl(Eq, 2, 64)) +
-                              __shfl(Eq, 3, 64);
-            const double ET0 = ((__shfl(Eq, 4, 64) + __shfl(Eq, 5, 64)) + __shfl(Eq, 6, 64)) +
-                               __shfl(Eq, 7, 64);
-            // edges i->c and j->b replace j->c and i->b in the exchange
-            const double lh = (double)p.lm(e);
-            const double lp1 = (double)p.lm(t.he_edge[p1]), ln1 = (double)p.lm(t.he_edge[n1]);
-            const double lp2 = (double)p.lm(t.he_edge[p2]), ln2 = (double)p.lm(t.he_edge[n2]);
-            const double ESe = lh * ov_len<PosT>(t, X, S, i, j, rh.ox, rh.oy) +
-                               lp1 * ov_len<PosT>(t, X, S, rp1.src, i, rp1.ox, rp1.oy) +
-                               ln1 * ov_len<PosT>(t, X, S, j, rn1.tgt, rn1.ox, rn1.oy) +
-                               lp2 * ov_len<PosT>(t, X, S, rp2.src, j, rp2.ox, rp2.oy) +
-                               ln2 * ov_len<PosT>(t, X, S, i, rn2.tgt, rn2.ox, rn2.oy);
-            const double ETe = lh * ov_len<PosT>(t, X, T, i, j, rh.ox, rh.oy) +
-                               lp1 * ov_len<PosT>(t, X, T, rp1.src, i, rp1.ox, rp1.oy) +
-                               ln1 * ov_len<PosT>(t, X, T, i, rn1.tgt, rn1.ox + rh.ox, rn1.oy + rh.oy) +
-                               lp2 * ov_len<PosT>(t, X, T, rp2.src, j, rp2.ox, rp2.oy) +
-                               ln2 * ov_len<PosT>(t, X, T, j, rn2.tgt, rn2.ox - rh.ox, rn2.oy - rh.oy);
-            take_T = ET0 + ETe < ES + ESe;
+            auto energy = [&](double A, double P) {
+                const double da = A - a0, dp = P - p0;
+                return ka * da * da + kp * dp * dp;
+            };
+            const double eS = energy(AS, PS), eT = energy(AT, PT);
+            const double ES = ((readlane_f64(eS, 0) + readlane_f64(eS, 16)) + readlane_f64(eS, 32)) +
+                              readlane_f64(eS, 48);
+            const double ET0 = ((readlane_f64(eT, 0) + readlane_f64(eT, 16)) + readlane_f64(eT, 32)) +
+                               readlane_f64(eT, 48);
+            const bool exch = (lane & 8) != 0;
+            const double ix = exch ? T.xi : S.xi, iy = exch ? T.yi : S.yi;
+            const double jx = exch ? T.xj : S.xj, jy = exch ? T.yj : S.yj;
+            // source and target of the edge, its image offset
+            const bool c_at_i = er == 2 && exch, b_at_j = er == 4 && exch;
+            const double gx = er == 0 ? jx : er == 1 ? ix : er == 3 ? jx : xf;
+            const double gy = er == 0 ? jy : er == 1 ? iy : er == 3 ? jy : yf;
+            const double sx = er == 0 ? ix : er == 2 ? (c_at_i ? ix : jx)
+                                                     : er == 4 ? (b_at_j ? jx : ix) : xf;
+            const double sy = er == 0 ? iy : er == 2 ? (c_at_i ? iy : jy)
+                                                     : er == 4 ? (b_at_j ? jy : iy) : yf;
+            const int ox = er == 0 ? hox : er == 1 ? p1x : er == 2 ? n1x + (c_at_i ? hox : 0)
+                         : er == 3 ? p2x : n2x - (b_at_j ? hox : 0);
+            const int oy = er == 0 ? hoy : er == 1 ? p1y : er == 2 ? n1y + (c_at_i ? hoy : 0)
+                         : er == 3 ? p2y : n2y - (b_at_j ? hoy : 0);
+            const double ddx = gx + ox * t.Lx - sx, ddy = gy + oy * t.Ly - sy;
+            const double le = el * len_of(ddx * ddx + ddy * ddy);
+            auto edges = [&](int o) {
+                return (((readlane_f64(le, o) + readlane_f64(le, o + 1)) + readlane_f64(le, o + 2)) +
+                        readlane_f64(le, o + 3)) + readlane_f64(le, o + 4);
+            };
+            take_T = ET0 + edges(8) < ES + edges(0);
         }
-        const PosOverride<PosT> W = take_T ? T : S;
-        // the kept candidate's lanes write the new coefficients of C1..C4
-        if ((take_T && lane >= 4 && lane < 8) || (!take_T && lane < 4)) {
-            cap[2 * (int64_t)cq] = (M)(2.0 * (double)p.ka(cq) * (A - (double)p.a0(cq)));
-            cap[2 * (int64_t)cq + 1] = (M)(2.0 * (double)p.kp(cq) * (P - (double)p.p0(cq)));
+        take_T = __builtin_amdgcn_readfirstlane(take_T ? 1 : 0) != 0;
+        const double Wxi = take_T ? T.xi : S.xi, Wyi = take_T ? T.yi : S.yi;
+        const double Wxj = take_T ? T.xj : S.xj, Wyj = take_T ? T.yj : S.yj;
+        // coefficients of C1..C4 from the kept outcome's geometry
+        if (s == 0) {
+            cap[2 * (int64_t)cq] = (M)(2.0 * ka * ((take_T ? AT : AS) - a0));
+            cap[2 * (int64_t)cq + 1] = (M)(2.0 * kp * ((take_T ? PT : PS) - p0));
         }
-        __builtin_amdgcn_wave_barrier();
         if (lane == 0) {
-            X[2 * (int64_t)i] = (PosT)W.xi;
-            X[2 * (int64_t)i + 1] = (PosT)W.yi;
-            X[2 * (int64_t)j] = (PosT)W.xj;
-            X[2 * (int64_t)j + 1] = (PosT)W.yj;
-            if (take_T) {
-                t1_patch(t, h);
+            X[2 * (int64_t)i] = (PosT)Wxi;
+            X[2 * (int64_t)i + 1] = (PosT)Wyi;
+            X[2 * (int64_t)j] = (PosT)Wxj;
+            X[2 * (int64_t)j + 1] = (PosT)Wyj;
+        }
+        if (take_T) {
+            const int tn2 = __builtin_amdgcn_readfirstlane(tn2_v);
+            const int c1x = n1x + hox, c1y = n1y + hoy;  // i -> c
+            const int b2x = n2x - hox, b2y = n2y - hoy;  // j -> b
+            if (lane == 0) {
+                auto R = [&](int x) { return t.he + 8 * (int64_t)x; };
+                // C1: a->i -> i->c
+                R(p1)[HN] = n1;
+                R(n1)[HP] = p1;
+                R(n1)[HS] = i;
+                R(tn1)[HG] = i;
+                R(n1)[HOX] = c1x;
+                R(n1)[HOY] = c1y;
+                R(tn1)[HOX] = -c1x;
+                R(tn1)[HOY] = -c1y;
+                // C2: d->j -> j->b
+                R(p2)[HN] = n2;
+                R(n2)[HP] = p2;
+                R(n2)[HS] = j;
+                R(tn2)[HG] = j;
+                R(n2)[HOX] = b2x;
+                R(n2)[HOY] = b2y;
+                R(tn2)[HOX] = -b2x;
+                R(tn2)[HOY] = -b2y;
+                // C4: c->i -> i->j -> j->d
+                R(tn1)[HN] = h;
+                R(h)[HP] = tn1;
+                R(h)[HN] = tp2;
+                R(tp2)[HP] = h;
+                R(h)[HF] = C4;
+                // C3: b->j -> j->i -> i->a
+                R(tn2)[HN] = tw;
+                R(tw)[HP] = tn2;
+                R(tw)[HN] = tp1;
+                R(tp1)[HP] = tw;
+                R(tw)[HF] = C3;
                 if (t.cell_he[C1] == h) t.cell_he[C1] = n1;
                 if (t.cell_he[C2] == tw) t.cell_he[C2] = n2;
-                // rows: C1 drops j (i now leaves by n1), C2 drops i (j leaves
-                // by n2), C3 gains j (leaving by tw) before i, C4 gains i (by
-                // h) before j
-                bool ok = row_edit(t, C1, 1, j, -1, n1, 0, 0, &out.relocated);
-                ok = row_edit(t, C2, 1, i, -1, n2, 0, 0, &out.relocated) && ok;
-                ok = row_edit(t, C3, 2, i, j, tw, rh.ox, rh.oy, &out.relocated) && ok;
-                ok = row_edit(t, C4, 2, j, i, h, -rh.ox, -rh.oy, &out.relocated) && ok;
-                if (!ok) out.overflow = 2;
-                // stars of i and j are rebuilt; c and b changed neighbour
-                star_refresh(t, i, h);
-                star_refresh(t, j, tw);
-                star_refresh(t, rn1.tgt, tn1);   // c
-                star_refresh(t, rn2.tgt, tn2);   // b
+            }
+            // stars: i from h (i->j, i->c, i->a), j from the twin (j->i, j->b,
+            // j->d); c and b turned so that the changed half-edge comes first
+            if ((lane & 3) < 3 && lane < 7) {
+                const int k = lane & 3;
+                const bool at_j2 = (lane & 4) != 0;
+                const int v = at_j2 ? j : i;
+                int32_t w, c, ed2, he2;
+                if (!at_j2) {
+                    w = k == 0 ? pack_id(j, hox, hoy) : k == 1 ? pack_id(vc_, c1x, c1y) : wa;
+                    c = k == 0 ? C4 : k == 1 ? C1 : C3;
+                    ed2 = k == 0 ? e : k == 1 ? ec : ea;
+                    he2 = k == 0 ? h : k == 1 ? n1 : tp1;
+                } else {
+                    w = k == 0 ? pack_id(i, -hox, -hoy) : k == 1 ? pack_id(vb_, b2x, b2y) : wd;
+                    c = k == 0 ? C3 : k == 1 ? C2 : C4;
+                    ed2 = k == 0 ? e : k == 1 ? eb : ed;
+                    he2 = k == 0 ? tw : k == 1 ? n2 : tp2;
+                }
+                t.star[star_nb_at(nv, k, v)] = w;
+                t.star[star_cell_at(nv, k, v)] = c;
+                t.star[star_edge_at(nv, k, v)] = ed2;
+                t.star_he[k * nv + v] = he2;
+            }
+            {
+                const int moved = (lane & 4) ? tn2 : tn1;
+                const bool slot = (lane & 3) < 3 && lane < 7;
+                const uint64_t first = __builtin_amdgcn_ballot_w64(slot && cb_h == moved);
+                const int f0 = (int)(first & 7u), f1 = (int)((first >> 4) & 7u);
+                const int f = (lane & 4) ? (f1 ? __builtin_ctz(f1) : 0) : (f0 ? __builtin_ctz(f0) : 0);
+                if (slot) {
+                    const int k = ((lane & 3) + 3 - f) % 3;
+                    const int32_t w = k != 0 ? cb_w
+                                             : (lane & 4) ? pack_id(j, -b2x, -b2y)
+                                                          : pack_id(i, -c1x, -c1y);
+                    t.star[star_nb_at(nv, k, cv)] = w;
+                    t.star[star_cell_at(nv, k, cv)] = cb_c;
+                    t.star[star_edge_at(nv, k, cv)] = cb_e;
+                    t.star_he[k * nv + cv] = cb_h;
+                }
+            }
+            // rows
+            if (wide) {
+                // a row without a spare slot moves to the pool (C3 first)
+                const bool grow = ed_q == 2 && xm > rc;
+                const uint64_t grows = __builtin_amdgcn_ballot_w64(grow);
+                const bool g3 = ((grows >> 32) & 1u) != 0, g4 = ((grows >> 48) & 1u) != 0;
+                int rb2 = rb;
+                if (g3 || g4) {
+                    const int top = __builtin_amdgcn_readfirstlane(*t.pool_top);
+                    const int cap3 = g3 ? nC3 + 1 + kRowExtra : 0, cap4 = g4 ? nC4 + 1 + kRowExtra : 0;
+                    if (top + cap3 + cap4 > t.corner_cap) ok = false;
+                    if (grow) rb2 = q == 2 ? top : top + cap3;
+                    if (lane == 0) *t.pool_top = top + cap3 + cap4;
+                    out.relocated = 1;
+                }
+                // images relative to the (new) first corner
+                xox -= lane_int(xox, 0) * (q == 0) + lane_int(xox, 16) * (q == 1) +
+                       lane_int(xox, 32) * (q == 2) + lane_int(xox, 48) * (q == 3);
+                xoy -= lane_int(xoy, 0) * (q == 0) + lane_int(xoy, 16) * (q == 1) +
+                       lane_int(xoy, 32) * (q == 2) + lane_int(xoy, 48) * (q == 3);
+                if (s < xm && (xox < -1 || xox > 1 || xoy < -1 || xoy > 1)) ok = false;
+                if (__builtin_amdgcn_ballot_w64(!ok) != 0) {
+                    out.overflow = 2;
+                } else {
+                    if (s < xm) {
+                        t.corner[rb2 + s] = pack_id(xw, xox, xoy);
+                        t.corner_he[rb2 + s] = xh;
+                    }
+                    if (s == 0) {
+                        t.nsides[cq] = xm;
+                        if (grow) {
+                            t.row_ptr[cq] = rb2;
+                            t.row_cap[cq] = xm + kRowExtra;
+                        }
+                    }
+                }
+            } else {
+                int bad = 0, moved = 0;
+                if (lane == 0) {
+                    bool good = row_edit(t, C1, 1, j, -1, n1, 0, 0, &moved);
+                    good = row_edit(t, C2, 1, i, -1, n2, 0, 0, &moved) && good;
+                    good = row_edit(t, C3, 2, i, j, tw, hox, hoy, &moved) && good;
+                    good = row_edit(t, C4, 2, j, i, h, -hox, -hoy, &moved) && good;
+                    bad = good ? 0 : 1;
+                }
+                if (lane_int(bad, 0)) out.overflow = 2;
+                if (lane_int(moved, 0)) out.relocated = 1;
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        out.overflow = __shfl(out.overflow, 0, 64);
-        out.relocated = __shfl(out.relocated, 0, 64);
         if (out.overflow == 2) return out;
         if (take_T) {
             ++out.swaps;
@@ -669,16 +822,30 @@ __device__ __noinline__ T1Counts t1_sequential(const DevTissue &t, PosT *X, cons
             ++out.stretches;
         }
         // the four other edges at i and j may have become short: a->i, and
-        // i->c, d->j, j->b after an exchange (j->c, i->b after a stretch)
-        const int nbr[4] = {p1, n1, p2, n2};
-        const int ns[4] = {rp1.src, take_T ? i : j, rp2.src, take_T ? j : i};
-        const int ng[4] = {i, rn1.tgt, j, rn2.tgt};
-        const int nox[4] = {rp1.ox, rn1.ox + (take_T ? rh.ox : 0), rp2.ox, rn2.ox - (take_T ? rh.ox : 0)};
-        const int noy[4] = {rp1.oy, rn1.oy + (take_T ? rh.oy : 0), rp2.oy, rn2.oy - (take_T ? rh.oy : 0)};
-        for (int a = 0; a < 4; ++a) {
-            const int e2 = t.he_edge[nbr[a]];
-            if (e2 <= e) continue;
-            if (ov_len<PosT>(t, X, W, ns[a], ng[a], nox[a], noy[a]) < l_min) {
+        // i->c, d->j, j->b after an exchange (j->c, i->b after a stretch);
+        // lanes 0-3 in the order a, c, d, b
+        {
+            const double far_x = __shfl(xf, (lane & 3) + 1, 64), far_y = __shfl(yf, (lane & 3) + 1, 64);
+            const int r = lane & 3;
+            const bool near_i = r == 0 || (r == 1 && take_T) || (r == 3 && !take_T);
+            const double wx = near_i ? Wxi : Wxj, wy = near_i ? Wyi : Wyj;
+            // (the far end is i or j itself only in tilings of a few cells)
+            const int fv = r == 0 ? va_ : r == 1 ? vc_ : r == 2 ? vd_ : vb_;
+            const double farx = fv == i ? Wxi : fv == j ? Wxj : far_x;
+            const double fary = fv == i ? Wyi : fv == j ? Wyj : far_y;
+            const bool out_going = (r & 1) != 0;  // from i or j to the far vertex
+            const int ox = r == 0 ? p1x : r == 1 ? n1x + (take_T ? hox : 0)
+                         : r == 2 ? p2x : n2x - (take_T ? hox : 0);
+            const int oy = r == 0 ? p1y : r == 1 ? n1y + (take_T ? hoy : 0)
+                         : r == 2 ? p2y : n2y - (take_T ? hoy : 0);
+            const double gx = out_going ? farx : wx, gy = out_going ? fary : wy;
+            const double fx = out_going ? wx : farx, fy = out_going ? wy : fary;
+            const double ddx = gx + ox * t.Lx - fx, ddy = gy + oy * t.Ly - fy;
+            const uint64_t shorts = __builtin_amdgcn_ballot_w64(
+                lane < 4 && len_of(ddx * ddx + ddy * ddy) < l_min);
+            for (int a = 0; a < 4; ++a) {
+                const int e2 = a == 0 ? ea : a == 1 ? ec : a == 2 ? ed : eb;
+                if (e2 <= e || !((shorts >> a) & 1u)) continue;
                 bool present = false;
                 for (int b = 0; b < n_extra; ++b) present |= extra[b] == e2;
                 if (!present) {

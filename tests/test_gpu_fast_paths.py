@@ -156,3 +156,41 @@ def test_one_launch_step_equals_the_batched_loop(vtx, mode, t1, n_cell, chunk):
         F = T1.energy_forces(X1, P, mode=mode)[1]
         assert torch.equal(F, T1.vertex_forces(X1, P, T1.cell_coeffs(X1, P, mode=mode),
                                                mode=mode)[0])
+
+
+def _fan(n_petals):
+    """A tiling with one cell of many sides: n_petals seeds on a circle around
+    one, the rest at random outside."""
+    L = 14.0
+    rng = np.random.default_rng(n_petals)
+    a = 2.0 * np.pi * (np.arange(n_petals) + 0.3) / n_petals
+    ring = 7.0 + 2.0 * np.stack([np.cos(a), np.sin(a)], 1)
+    out = rng.uniform(0.0, L, size=(400, 2))
+    out = out[np.hypot(*(out - 7.0).T) > 2.6][:150]
+    return g.periodic_voronoi(np.concatenate([[[7.0, 7.0]], ring, out]), L, L)
+
+
+@pytest.mark.parametrize("mode", ["f64", "f32"])
+@pytest.mark.parametrize("petals", [12, 13, 14, 15, 16, 22])
+def test_t1_pass_around_long_rows(vtx, oracle, petals, mode):
+    """T1 passes next to a cell of 12 to 22 sides: rows of up to 14 corners
+    are evaluated and edited by 16 lanes, longer ones by one.  Topology and
+    counts are the oracle's exactly."""
+    V = vtx
+    t = _fan(petals)
+    sides = np.bincount(t.he[:, g.HE_FACE])
+    assert sides.max() == petals
+    p = g.uniform_params(t, P0=3.6, lam=0.1)
+    X = _dev(t.X, V.pos_dtype(mode))
+    Xo = X.cpu().numpy().astype(np.float64)
+    T, m = V.Tissue.from_tissue(t), oracle.Mesh.from_tissue(t)
+    for l_min in (0.05, 1.2 * 2.0 * np.pi / petals):  # the second takes the long cell's own sides
+        got = T.t1(X, V.Params(P0=3.6, lam=0.1), l_min, mode=mode)
+        ref = oracle.t1_pass(m, Xo, p, l_min, 2.0 * l_min)
+        if mode == "f32":  # the oracle goes on from the stored positions
+            Xo = X.cpu().numpy().astype(np.float64)
+        assert got[0] > 0 and tuple(got) == tuple(ref)[:2]
+        assert np.array_equal(T.topology(), m.he)
+    F = T.energy_forces(X, V.Params(P0=3.6, lam=0.1), mode=mode)[1]
+    Fo = oracle.energy_forces(m, Xo, p)[1]
+    assert np.abs(F.cpu().numpy() - Fo).max() / np.abs(Fo).max() < (1e-10 if mode == "f64" else 1e-5)
