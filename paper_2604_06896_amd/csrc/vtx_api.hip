@@ -52,6 +52,7 @@ struct vtx_tissue_s {
     TileTables tiles;    // fused evaluation; rebuilt in stream order after topology changes
     int64_t n_vert, n_cell, n_edge, n_he;
     double *ep_buf;      // two position buffers for EP (double-sized)
+    HessRows hess;       // one-launch CG step; allocated at the first solve that takes it
     int64_t t1_cap;
 };
 
@@ -93,6 +94,12 @@ ParamsRaw raw(const vtx_params *p) {
 // captured graph.
 constexpr int64_t kStepMaxVerts = 131072;
 constexpr int kStepChunk = 252;
+
+// The same for the one-launch CG step (even, so that every replay starts on
+// the same vectors).
+constexpr int64_t kCgStepMaxVerts = 65536;
+constexpr int kCgChunk = 256;
+static_assert(kCgStepMaxVerts <= kStepMaxVerts, "per-block results");
 
 // Host copy of the staged layouts.
 struct Staged {
@@ -243,6 +250,7 @@ void free_tissue(vtx_tissue t) {
                     t->w.cap, t->w.cell_aux, t->w.partials, t->w.partials2, t->w.mpart,
                     t->w.t1_list,
                     t->w.ctl, t->w.cg, t->w.scal, t->w.one, t->w.step, t->w.step_part,
+                    t->w.cg_state, t->w.max_sides, t->hess.col, t->hess.top, t->hess.bottom,
                     t->ep_buf,
                     t->tiles.cells, t->tiles.info, t->tiles.halo, t->tiles.cstart,
                     t->tiles.corners, t->tiles.fstar, t->tiles.fe};
@@ -250,6 +258,7 @@ void free_tissue(vtx_tissue t) {
         if (p) (void)hipFree(p);
     if (t->w.ctl_host) (void)hipHostFree(t->w.ctl_host);
     if (t->w.step_host) (void)hipHostFree(t->w.step_host);
+    if (t->w.cg_host) (void)hipHostFree(t->w.cg_host);
     if (t->w.cap_stream) (void)hipStreamDestroy(t->w.cap_stream);
     delete t;
 }
@@ -483,6 +492,7 @@ int vtx_tissue_create(const int32_t *he, int64_t n_he, int64_t n_vert, int64_t n
     std::memset(&t->d, 0, sizeof t->d);
     std::memset(&t->w, 0, sizeof t->w);
     t->ep_buf = nullptr;
+    t->hess = HessRows{};
     t->n_vert = n_vert;
     t->n_cell = n_cell;
     t->n_he = n_he;
@@ -541,7 +551,9 @@ int vtx_tissue_create(const int32_t *he, int64_t n_he, int64_t n_vert, int64_t n
     A(&w.one, kOneBytes);
     A((void **)&w.step, sizeof(StepCtl));
     A((void **)&w.step_part,
-      2 * sizeof(double) * (size_t)((4 * std::min(n_vert, kStepMaxVerts) + kBlock - 1) / kBlock));
+      2 * 4 * sizeof(double) * (size_t)((4 * std::min(n_vert, kStepMaxVerts) + kBlock - 1) / kBlock));
+    A((void **)&w.cg_state, 2 * sizeof(CgState));
+    A((void **)&w.max_sides, sizeof(int32_t));
     A((void **)&t->ep_buf, 2 * 16 * (size_t)n_vert);
     const size_t n_tiles = (size_t)n_tiles_for(n_vert);
     A((void **)&t->tiles.cells, 4 * (size_t)kTileCap * n_tiles);
@@ -553,6 +565,7 @@ int vtx_tissue_create(const int32_t *he, int64_t n_he, int64_t n_vert, int64_t n
     A((void **)&t->tiles.fe, 8 * (size_t)n_vert);
     if (e == hipSuccess) e = hipHostMalloc((void **)&w.ctl_host, 2 * sizeof(LoopCtl), 0);
     if (e == hipSuccess) e = hipHostMalloc((void **)&w.step_host, sizeof(StepCtl), 0);
+    if (e == hipSuccess) e = hipHostMalloc((void **)&w.cg_host, 2 * sizeof(CgState), 0);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&w.cap_stream, hipStreamNonBlocking);
     if (e == hipSuccess) {
         LoopCtl z{};
@@ -767,6 +780,50 @@ int vtx_v2v(vtx_tissue t, int32_t mode, const void *X, const void *X_target, dou
     return check_launch("vtx_v2v");
 }
 
+// CG by one launch per iteration (k_cg_step) on the rows of the Hessian,
+// FP64; the solution is left in w.cg, not yet projected.  The rows' memory is
+// the tissue's, kept for later solves, and grows with the largest cell.
+static int cg_steps(vtx_tissue t, const void *X, const vtx_params *p, const double *b, double tol,
+                    int64_t max_iter, hipStream_t s, vtx_grad_result *r) {
+    CgState &h = t->w.cg_host[0];
+    launch_max_sides(t->d, t->w, s);
+    int rc;
+    if ((rc = check_launch("largest cell"))) return rc;
+    h = CgState{};
+    HIPCHK(hipMemcpyAsync(t->w.cg_state, &h, sizeof h, hipMemcpyHostToDevice, s));
+    int32_t sides = 0;
+    HIPCHK(hipMemcpyAsync(&sides, t->w.max_sides, sizeof sides, hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    HessRows &H = t->hess;
+    if (sides - 2 > H.width) {
+        const int width = std::max(sides - 2, 6);  // six: cells of up to eight sides
+        const size_t n = (size_t)width * (size_t)hess_lanes(t->n_vert);
+        void *old[] = {H.col, H.top, H.bottom};
+        H = HessRows{};
+        for (void *q : old)
+            if (q) HIPCHK(hipFree(q));
+        HIPCHK(hipMalloc((void **)&H.col, 4 * n));
+        HIPCHK(hipMalloc((void **)&H.top, 16 * n));
+        HIPCHK(hipMalloc((void **)&H.bottom, 16 * n));
+        H.width = width;
+    }
+    HessRows use = H;
+    use.width = sides - 2;  // slots in use now
+    launch_hess_rows(t->d, t->w, use, X, raw(p), s);
+    launch_cg_step_init(t->w, (int)t->n_vert, b, s);
+    if ((rc = check_launch("Hessian rows"))) return rc;
+    rc = run_loop(
+        t, kCgChunk, max_iter + 2, s,
+        [&](int k, hipStream_t cs) { launch_cg_step(t->d, t->w, use, tol, max_iter, k, cs); },
+        [&]() { return hipMemcpyAsync(&h, t->w.cg_state, sizeof h, hipMemcpyDeviceToHost, s); },
+        [&]() { return h.done != 0; });
+    if (rc) return rc;
+    r->cg_iters = h.it;
+    r->cg_rel_res = h.rel_res;
+    r->status = h.status;
+    return VTX_OK;
+}
+
 // Solves H x = P b at X (H restricted to the zero-mean subspace) by CG or
 // MINRES on the device, x left projected in the first workspace vector, then
 // contracts it with the mixed derivatives of theta into g unless g is NULL.
@@ -784,6 +841,12 @@ static int solve_hessian(vtx_tissue t, int mode, const void *X, const vtx_params
         return VTX_OK;
     }
     launch_cell_coeffs(t->d, t->w, mode, X, raw(p), s);
+    if (mode == VTX_F64 && !minres && t->n_vert <= kCgStepMaxVerts) {
+        if ((rc = cg_steps(t, X, p, b, tol, max_iter, s, r))) return rc;
+        launch_project(t->w, nv, t->w.cg, s);
+        if (g) launch_contract(t->d, mode, X, raw(p), theta, t->w.cg, g, s);
+        return check_launch("CG solve");
+    }
     LoopCtl c{};
     c.status = VTX_CG_MAXITER;
     c.tol = tol;

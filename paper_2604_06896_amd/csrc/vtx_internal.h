@@ -176,6 +176,23 @@ struct StepCtl {
     uint32_t cnt[3];     // short edges: read k mod 3, add to the next, clear the one after
 };
 
+// Scalars of the one-launch CG step (k_cg_step) between launches.
+struct CgState {
+    double rr0, rel_res, alpha;
+    int64_t it;
+    int32_t started;     // a launch has formed H q
+    int32_t done, status, pad;
+};
+
+// Rows of the Hessian at fixed positions for k_cg_step: quad of lanes 4 v to
+// 4 v + 3 of vertex v, slot j of a lane at [j * lanes + lane] (`lanes` a
+// multiple of the block size): column and 2 x 2 block.
+struct HessRows {
+    int32_t *col;
+    double2 *top, *bottom;
+    int32_t width;       // slots allocated per lane (0: none)
+};
+
 struct Workspace {
     void *xbuf;          // second position buffer (double [n_vert][2])
     double *cap;         // per-cell (cA, cP) in the arithmetic type, sized for double
@@ -191,6 +208,9 @@ struct Workspace {
     StepCtl *step;       // device
     double *step_part;   // max |F| of each block of a step, [2][blocks]
     StepCtl *step_host;  // pinned host mirror
+    CgState *cg_state;   // device [2]
+    CgState *cg_host;    // pinned host mirror [2]
+    int32_t *max_sides;  // device int
     void *one;           // device: item and result of a one-workgroup launch (OneSlot)
     hipStream_t cap_stream;
 };

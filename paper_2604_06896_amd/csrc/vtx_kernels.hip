@@ -16,6 +16,7 @@
 // Adjoint (Methods, "Implicit differentiation (ID)"): k_hvp_cell/k_hvp_vertex
 // form H v with the same gathers, k_cg_* run conjugate gradients with FP64
 // dots and device-side scalars, k_contract_* apply the mixed derivatives.
+#include <algorithm>
 #include <climits>
 
 #include "vtx_device.h"
@@ -656,7 +657,7 @@ __global__ __launch_bounds__(kTileV) void k_eval_fused(DevTissue t, const PosT *
 
 // ---------------------------------------------------------------------- T1
 template <typename PosT, typename M>
-__global__ __launch_bounds__(kBlock, 4) void k_t1(DevTissue t, PosT *X, DevParams<PosT> p, M *cap,
+__global__ __launch_bounds__(kBlock, 3) void k_t1(DevTissue t, PosT *X, DevParams<PosT> p, M *cap,
                                                LoopCtl *ctl, int32_t *list_g, double l_min,
                                                double l_new) {
     __shared__ int32_t buf[kT1SortCap];
@@ -732,22 +733,27 @@ constexpr int kQuad0 = 0x00, kQuad1 = 0x55, kQuad2 = 0xAA;
 // positions, and take the step again in the launch after, from the
 // coefficients this launch stored and the pass changed.  Kernel boundaries
 // give the ordering that device-scope arrivals or k_finish gave before.
-// (Four waves per SIMD: the T1 pass, which one wave runs, would take all 512
+// (Three waves per SIMD: the T1 pass, which one wave runs, would take all 512
 // registers and leave the step one wave per SIMD.)
 template <typename PosT, typename M, bool T1>
-__global__ __launch_bounds__(kBlock, 4) void k_relax_step(DevTissue t, PosT *X0, PosT *X1,
+__global__ __launch_bounds__(kBlock, 3) void k_relax_step(DevTissue t, PosT *X0, PosT *X1,
                                                        DevParams<PosT> p, M *cap, StepCtl *ctl,
                                                        int32_t *list, StepArgs a) {
     __shared__ int32_t sort_buf[T1 ? kT1SortCap : 1];
     __shared__ int32_t extra[T1 ? kT1Extra : 1];
     __shared__ int32_t scan[T1 ? kBlock : 1];
     __shared__ double sh[2 * (kBlock / 64)];
-    StepState S = ctl->s[a.k2];
-    if (S.done) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) ctl->s[a.k2 ^ 1] = S;
-        return;
-    }
     const int tid = threadIdx.x, nv = t.n_vert;
+    // the maxima of the launch before, needed last but issued first (loads
+    // return in order)
+    constexpr int PU = 2;
+    const double *part = a.part + (int64_t)a.k2 * gridDim.x;
+    double pre[PU];
+#pragma unroll
+    for (int u = 0; u < PU; ++u) {
+        const int i = tid + u * kBlock;
+        pre[u] = part[i < (int)gridDim.x ? i : 0];
+    }
     const int gid = xcd_block() * kBlock + tid;
     const int v = gid >> 2, k = gid & 3;
     const bool live = v < nv && k < 3;
@@ -766,43 +772,18 @@ __global__ __launch_bounds__(kBlock, 4) void k_relax_step(DevTissue t, PosT *X0,
 #pragma unroll
         for (int j = 0; j < U; ++j) wc[j] = t.corner[rb + (j < n ? j : 0)];
     }
-    // the launch before: its step stands, is dropped for a T1 pass, or ends
-    // the loop
-    const uint32_t ncand = T1 ? ctl->cnt[a.k3] : 0u;
-    bool pass = false;
-    if (S.pending) {
-        double m = 0.0;
-        const double *part = a.part + (int64_t)a.k2 * gridDim.x;
-        for (int i = tid; i < (int)gridDim.x; i += kBlock) m = fmax(m, part[i]);
-        m = wave_max_plain(m);
-        if ((tid & 63) == 0) sh[tid >> 6] = m;
-        __syncthreads();
-        m = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
-        if (T1 && S.det && ncand > 0) {
-            pass = true;
-        } else {
-            S.iter += 1;
-            S.last_maxf = m;
-            if (!(m <= 1.7976931348623157e308)) {
-                S.done = 1;
-                S.status = VTX_E_NONFINITE;
-                S.result_buf = S.cur;
-            } else {
-                S.count = m < a.tol ? S.count + 1 : 0;
-                if (S.count >= a.patience) {
-                    S.done = 1;
-                    S.status = VTX_CONVERGED;
-                    S.result_buf = S.cur;
-                } else if (S.iter >= a.max_iter) {
-                    S.done = 1;
-                    S.status = VTX_NOT_CONVERGED;
-                    S.result_buf = S.cur ^ 1;
-                }
-            }
-            S.cur ^= 1;
-            S.redo = 0;
-        }
+    const StepState &S = ctl->s[a.k2];
+    StepState &N = ctl->s[a.k2 ^ 1];  // written by one thread of block 0
+    const bool writer = blockIdx.x == 0 && tid == 0;
+    if (S.done) {
+        if (writer) N = S;
+        return;
     }
+    // The launch before: its step is dropped for a T1 pass, or stands (then
+    // the loop may end with it, which is known once the maxima are in; what
+    // follows only needs the buffer).
+    const uint32_t ncand = T1 ? ctl->cnt[a.k3] : 0u;
+    const bool pass = T1 && S.pending && S.det && ncand > 0;
     if (pass) {  // T1 pass on the positions the dropped step started from
         if (blockIdx.x != 0) return;
         PosT *X = S.cur ? X1 : X0;
@@ -817,52 +798,43 @@ __global__ __launch_bounds__(kBlock, 4) void k_relax_step(DevTissue t, PosT *X0,
             const T1Counts r = t1_sequential<PosT, M>(t, X, p, cap, arr, (int)ncand, extra,
                                                       a.l_min, a.l_new);
             if (tid == 0) {
-                S.n_t1 += r.swaps;
-                S.n_stretch += r.stretches;
-                if (r.overflow) S.t1_overflow = r.overflow;
-                if (r.overflow == 2) S.done = 1;  // the host reports it
+                N = S;
+                N.n_t1 = S.n_t1 + r.swaps;
+                N.n_stretch = S.n_stretch + r.stretches;
+                if (r.overflow) N.t1_overflow = r.overflow;
+                if (r.overflow == 2) N.done = 1;  // the host reports it
+                N.pending = 0;
+                N.redo = 1;
+                ctl->cnt[(a.k3 + 2) % 3] = 0u;
                 s_relocated = r.relocated;
             }
         }
         __syncthreads();
-        int bad = 0;
-        if (s_relocated) bad = rebuild_rows_block(t, scan);
-        if (tid == 0) {
-            if (bad) {
-                S.t1_overflow = 2;
-                S.done = 1;
-            }
-            S.pending = 0;
-            S.redo = 1;
-            ctl->s[a.k2 ^ 1] = S;
-            ctl->cnt[(a.k3 + 2) % 3] = 0u;
+        if (s_relocated && rebuild_rows_block(t, scan) && tid == 0) {
+            N.t1_overflow = 2;
+            N.done = 1;
         }
         return;
     }
-    const bool det = T1 && !S.redo;
-    if (blockIdx.x == 0 && tid == 0) {
-        StepState N = S;
-        N.pending = 1;
-        N.det = det ? 1 : 0;
-        ctl->s[a.k2 ^ 1] = N;
-        ctl->cnt[(a.k3 + 2) % 3] = 0u;
-    }
-    if (S.done) return;
-    const PosT *X = S.cur ? X1 : X0;
-    PosT *out = S.cur ? X0 : X1;
+    const int was = S.cur, pending = S.pending;
+    const int cur = pending ? was ^ 1 : was;
+    const bool redo = T1 && !pending && S.redo != 0;
+    const bool det = T1 && !redo;
+    const PosT *X = cur ? X1 : X0;
+    PosT *out = cur ? X0 : X1;
     double mf = 0.0;
     M tx = 0, ty = 0;
-    typename Vec2<PosT>::type pi{};
+    typename Vec2<PosT>::type pi{}, qn{};
     typename Vec2<M>::type cc{};
     M dx = 0, dy = 0, ux = 0, uy = 0, lam = 0;
     if (live) {
-        const PosT Lx = (PosT)t.Lx, Ly = (PosT)t.Ly;
         pi = ld2(X, v);
-        const auto qn = ld2(X, id_of(wn));
+        qn = ld2(X, id_of(wn));
         lam = (M)p.lm(e);
+        const PosT Lx = (PosT)t.Lx, Ly = (PosT)t.Ly;
         const PosT ex = pdiff<PosT>(qn.x, pi.x, ox_of(wn), Lx);
         const PosT ey = pdiff<PosT>(qn.y, pi.y, oy_of(wn), Ly);
-        if (S.redo) {
+        if (redo) {
             cc = ld2((const M *)cap, c);
         } else {
             PosT A, P;
@@ -901,6 +873,55 @@ __global__ __launch_bounds__(kBlock, 4) void k_relax_step(DevTissue t, PosT *X0,
     fy += quad<kQuad1>(ty);
     fx += quad<kQuad2>(tx);
     fy += quad<kQuad2>(ty);
+    // whether the loop ended with the step before (what was computed and
+    // listed above is then left behind)
+    int64_t iter = S.iter, count = S.count;
+    int done = 0, status = VTX_NOT_CONVERGED, result_buf = 0;
+    double m = S.last_maxf;
+    if (pending) {
+        m = 0.0;
+#pragma unroll
+        for (int u = 0; u < PU; ++u)
+            if (tid + u * kBlock < (int)gridDim.x) m = fmax(m, pre[u]);
+        for (int i = tid + PU * kBlock; i < (int)gridDim.x; i += kBlock) m = fmax(m, part[i]);
+        m = wave_max_plain(m);
+        if ((tid & 63) == 0) sh[tid >> 6] = m;
+        __syncthreads();
+        m = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
+        iter += 1;
+        if (!(m <= 1.7976931348623157e308)) {
+            done = 1;
+            status = VTX_E_NONFINITE;
+            result_buf = was;
+        } else {
+            count = m < a.tol ? count + 1 : 0;
+            if (count >= a.patience) {
+                done = 1;
+                status = VTX_CONVERGED;
+                result_buf = was;
+            } else if (iter >= a.max_iter) {
+                done = 1;
+                result_buf = was ^ 1;
+            }
+        }
+    }
+    if (writer) {
+        N.iter = iter;
+        N.count = count;
+        N.n_t1 = S.n_t1;
+        N.n_stretch = S.n_stretch;
+        N.last_maxf = m;
+        N.cur = cur;
+        N.pending = 1;
+        N.det = det ? 1 : 0;
+        N.redo = redo ? 1 : 0;
+        N.done = done;
+        N.status = status;
+        N.result_buf = result_buf;
+        N.t1_overflow = S.t1_overflow;
+        ctl->cnt[(a.k3 + 2) % 3] = 0u;
+    }
+    if (done) return;
     if (live && k == 0) {
         const double gx = fx, gy = fy;
         mf = fmax(fabs(gx), fabs(gy));
@@ -1124,6 +1145,306 @@ __global__ __launch_bounds__(kBlock) void k_cg_dir(const double *__restrict__ r,
     const int64_t k = 2 * (int64_t)v;
     q[k] = r[k] + be * q[k];
     q[k + 1] = r[k + 1] + be * q[k + 1];
+}
+
+// ------------------------------------------------------- one-launch CG step
+__global__ __launch_bounds__(kBlock) void k_max_sides(DevTissue t, int32_t *out) {
+    int m = 0;
+    for (int c = blockIdx.x * kBlock + threadIdx.x; c < t.n_cell; c += gridDim.x * kBlock)
+        m = max(m, t.nsides[c]);
+    for (int off = 32; off; off >>= 1) m = max(m, __shfl_xor(m, off, 64));
+    if ((threadIdx.x & 63) == 0) atomicMax(out, m);
+}
+
+__global__ void k_zero_int(int32_t *p) { *p = 0; }
+
+// The 2 x 2 blocks of the Hessian's row of every vertex (FP64).  Lane k < 3 of
+// a vertex's quad takes sector cell k, whose corners from the vertex on are
+// v, nb_k, the far corners, nb_{k+1}: a far corner u couples to v through the
+// cell's area and perimeter only, 2 K_A gA_v gA_u^T + 2 K_P gP_v gP_u^T (gA, gP
+// the gradients of both); nb_k also through cell k - 1 (that lane's term
+// comes by a lane move) and the edge: -T/l (I - u u^T) and the pressure step
+// across it.  Lane 3 takes the block of v itself.
+__global__ __launch_bounds__(kBlock) void k_hess_rows(DevTissue t, const double *__restrict__ X,
+                                                      DevParams<double> p,
+                                                      const double *__restrict__ cap,
+                                                      HessRows H) {
+    const int64_t lanes = (int64_t)gridDim.x * kBlock;
+    const int64_t gid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int v = (int)(gid >> 2), k = (int)(gid & 3), nv = t.n_vert;
+    const bool live = v < nv && k < 3;
+    double4 self{0, 0, 0, 0}, next{0, 0, 0, 0}, prev{0, 0, 0, 0};  // row-major 2 x 2
+    double cA = 0.0, cP = 0.0, ux = 0.0, uy = 0.0, inv = 0.0, lam = 0.0;
+    int nb = 0, n = 0;
+    auto add = [](double4 &m, double s, double ax, double ay, double bx, double by) {
+        m.x += s * ax * bx;
+        m.y += s * ax * by;
+        m.z += s * ay * bx;
+        m.w += s * ay * by;
+    };
+    if (live) {
+        const int c = t.star[star_cell_at(nv, k, v)];
+        const int rb = t.row_ptr[c];
+        n = t.nsides[c];
+        nb = id_of(t.star[star_nb_at(nv, k, v)]);
+        const double2 cc = ld2(cap, c);
+        cA = cc.x;
+        cP = cc.y;
+        lam = p.lm(t.star[star_edge_at(nv, k, v)]);
+        const double ka2 = 2.0 * p.ka(c), kp2 = 2.0 * p.kp(c);
+        // the corner that leaves by the vertex's half-edge in this cell
+        const int he = t.star_he[k * nv + v];
+        int at = 0;
+        while (at < n - 1 && t.corner_he[rb + at] != he) ++at;
+        const double2 q0 = ld2(X, id_of(t.corner[rb]));
+        auto pos = [&](int j) {  // corner at + j, relative to corner 0
+            const int i = at + j < n ? at + j : at + j - n;
+            const int32_t w = t.corner[rb + i];
+            const double2 x = ld2(X, id_of(w));
+            return double2{pdiff<double>(x.x, q0.x, ox_of(w), t.Lx),
+                           pdiff<double>(x.y, q0.y, oy_of(w), t.Ly)};
+        };
+        auto unit = [](double2 a, double2 b, double &l, double &iv) {  // from a to b
+            const double dx = b.x - a.x, dy = b.y - a.y;
+            len_inv(dx * dx + dy * dy, l, iv);
+            return double2{dx * iv, dy * iv};
+        };
+        double l, iv;
+        double2 rp = pos(n - 1), rc = pos(0), rn = pos(1);
+        double2 uin = unit(rp, rc, l, iv), uout = unit(rc, rn, l, inv);
+        ux = uout.x;
+        uy = uout.y;
+        // gradients at the vertex itself
+        const double vax = 0.5 * (rn.y - rp.y), vay = -0.5 * (rn.x - rp.x);
+        const double vpx = uin.x - uout.x, vpy = uin.y - uout.y;
+        add(self, ka2, vax, vay, vax, vay);
+        add(self, kp2, vpx, vpy, vpx, vpy);
+        for (int j = 1; j < n; ++j) {
+            rp = rc;
+            rc = rn;
+            rn = pos(j + 1 < n ? j + 1 : 0);
+            uin = uout;
+            uout = unit(rc, rn, l, iv);
+            const double ax = 0.5 * (rn.y - rp.y), ay = -0.5 * (rn.x - rp.x);
+            const double px = uin.x - uout.x, py = uin.y - uout.y;
+            double4 b{0, 0, 0, 0};
+            add(b, ka2, vax, vay, ax, ay);
+            add(b, kp2, vpx, vpy, px, py);
+            if (j == 1) next = b;
+            else if (j == n - 1) prev = b;
+            else {
+                const int i = at + j < n ? at + j : at + j - n;
+                const int64_t o = (int64_t)(j - 1) * lanes + gid;
+                H.col[o] = id_of(t.corner[rb + i]);
+                H.top[o] = double2{b.x, b.y};
+                H.bottom[o] = double2{b.z, b.w};
+            }
+        }
+    }
+    // nb_k also lies in cell k - 1, as its nb_{(k-1)+1}
+    next.x += dpp_f64<kQuadPrev>(prev.x);
+    next.y += dpp_f64<kQuadPrev>(prev.y);
+    next.z += dpp_f64<kQuadPrev>(prev.z);
+    next.w += dpp_f64<kQuadPrev>(prev.w);
+    const double ti = (lam + cP + dpp_f64<kQuadPrev>(cP)) * inv;
+    const double dC = 0.5 * (cA - dpp_f64<kQuadPrev>(cA));
+    const double exx = ti * (1.0 - ux * ux), exy = -ti * ux * uy, eyy = ti * (1.0 - uy * uy);
+    if (live) {
+        self.x += exx;
+        self.y += exy;
+        self.z += exy;
+        self.w += eyy;
+        const double4 b{next.x - exx, next.y - exy + dC, next.z - exy - dC, next.w - eyy};
+        H.col[gid] = nb;
+        H.top[gid] = double2{b.x, b.y};
+        H.bottom[gid] = double2{b.z, b.w};
+    }
+    auto sum3 = [](double x) {
+        return dpp_f64<kQuad0>(x) + dpp_f64<kQuad1>(x) + dpp_f64<kQuad2>(x);
+    };
+    const double4 d{sum3(self.x), sum3(self.y), sum3(self.z), sum3(self.w)};
+    if (v < nv && k == 3) {
+        H.col[gid] = v;
+        H.top[gid] = double2{d.x, d.y};
+        H.bottom[gid] = double2{d.z, d.w};
+    }
+    // slots not filled above
+    const int filled = live ? n - 2 : k == 3 && v < nv ? 1 : 0;
+    for (int j = filled; j < H.width; ++j) H.col[(int64_t)j * lanes + gid] = -1;
+}
+
+// r = b - mean(b); the other vectors of the first launch and the solution 0
+__global__ __launch_bounds__(kBlock) void k_cg_step_init(const double *__restrict__ b, int nv,
+                                                         const double *mean, double2 *x,
+                                                         double2 *r, double2 *q, double2 *h) {
+    const int v = blockIdx.x * kBlock + threadIdx.x;
+    if (v >= nv) return;
+    r[v] = double2{b[2 * (int64_t)v] - mean[0], b[2 * (int64_t)v + 1] - mean[1]};
+    x[v] = q[v] = h[v] = double2{0.0, 0.0};
+}
+
+// One CG iteration in one launch, for FP64 tissues beyond one workgroup.  The
+// launch before left h = H q and per-block sums of q.h, r.r, r.h and h.h.
+// Every block adds them up for itself (in the same order), takes the
+// stopping tests and the step length alpha = r.r / q.h, and knows the next
+// r.r before forming r: |r - alpha h|^2 = r.r - 2 alpha r.h + alpha^2 h.h,
+// hence beta; alpha itself always uses the r.r of the vector.  Each lane then
+// gathers r, q and h of its columns, forms the new q = (r - alpha h) + beta q
+// there, and multiplies by its blocks; the quad adds up.  Vectors are double
+// buffered, so nothing but the kernel boundary orders the launches (the
+// former step took six launches, two of them one-block reductions).  The
+// blocks (416 B a vertex at six sides) stay in the L2s: 2.1 MB of each 4 MB
+// at 20000 cells.
+struct CgStepArgs {
+    double tol;
+    int64_t max_iter;
+    const double2 *r0, *q0, *h0;
+    double2 *x, *r1, *q1, *h1;
+    double4 *part;   // [2][gridDim.x]
+    int k2;
+};
+
+__global__ __launch_bounds__(kBlock) void k_cg_step(HessRows H, int nv, CgState *state,
+                                                    CgStepArgs a) {
+    __shared__ double sh[4 * (kBlock / 64)];
+    const int tid = threadIdx.x;
+    const int64_t lanes = (int64_t)gridDim.x * kBlock;
+    const int64_t gid = (int64_t)xcd_block() * kBlock + tid;
+    const int v = (int)(gid >> 2);
+    // Loads that wait for nothing, in the order their values are needed (they
+    // return in that order): the sums of the launch before, the rows, then
+    // the vectors at the rows' columns, which arrive while the sums are added
+    constexpr int PU = 3, U = 4;
+    const double4 *part = a.part + (int64_t)a.k2 * gridDim.x;
+    double4 pre[PU];
+#pragma unroll
+    for (int u = 0; u < PU; ++u) {
+        const int i = tid + u * kBlock;
+        pre[u] = part[i < (int)gridDim.x ? i : 0];
+    }
+    int32_t col[U];
+    double2 top[U], bot[U], r[U], q[U], h[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) col[j] = j < H.width ? H.col[(int64_t)j * lanes + gid] : -1;
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+        top[j] = bot[j] = r[j] = q[j] = h[j] = double2{0.0, 0.0};
+        if (col[j] >= 0) {
+            const int64_t o = (int64_t)j * lanes + gid;
+            r[j] = a.r0[col[j]];
+            q[j] = a.q0[col[j]];
+            h[j] = a.h0[col[j]];
+            top[j] = H.top[o];
+            bot[j] = H.bottom[o];
+        }
+    }
+    CgState S = state[a.k2];
+    if (S.done) {
+        if (blockIdx.x == 0 && tid == 0) state[a.k2 ^ 1] = S;
+        return;
+    }
+    double alpha = 0.0, beta = 0.0;
+    if (S.started) {
+        double4 s{0, 0, 0, 0};
+        auto add = [&](double4 x) {
+            s.x += x.x;
+            s.y += x.y;
+            s.z += x.z;
+            s.w += x.w;
+        };
+#pragma unroll
+        for (int u = 0; u < PU; ++u)
+            if (tid + u * kBlock < (int)gridDim.x) add(pre[u]);
+        for (int i = tid + PU * kBlock; i < (int)gridDim.x; i += kBlock) add(part[i]);
+        s.x = wave_sum(s.x);
+        s.y = wave_sum(s.y);
+        s.z = wave_sum(s.z);
+        s.w = wave_sum(s.w);
+        if ((tid & 63) == 0) {
+            double *d = sh + 4 * (tid >> 6);
+            d[0] = s.x;
+            d[1] = s.y;
+            d[2] = s.z;
+            d[3] = s.w;
+        }
+        __syncthreads();
+        auto tot = [&](int i) { return (sh[i] + sh[4 + i]) + (sh[8 + i] + sh[12 + i]); };
+        const double qh = tot(0), rr = tot(1), rh = tot(2), hh = tot(3);
+        __syncthreads();
+        if (S.it == 0) S.rr0 = rr;
+        S.rel_res = S.rr0 > 0.0 ? sqrt(rr / S.rr0) : 0.0;
+        if (sqrt(rr) <= a.tol * sqrt(S.rr0)) {
+            S.done = 1;
+            S.status = VTX_CONVERGED;
+        } else if (S.it >= a.max_iter) {
+            S.done = 1;
+            S.status = VTX_CG_MAXITER;
+        } else if (!(qh > 0.0)) {
+            S.done = 1;
+            S.status = VTX_CG_NEG_CURVATURE;
+        } else {
+            alpha = rr / qh;
+            const double rn = rr - 2.0 * alpha * rh + alpha * alpha * hh;
+            beta = rn > 0.0 ? rn / rr : 0.0;
+            S.it += 1;
+        }
+    }
+    if (blockIdx.x == 0 && tid == 0) {
+        CgState N = S;
+        N.started = 1;
+        state[a.k2 ^ 1] = N;
+    }
+    if (S.done) return;
+    double yx = 0.0, yy = 0.0;
+    double2 rv, qv;
+    auto slot = [&](double2 t, double2 b, double2 r, double2 q, double2 h) {
+        rv = double2{fma(-alpha, h.x, r.x), fma(-alpha, h.y, r.y)};
+        qv = double2{fma(beta, q.x, rv.x), fma(beta, q.y, rv.y)};
+        yx = fma(t.x, qv.x, fma(t.y, qv.y, yx));
+        yy = fma(b.x, qv.x, fma(b.y, qv.y, yy));
+    };
+    slot(top[0], bot[0], r[0], q[0], h[0]);
+    const double2 qo = q[0], ro = rv, qn = qv;  // lane 3: the vertex's own
+#pragma unroll
+    for (int j = 1; j < U; ++j) slot(top[j], bot[j], r[j], q[j], h[j]);
+    for (int j = U; j < H.width; ++j) {
+        const int64_t o = (int64_t)j * lanes + gid;
+        const int32_t c = H.col[o];
+        if (c >= 0) slot(H.top[o], H.bottom[o], a.r0[c], a.q0[c], a.h0[c]);
+    }
+    yx += dpp_f64<kDppXor1>(yx);
+    yy += dpp_f64<kDppXor1>(yy);
+    yx += dpp_f64<kDppXor2>(yx);
+    yy += dpp_f64<kDppXor2>(yy);
+    double4 s{0, 0, 0, 0};
+    if (v < nv && (tid & 3) == 3) {
+        a.r1[v] = ro;
+        a.q1[v] = qn;
+        a.h1[v] = double2{yx, yy};
+        const double2 x = a.x[v];
+        a.x[v] = double2{fma(alpha, qo.x, x.x), fma(alpha, qo.y, x.y)};
+        s.x = fma(qn.x, yx, qn.y * yy);
+        s.y = fma(ro.x, ro.x, ro.y * ro.y);
+        s.z = fma(ro.x, yx, ro.y * yy);
+        s.w = fma(yx, yx, yy * yy);
+    }
+    s.x = wave_sum(s.x);
+    s.y = wave_sum(s.y);
+    s.z = wave_sum(s.z);
+    s.w = wave_sum(s.w);
+    if ((tid & 63) == 0) {
+        double *d = sh + 4 * (tid >> 6);
+        d[0] = s.x;
+        d[1] = s.y;
+        d[2] = s.z;
+        d[3] = s.w;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        auto tot = [&](int i) { return (sh[i] + sh[4 + i]) + (sh[8 + i] + sh[12 + i]); };
+        a.part[(int64_t)(a.k2 ^ 1) * gridDim.x + blockIdx.x] =
+            double4{tot(0), tot(1), tot(2), tot(3)};
+    }
 }
 
 // ------------------------------------------------------------ contractions
@@ -1722,6 +2043,54 @@ void launch_cg_iter(const DevTissue &t, const Workspace &w, int mode, const void
                        (const double *)Aq, nv, w.partials, w.ctl);
     launch_fin(gv, w.partials, w.ctl, FinCgUpdate{}, s);
     hipLaunchKernelGGL(k_cg_dir, dim3(gv), dim3(kBlock), 0, s, (const double *)r, q, nv, w.ctl);
+}
+
+int64_t hess_lanes(int64_t n_vert) { return (int64_t)blocks_for(4 * n_vert) * kBlock; }
+
+void launch_max_sides(const DevTissue &t, const Workspace &w, hipStream_t s) {
+    hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(1), 0, s, w.max_sides);
+    hipLaunchKernelGGL(k_max_sides, dim3(std::min(blocks_for(t.n_cell), (unsigned)kRedBlocks)),
+                       dim3(kBlock), 0, s, t, w.max_sides);
+}
+
+void launch_hess_rows(const DevTissue &t, const Workspace &w, const HessRows &H, const void *X,
+                      const ParamsRaw &p, hipStream_t s) {
+    hipLaunchKernelGGL(k_hess_rows, dim3(blocks_for(4 * (int64_t)t.n_vert)), dim3(kBlock), 0, s, t,
+                       (const double *)X, dev_params<double>(p), (const double *)w.cap, H);
+}
+
+// Vectors of the one-launch step: the solution, then (r, q, h) of even and of
+// odd launches, in the six Krylov vectors and the second position buffer.
+static void cg_step_vecs(const Workspace &w, int nv, double2 *&x, double2 *(&even)[3],
+                         double2 *(&odd)[3]) {
+    double2 *base = (double2 *)w.cg;
+    x = base;
+    for (int i = 0; i < 3; ++i) even[i] = base + (int64_t)(1 + i) * nv;
+    odd[0] = base + (int64_t)4 * nv;
+    odd[1] = base + (int64_t)5 * nv;
+    odd[2] = (double2 *)w.xbuf;
+}
+
+void launch_cg_step_init(const Workspace &w, int nv, const double *b, hipStream_t s) {
+    const unsigned gv = blocks_for(nv);
+    const unsigned gm = gv < (unsigned)kRedBlocks ? gv : (unsigned)kRedBlocks;
+    double2 *x, *even[3], *odd[3];
+    cg_step_vecs(w, nv, x, even, odd);
+    hipLaunchKernelGGL(k_mean2, dim3(gm), dim3(kBlock), 0, s, b, nv, w.partials2, w.ctl + 1,
+                       w.scal);
+    hipLaunchKernelGGL(k_cg_step_init, dim3(gv), dim3(kBlock), 0, s, b, nv,
+                       (const double *)w.scal, x, even[0], even[1], even[2]);
+}
+
+void launch_cg_step(const DevTissue &t, const Workspace &w, const HessRows &H, double tol,
+                    int64_t max_iter, int k, hipStream_t s) {
+    double2 *x, *v[2][3];
+    cg_step_vecs(w, t.n_vert, x, v[0], v[1]);
+    const int k2 = k & 1;
+    const CgStepArgs a{tol,       max_iter,      v[k2][0],      v[k2][1],      v[k2][2], x,
+                       v[k2 ^ 1][0], v[k2 ^ 1][1], v[k2 ^ 1][2], (double4 *)w.step_part, k2};
+    hipLaunchKernelGGL(k_cg_step, dim3(blocks_for(4 * (int64_t)t.n_vert)), dim3(kBlock), 0, s, H,
+                       t.n_vert, w.cg_state, a);
 }
 
 static MinresVecs minres_vecs(const Workspace &w, int nv) {

@@ -71,6 +71,16 @@ void launch_dot_pos(const Workspace &w, int mode, int nv, const double *g, const
 void launch_mean_pos(const Workspace &w, int mode, int nv, const void *a, double *mean_out,
                      hipStream_t s);
 
+// The one-launch CG step (FP64): the largest cell's sides into *w.max_sides;
+// the rows of the Hessian; the start (r = P b, everything else 0); launch k
+// of a captured chunk of even length.
+void launch_max_sides(const DevTissue &t, const Workspace &w, hipStream_t s);
+void launch_hess_rows(const DevTissue &t, const Workspace &w, const HessRows &H, const void *X,
+                      const ParamsRaw &p, hipStream_t s);
+void launch_cg_step_init(const Workspace &w, int nv, const double *b, hipStream_t s);
+void launch_cg_step(const DevTissue &t, const Workspace &w, const HessRows &H, double tol,
+                    int64_t max_iter, int k, hipStream_t s);
+int64_t hess_lanes(int64_t n_vert);
 // Bytes of Workspace::one.
 constexpr size_t kOneBytes = 1024;
 // Relaxation of a tissue that fits one workgroup's LDS (vtx_batch.hip):

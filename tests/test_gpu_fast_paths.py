@@ -194,3 +194,50 @@ def test_t1_pass_around_long_rows(vtx, oracle, petals, mode):
     F = T.energy_forces(X, V.Params(P0=3.6, lam=0.1), mode=mode)[1]
     Fo = oracle.energy_forces(m, Xo, p)[1]
     assert np.abs(F.cpu().numpy() - Fo).max() / np.abs(Fo).max() < (1e-10 if mode == "f64" else 1e-5)
+
+
+@pytest.mark.parametrize("make,theta", [("random", "lambda"), ("random", "P0"), ("hex", "P0"),
+                                        ("fan", "lambda")])
+def test_one_launch_cg_matches_the_oracle(vtx, oracle, make, theta):
+    """CG beyond one workgroup runs on the assembled rows of the Hessian, one
+    launch per iteration: random tilings (3 to 12 sides), hexagons (no row
+    longer than the least width) and a cell of 22 sides (a wider table), the
+    last two after a smaller table was built for the same tissue.  Step counts
+    agree with the oracle's to one (sums are added in another order) and
+    gradients to the residual of 1e-12 times the condition number."""
+    V = vtx
+    rng = np.random.default_rng(12)
+    if make == "random":
+        t = g.random_tissue(1500, seed=31)
+    elif make == "hex":
+        t = g.hex_lattice(34, 34, float(np.sqrt(2.0 / (3.0 * np.sqrt(3.0)))))
+    else:
+        one = _fan(22)
+        seeds = np.concatenate([one.seeds + [14.0 * i, 14.0 * j] for i in range(3) for j in range(3)])
+        t = g.periodic_voronoi(seeds, 42.0, 42.0)
+        assert t.n_cell > 1024 and np.bincount(t.he[:, g.HE_FACE]).max() == 22
+    p = g.uniform_params(t, KA=0.02, P0=0.5, lam=1.0)
+    p.lam = rng.uniform(0.9, 1.1, t.n_edge)
+    b = rng.normal(size=(t.n_vert, 2))
+    T, m = V.Tissue.from_tissue(t), oracle.Mesh.from_tissue(t)
+    P = V.Params(KA=0.02, A0=1.0, KP=1.0, P0=0.5, lam=_dev(p.lam))
+    got, info = T.param_grad(_dev(t.X), P, dC_dX=_dev(b), theta=theta, cg_tol=1e-12)
+    ref, info_o = oracle.adjoint_grad(m, t.X, p, b, theta=theta, tol=1e-12)
+    assert info["status"] == V.CONVERGED and info["cg_rel_res"] <= 1e-12
+    assert abs(info["cg_iters"] - info_o["iters"]) <= 0.02 * info_o["iters"] + 1
+    assert np.abs(got.cpu().numpy() - ref).max() / np.abs(ref).max() < 1e-7
+    # the residual of the solution, through the separate product
+    d = _dev(rng.normal(size=t.n_edge if theta == "lambda" else t.n_cell))
+    _, w, _ = T.param_sens(_dev(t.X), P, d, _dev(b), theta=theta, cg_tol=1e-12, want_dX=True)
+    Hw = oracle.hvp(m, t.X, p, w.cpu().numpy())
+    Hg = T.hvp(_dev(t.X), P, w).cpu().numpy()
+    assert np.abs(Hw - Hg).max() / np.abs(Hw).max() < 1e-11
+    # stopping at the step limit and at a constant (zero-mean zero) right side
+    _, i1 = T.param_grad(_dev(t.X), P, dC_dX=_dev(b), theta=theta, cg_tol=1e-12, cg_max_iter=5)
+    assert (i1["cg_iters"], i1["status"]) == (5, V.CG_MAXITER)
+    g0, i0 = T.param_grad(_dev(t.X), P, dC_dX=_dev(np.ones_like(b)), theta=theta, cg_tol=1e-12)
+    assert (i0["cg_iters"], i0["status"]) == (0, V.CONVERGED) and float(g0.abs().max()) == 0.0
+    # a state that is no minimum stops with the curvature status
+    Pn = V.Params(KA=1.0, A0=1.0, KP=1.0, P0=6.0, lam=-1.0)
+    _, i2 = T.param_grad(_dev(t.X), Pn, dC_dX=_dev(b), theta=theta, cg_tol=1e-12)
+    assert i2["status"] == V.CG_NEG_CURVATURE
