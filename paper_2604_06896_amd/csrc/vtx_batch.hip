@@ -77,27 +77,35 @@ __host__ __device__ inline bool cg_fast_fits(int64_t n_vert, int64_t n_cell, int
 }
 
 // Cells of a tissue handed to the threads of the one-workgroup kernels by
-// side count.  The cells, stably sorted by min(sides, 15), are cut into K
-// runs of ceil(n_cell / K) (one run where there is a thread for every cell);
-// slot k of thread i takes entry i of run k, counted from the front in even
-// runs and from the back in odd ones.  The cells of one slot across a wave
-// then have about the same number of corners (the wave walks them in step),
-// and each thread's K cells about K times the mean, so the waves finish the
-// cell phase together.  `tmp` holds n_cell ints.  cid[k] is the cell of the
-// thread's slot k, -1 if the run has no entry i.
+// (crosses the box, side count).  The cells, stably sorted by that, are cut
+// into K runs of ceil(n_cell / K) (one run where there is a thread for every
+// cell); slot k of thread i takes entry i of run k, counted from the front in
+// even runs and from the back in odd ones.  The cells of one slot across a
+// wave then have about the same number of corners (the wave walks them in
+// step), each thread's K cells about K times the mean, so the waves finish
+// the cell phase together, and most waves hold no cell that needs periodic
+// images.  `tmp` holds n_cell ints.  cid[k] is the cell of the thread's slot
+// k, -1 if the run has no entry i.
 template <int K>
 __device__ __forceinline__ void cells_by_sides(const DevTissue &t, int *tmp, int *s_scan,
                                                int (&cid)[K]) {
-    constexpr int kBuckets = 16;
+    constexpr int kSides = 8;  // 3 .. 9, 10 or more
     const int tid = threadIdx.x, bd = blockDim.x, nc = t.n_cell;
     int b[K];
 #pragma unroll
     for (int i = 0; i < K; ++i) {
         const int c = tid + i * bd;
-        b[i] = c < nc ? min(t.nsides[c], kBuckets - 1) : -1;
+        b[i] = -1;
+        if (c < nc) {
+            const int n = t.nsides[c], rb = t.row_ptr[c];
+            int img = 0;
+            for (int k = 0; k < n; ++k)
+                img |= ((uint32_t)t.corner[rb + k] >> kIdBits) != kZeroImage ? 1 : 0;
+            b[i] = kSides * img + min(n - 3, kSides - 1);
+        }
     }
     int base = 0;
-    for (int bucket = 0; bucket < kBuckets; ++bucket) {
+    for (int bucket = 0; bucket < 2 * kSides; ++bucket) {
         int cnt = 0;
 #pragma unroll
         for (int i = 0; i < K; ++i) cnt += b[i] == bucket ? 1 : 0;
@@ -1056,11 +1064,13 @@ static_assert(kRelaxLdsThreads <= 512, "block_allsum2 holds the sums of eight wa
 // of 4.8, and of 128 nudged FP64 relaxations of 1000 cells 8.0 instead of
 // 9.7; through one launch per pass (Tissue.relax before) the first took
 // 15.4 us.
-template <typename PosT, typename M, bool T1>
+// KV: vertices per thread, 4 or, for tissues of up to a workgroup's threads, 1
+// (which needs a third of the registers and walks no empty slots).
+template <typename PosT, typename M, bool T1, int KV>
 __global__ __launch_bounds__(kRelaxLdsThreads) void k_batch_relax_lds(
     const BatchItem *__restrict__ items, const int32_t *__restrict__ order, BatchOpts o,
     vtx_relax_result *res) {
-    constexpr int K = kRelaxLdsK, KV = 2 * kRelaxLdsK;
+    constexpr int K = KV > 1 ? KV / 2 : 1;
     extern __shared__ __align__(16) unsigned char lds_dyn[];
     __shared__ int32_t sort_buf[T1 ? kT1SortCap : 1];
     __shared__ int32_t extra[T1 ? kT1Extra : 1];
@@ -1093,6 +1103,10 @@ __global__ __launch_bounds__(kRelaxLdsThreads) void k_batch_relax_lds(
         PosT ka[K], a0[K], kp[K], p0[K];
         int32_t sw[KV][3], sc[KV][3];
         PosT sl[KV][3];
+        // whether a cell or vertex of the slot needs images, in any lane of the
+        // wave: most waves take plain differences (the same values), which
+        // saves half of a corner's instructions
+        bool cell_img[K], vert_img[KV];
         // the topology a step reads: rows into LDS, stars and tensions into
         // registers (again after every T1 pass)
         auto load_topology = [&]() {
@@ -1110,11 +1124,18 @@ __global__ __launch_bounds__(kRelaxLdsThreads) void k_batch_relax_lds(
                 lrb[i] = rows_base + block_exclusive_scan(cn[i], s_scan, tot);
                 rows_base += tot;
                 const int nk = min(cn[i], t.n_he - lrb[i]);  // the rows hold n_he corners
-                for (int k = 0; k < nk; ++k) rowl[lrb[i] + k] = t.corner[grb[i] + k];
+                bool img = false;
+                for (int k = 0; k < nk; ++k) {
+                    const int32_t w = t.corner[grb[i] + k];
+                    img |= ((uint32_t)w >> kIdBits) != kZeroImage;
+                    rowl[lrb[i] + k] = w;
+                }
+                cell_img[i] = __builtin_amdgcn_ballot_w64(img) != 0;
             }
 #pragma unroll
             for (int j = 0; j < KV; ++j) {
                 const int v = tid + j * bd;
+                bool img = false;
                 if (v < nv) {
                     const int4 a = reinterpret_cast<const int4 *>(t.star)[v];
                     const int4 b = reinterpret_cast<const int4 *>(t.star + 4 * (int64_t)nv)[v];
@@ -1126,8 +1147,12 @@ __global__ __launch_bounds__(kRelaxLdsThreads) void k_batch_relax_lds(
                     sc[j][1] = b.x;
                     sc[j][2] = b.y;
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) sl[j][k] = p.lam ? p.lam[e[k]] : p.lam_s;
+                    for (int k = 0; k < 3; ++k) {
+                        sl[j][k] = p.lam ? p.lam[e[k]] : p.lam_s;
+                        img |= ((uint32_t)sw[j][k] >> kIdBits) != kZeroImage;
+                    }
                 }
+                vert_img[j] = __builtin_amdgcn_ballot_w64(img) != 0;
             }
         };
         load_topology();
@@ -1198,8 +1223,14 @@ __global__ __launch_bounds__(kRelaxLdsThreads) void k_batch_relax_lds(
                 if (c >= 0) {
                     PosT A, P;
                     auto corner_at = [&](int k) { return rowl[base + (k < cn[i] ? k : 0)]; };
-                    cell_geom_flat<PosT>(t, Xc, cn[i], corner_at, corner_at, grb[i], A, P,
-                                         T1 && o.t1_enable != 0, lmin2p, B.t1_list, &s_cnt[par]);
+                    if (cell_img[i])
+                        cell_geom_flat<PosT, false>(t, Xc, cn[i], corner_at, corner_at, grb[i], A,
+                                                    P, T1 && o.t1_enable != 0, lmin2p, B.t1_list,
+                                                    &s_cnt[par]);
+                    else
+                        cell_geom_flat<PosT, true>(t, Xc, cn[i], corner_at, corner_at, grb[i], A, P,
+                                                   T1 && o.t1_enable != 0, lmin2p, B.t1_list,
+                                                   &s_cnt[par]);
                     st2(capl, c, (M)((PosT)2 * ka[i] * (A - a0[i])),
                         (M)((PosT)2 * kp[i] * (P - p0[i])));
                 }
@@ -1261,7 +1292,8 @@ __global__ __launch_bounds__(kRelaxLdsThreads) void k_batch_relax_lds(
                     }
                     Star<PosT, M> s;
                     PosT xi, yi;
-                    star_math<PosT, M>(t, L, s, xi, yi);
+                    if (vert_img[j]) star_math<PosT, M, false>(t, L, s, xi, yi);
+                    else star_math<PosT, M, true>(t, L, s, xi, yi);
                     M fx, fy;
                     star_force<PosT, M>(s, fx, fy);
                     double gx = fx, gy = fy;
@@ -1467,6 +1499,9 @@ int launched() {
     return e == hipSuccess ? VTX_OK : hip_fail(e);
 }
 
+// Vertices of the batch's largest tissue.
+int64_t largest(vtx_batch b) { return tissue_size(b->ts[b->order[0]]); }
+
 // Launch of the batched adjoint with the dynamic LDS the largest tissue that
 // fits needs (tissues beyond the device's per-workgroup LDS keep their
 // arrays in global memory).  Workgroups of up to 512 threads run the kernel
@@ -1571,8 +1606,7 @@ int launch_batch_cg(vtx_batch b, const GradItem *gi, const int32_t *order, int n
         const int rc = solve_lds_plan(ts.data(), ts.size(), go.minres != 0, &lds);
         if (rc) return rc;
         if (lds > 0)
-            return launch_solve_lds(gi, order, n, tissue_size(b->ts[b->order[0]]), lds, go,
-                                    b->gres_d, s);
+            return launch_solve_lds(gi, order, n, largest(b), lds, go, b->gres_d, s);
     }
     if (block_threads == 0) {
         const int rc = auto_cg_threads<PosT, M>(b, go, &block_threads);
@@ -1629,11 +1663,11 @@ int relax_lds_plan_t(const DevTissue *const *ts, size_t n, int *lds) {
         e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
     hipFuncAttributes fa{};
     if (e == hipSuccess)
-        e = hipFuncGetAttributes(&fa,
-                                 reinterpret_cast<const void *>(&k_batch_relax_lds<PosT, M, T1>));
+        e = hipFuncGetAttributes(
+            &fa, reinterpret_cast<const void *>(&k_batch_relax_lds<PosT, M, T1, 4>));
     if (e != hipSuccess) return hip_fail(e);
     const int64_t budget = (int64_t)lds_max - (int64_t)fa.sharedSizeBytes;
-    int64_t need = 0;
+    int64_t need = 0, nv_max = 0;
     for (size_t i = 0; i < n; ++i) {
         const DevTissue &d = *ts[i];
         const int64_t nb = relax_lds_bytes<PosT, M>(d.n_vert, d.n_cell, d.n_he);
@@ -1641,9 +1675,13 @@ int relax_lds_plan_t(const DevTissue *const *ts, size_t n, int *lds) {
             d.n_vert > 2 * (int64_t)kRelaxLdsK * kRelaxLdsThreads || nb > budget)
             return VTX_OK;
         need = nb > need ? nb : need;
+        nv_max = std::max<int64_t>(nv_max, d.n_vert);
     }
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_batch_relax_lds<PosT, M, T1>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)need);
+    e = hipFuncSetAttribute(
+        nv_max <= kRelaxLdsThreads
+            ? reinterpret_cast<const void *>(&k_batch_relax_lds<PosT, M, T1, 1>)
+            : reinterpret_cast<const void *>(&k_batch_relax_lds<PosT, M, T1, 4>),
+        hipFuncAttributeMaxDynamicSharedMemorySize, (int)need);
     if (e != hipSuccess) return hip_fail(e);
     *lds = (int)need;
     return VTX_OK;
@@ -1674,24 +1712,29 @@ int relax_lds_threads(int64_t n_vert, bool nudged) {
     return nudged ? kRelaxLdsThreads
                   : (int)std::min<int64_t>(kRelaxLdsThreads, (n_vert + 63) / 64 * 64);
 }
-int relax_lds_threads(vtx_batch b, bool nudged) {
-    return relax_lds_threads(tissue_size(b->ts[b->order[0]]), nudged);
-}
 
 void launch_relax_lds(int mode, bool t1, const BatchItem *it, const int32_t *order, int n,
-                      int threads, int lds, const BatchOpts &bo, vtx_relax_result *res,
-                      hipStream_t s) {
-    auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(n), dim3(threads), (size_t)lds, s, it, order, bo, res);
+                      int64_t nv_max, bool nudged, int lds, const BatchOpts &bo,
+                      vtx_relax_result *res, hipStream_t s) {
+    auto go = [&](auto small, auto large) {
+        hipLaunchKernelGGL(nv_max <= kRelaxLdsThreads ? small : large, dim3(n),
+                           dim3(relax_lds_threads(nv_max, nudged)), (size_t)lds, s, it, order, bo,
+                           res);
     };
     if (mode == VTX_F32)
-        t1 ? go(k_batch_relax_lds<float, float, true>) : go(k_batch_relax_lds<float, float, false>);
+        t1 ? go(k_batch_relax_lds<float, float, true, 1>, k_batch_relax_lds<float, float, true, 4>)
+           : go(k_batch_relax_lds<float, float, false, 1>,
+                k_batch_relax_lds<float, float, false, 4>);
     else if (mode == VTX_F64)
-        t1 ? go(k_batch_relax_lds<double, double, true>)
-           : go(k_batch_relax_lds<double, double, false>);
+        t1 ? go(k_batch_relax_lds<double, double, true, 1>,
+                k_batch_relax_lds<double, double, true, 4>)
+           : go(k_batch_relax_lds<double, double, false, 1>,
+                k_batch_relax_lds<double, double, false, 4>);
     else
-        t1 ? go(k_batch_relax_lds<double, float, true>)
-           : go(k_batch_relax_lds<double, float, false>);
+        t1 ? go(k_batch_relax_lds<double, float, true, 1>,
+                k_batch_relax_lds<double, float, true, 4>)
+           : go(k_batch_relax_lds<double, float, false, 1>,
+                k_batch_relax_lds<double, float, false, 4>);
 }
 
 void launch_batch_relax(int mode, const BatchItem *it, const int32_t *order, int n, int threads,
@@ -1814,8 +1857,8 @@ int batch_relax_run(vtx_batch b, int mode, void *const *X, const vtx_params *p,
     int rc = VTX_OK;
     if (split_K == 0) {
         if (lds > 0)
-            launch_relax_lds(mode, t1, it, b->order_d, n, relax_lds_threads(b, beta != 0.0), lds,
-                             bo, b->res_d, s);
+            launch_relax_lds(mode, t1, it, b->order_d, n, largest(b), beta != 0.0, lds, bo,
+                             b->res_d, s);
         else
             launch_batch_relax(mode, it, b->order_d, n, block_threads, bo, b->res_d, s);
         rc = launched();
@@ -1877,8 +1920,7 @@ int batch_relax_pm(vtx_batch b, int mode, void *const *Xp, void *const *Xm, cons
     if (e != hipSuccess) return hip_fail(e);
     const BatchOpts bo{o->eta, o->tol, o->l_min, o->l_new, o->patience, o->max_iter, 0};
     const BatchItem *it = (const BatchItem *)b->items;
-    launch_relax_lds(mode, false, it, b->order_d, 2 * n, relax_lds_threads(b, true), lds, bo,
-                     b->res_d, s);
+    launch_relax_lds(mode, false, it, b->order_d, 2 * n, largest(b), true, lds, bo, b->res_d, s);
     if ((rc = launched())) return rc;
     std::vector<vtx_relax_result> r(2 * (size_t)n);
     e = hipMemcpyAsync(r.data(), b->res_d, sizeof(vtx_relax_result) * 2 * n,
@@ -1931,8 +1973,8 @@ int relax_one(const DevTissue &t, const Workspace &w, int mode, void *X, const P
                          ra.nudge ? ra.beta : 0.0};
     hipLaunchKernelGGL(k_put_item<BatchItem>, dim3(1), dim3(64), 0, s, item, &slot->item);
     const BatchOpts bo{ra.eta, tol, ra.l_min, ra.l_new, patience, max_iter, ra.t1_enable};
-    launch_relax_lds(mode, t1, &slot->item, nullptr, 1,
-                     relax_lds_threads(t.n_vert, ra.nudge != 0), lds, bo, &slot->res, s);
+    launch_relax_lds(mode, t1, &slot->item, nullptr, 1, t.n_vert, ra.nudge != 0, lds, bo,
+                     &slot->res, s);
     *res_d = &slot->res;
     return launched();
 }
