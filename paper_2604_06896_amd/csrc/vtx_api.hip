@@ -99,7 +99,7 @@ constexpr int kStepChunk = 252;
 // the same vectors).
 constexpr int64_t kCgStepMaxVerts = 65536;
 constexpr int kCgChunk = 256;
-static_assert(kCgStepMaxVerts <= kStepMaxVerts, "per-block results");
+static_assert(kCgStepMaxVerts <= (int64_t)kCgBlocks * kCgVerts, "vertices of a workgroup");
 
 // Host copy of the staged layouts.
 struct Staged {
@@ -251,6 +251,7 @@ void free_tissue(vtx_tissue t) {
                     t->w.t1_list,
                     t->w.ctl, t->w.cg, t->w.scal, t->w.one, t->w.step, t->w.step_part,
                     t->w.cg_state, t->w.max_sides, t->hess.col, t->hess.top, t->hess.bottom,
+                    t->hess.halo, t->hess.n_halo,
                     t->ep_buf,
                     t->tiles.cells, t->tiles.info, t->tiles.halo, t->tiles.cstart,
                     t->tiles.corners, t->tiles.fstar, t->tiles.fe};
@@ -797,14 +798,17 @@ static int cg_steps(vtx_tissue t, const void *X, const vtx_params *p, const doub
     HessRows &H = t->hess;
     if (sides - 2 > H.width) {
         const int width = std::max(sides - 2, 6);  // six: cells of up to eight sides
-        const size_t n = (size_t)width * (size_t)hess_lanes(t->n_vert);
-        void *old[] = {H.col, H.top, H.bottom};
+        void *old[] = {H.col, H.top, H.bottom, H.halo, H.n_halo};
         H = HessRows{};
+        hess_plan(t->n_vert, H);
+        const size_t n = 4 * (size_t)width * (size_t)H.verts * (size_t)H.blocks;
         for (void *q : old)
             if (q) HIPCHK(hipFree(q));
         HIPCHK(hipMalloc((void **)&H.col, 4 * n));
         HIPCHK(hipMalloc((void **)&H.top, 16 * n));
         HIPCHK(hipMalloc((void **)&H.bottom, 16 * n));
+        HIPCHK(hipMalloc((void **)&H.halo, 4 * (size_t)kCgHalo * (size_t)H.blocks));
+        HIPCHK(hipMalloc((void **)&H.n_halo, 4 * (size_t)H.blocks));
         H.width = width;
     }
     HessRows use = H;

@@ -178,19 +178,30 @@ struct StepCtl {
 
 // Scalars of the one-launch CG step (k_cg_step) between launches.
 struct CgState {
-    double rr0, rel_res, alpha;
+    double rr0, rel_res;
+    double stop;         // tol * sqrt(rr0)
     int64_t it;
     int32_t started;     // a launch has formed H q
     int32_t done, status, pad;
 };
 
 // Rows of the Hessian at fixed positions for k_cg_step: quad of lanes 4 v to
-// 4 v + 3 of vertex v, slot j of a lane at [j * lanes + lane] (`lanes` a
-// multiple of the block size): column and 2 x 2 block.
+// 4 v + 3 of vertex v, slot j of a lane at [j * lanes + lane]: column and
+// 2 x 2 block.  A workgroup takes `verts` vertices in id order; a column is
+// its index among the workgroup's vertices, then the `halo` columns it reads
+// of others (up to kCgHalo), or ~id where those are more.
+constexpr int kCgBlocks = 256;       // workgroups at most: one per CU
+constexpr int kCgVerts = 256;        // vertices of a workgroup at most
+constexpr int kCgHalo = 1024;
+constexpr int32_t kNoCol = INT32_MIN;
 struct HessRows {
     int32_t *col;
     double2 *top, *bottom;
+    int32_t *halo;       // [workgroups][kCgHalo]
+    int32_t *n_halo;     // [workgroups]
     int32_t width;       // slots allocated per lane (0: none)
+    int32_t verts;       // vertices per workgroup
+    int32_t blocks;
 };
 
 struct Workspace {

@@ -1169,7 +1169,7 @@ __global__ __launch_bounds__(kBlock) void k_hess_rows(DevTissue t, const double 
                                                       DevParams<double> p,
                                                       const double *__restrict__ cap,
                                                       HessRows H) {
-    const int64_t lanes = (int64_t)gridDim.x * kBlock;
+    const int64_t lanes = 4 * (int64_t)H.verts * H.blocks;
     const int64_t gid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int v = (int)(gid >> 2), k = (int)(gid & 3), nv = t.n_vert;
     const bool live = v < nv && k < 3;
@@ -1270,7 +1270,60 @@ __global__ __launch_bounds__(kBlock) void k_hess_rows(DevTissue t, const double 
     }
     // slots not filled above
     const int filled = live ? n - 2 : k == 3 && v < nv ? 1 : 0;
-    for (int j = filled; j < H.width; ++j) H.col[(int64_t)j * lanes + gid] = -1;
+    if (gid < lanes)
+        for (int j = filled; j < H.width; ++j) H.col[(int64_t)j * lanes + gid] = kNoCol;
+}
+
+// The distinct columns outside each workgroup's own vertices, and the columns
+// as indices into (own vertices, those).  A hash table in LDS numbers them in
+// the order of insertion, which moves no result: the index only says where a
+// value is kept.  A table that is full leaves the rest as ~id.
+constexpr int kCgHash = 4096;
+__global__ __launch_bounds__(4 * kCgVerts) void k_hess_halo(HessRows H) {
+    __shared__ int32_t key[kCgHash], val[kCgHash];
+    __shared__ int32_t s_n;
+    const int nt = blockDim.x, v0 = blockIdx.x * H.verts;
+    const int64_t lanes = 4 * (int64_t)H.verts * H.blocks;
+    const int64_t gid = (int64_t)blockIdx.x * nt + threadIdx.x;
+    int32_t *halo = H.halo + (int64_t)blockIdx.x * kCgHalo;
+    for (int i = threadIdx.x; i < kCgHash; i += nt) key[i] = val[i] = -1;
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    auto slot = [](int c) { return (int)(((uint32_t)c * 2654435761u) >> 20); };
+    static_assert(kCgHash == 1 << 12, "slot() takes the upper 12 bits");
+    for (int j = 0; j < H.width; ++j) {
+        const int c = H.col[(int64_t)j * lanes + gid];
+        if (c < 0 || (c >= v0 && c < v0 + H.verts)) continue;
+        for (int i = 0, h = slot(c); i < kCgHash; ++i, h = (h + 1) & (kCgHash - 1)) {
+            const int was = atomicCAS(&key[h], -1, c);
+            if (was == c) break;
+            if (was != -1) continue;
+            const int n = atomicAdd(&s_n, 1);
+            if (n < kCgHalo) {
+                halo[n] = c;
+                val[h] = H.verts + n;
+            }
+            break;
+        }
+    }
+    __syncthreads();
+    for (int j = 0; j < H.width; ++j) {
+        int32_t &c = H.col[(int64_t)j * lanes + gid];
+        if (c < 0) continue;
+        int32_t at = ~c;
+        if (c >= v0 && c < v0 + H.verts) at = c - v0;
+        else
+            for (int i = 0, h = slot(c); i < kCgHash && key[h] != -1;
+                 ++i, h = (h + 1) & (kCgHash - 1))
+                if (key[h] == c) {
+                    if (val[h] >= 0) at = val[h];
+                    break;
+                }
+        c = at;
+    }
+    const int n = min(s_n, kCgHalo);
+    if (threadIdx.x == 0) H.n_halo[blockIdx.x] = n;
+    for (int i = n + (int)threadIdx.x; i < kCgHalo; i += nt) halo[i] = -1;
 }
 
 // r = b - mean(b); the other vectors of the first launch and the solution 0
@@ -1283,61 +1336,84 @@ __global__ __launch_bounds__(kBlock) void k_cg_step_init(const double *__restric
     x[v] = q[v] = h[v] = double2{0.0, 0.0};
 }
 
+// Sum over the wave's quads of one double per lane: lane l ends with the sum
+// of the lanes l mod 4.  All 64 lanes must be active.
+constexpr int kDppRor4 = 0x124, kDppRor8 = 0x128;  // rotations of a row of 16
+__device__ __forceinline__ double quads_sum(double v) {
+    v += dpp_f64<kDppRor4>(v);
+    v += dpp_f64<kDppRor8>(v);
+    v += __shfl_xor(v, 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    return v;
+}
+
 // One CG iteration in one launch, for FP64 tissues beyond one workgroup.  The
 // launch before left h = H q and per-block sums of q.h, r.r, r.h and h.h.
 // Every block adds them up for itself (in the same order), takes the
 // stopping tests and the step length alpha = r.r / q.h, and knows the next
 // r.r before forming r: |r - alpha h|^2 = r.r - 2 alpha r.h + alpha^2 h.h,
-// hence beta; alpha itself always uses the r.r of the vector.  Each lane then
-// gathers r, q and h of its columns, forms the new q = (r - alpha h) + beta q
-// there, and multiplies by its blocks; the quad adds up.  Vectors are double
-// buffered, so nothing but the kernel boundary orders the launches (the
-// former step took six launches, two of them one-block reductions).  The
-// blocks (416 B a vertex at six sides) stay in the L2s: 2.1 MB of each 4 MB
-// at 20000 cells.
+// hence beta; alpha itself always uses the r.r of the vector.  The new
+// q = (r - alpha h) + beta q goes to LDS for the block's vertices and for the
+// columns it reads of others, once each; each lane multiplies by its blocks
+// and the quad adds up.  (A vertex is a column of 13 rows: gathering r, q and
+// h in every row, in blocks of 64 vertices that each added 625 partial sums,
+// took 8.75 us a step at 20000 cells; now 6.5, 5.1 at 5000.)  Vectors are
+// double buffered, so nothing but the kernel boundary orders the launches.
+// Up to 256 blocks, one per CU: the sums of the launch before are then one
+// load for a quarter of the threads at most.  The rows (416 B a vertex at
+// six sides) stay in the L2s: 2.1 MB of each 4 MB at 20000 cells.
 struct CgStepArgs {
     double tol;
     int64_t max_iter;
     const double2 *r0, *q0, *h0;
     double2 *x, *r1, *q1, *h1;
-    double4 *part;   // [2][gridDim.x]
+    double *part;    // [2][gridDim.x][4]
     int k2;
 };
 
-__global__ __launch_bounds__(kBlock) void k_cg_step(HessRows H, int nv, CgState *state,
-                                                    CgStepArgs a) {
-    __shared__ double sh[4 * (kBlock / 64)];
-    const int tid = threadIdx.x;
-    const int64_t lanes = (int64_t)gridDim.x * kBlock;
-    const int64_t gid = (int64_t)xcd_block() * kBlock + tid;
-    const int v = (int)(gid >> 2);
-    // Loads that wait for nothing, in the order their values are needed (they
-    // return in that order): the sums of the launch before, the rows, then
-    // the vectors at the rows' columns, which arrive while the sums are added
-    constexpr int PU = 3, U = 4;
-    const double4 *part = a.part + (int64_t)a.k2 * gridDim.x;
-    double4 pre[PU];
-#pragma unroll
-    for (int u = 0; u < PU; ++u) {
-        const int i = tid + u * kBlock;
-        pre[u] = part[i < (int)gridDim.x ? i : 0];
-    }
+__global__ __launch_bounds__(4 * kCgVerts) void k_cg_step(HessRows H, int nv, CgState *state,
+                                                          CgStepArgs a) {
+    __shared__ double2 sq[kCgVerts + kCgHalo], sr[kCgVerts];
+    __shared__ double sh[4 * 4 * kCgVerts / 64];
+    static_assert(kCgBlocks <= 256, "one partial sum for each of the first four waves' lanes");
+    const int tid = threadIdx.x, nt = blockDim.x, nb = gridDim.x, blk = xcd_block();
+    const int64_t lanes = (int64_t)nb * nt;
+    const int64_t gid = (int64_t)blk * nt + tid;
+    const int v0 = blk * H.verts;
+    // Loads that wait for nothing, in the order their values are needed: the
+    // sums of the launch before, the vectors, the rows
+    double4 pre{0, 0, 0, 0};
+    if (tid < nb) pre = reinterpret_cast<const double4 *>(a.part)[(int64_t)a.k2 * nb + tid];
+    const int32_t *halo = H.halo + (int64_t)blk * kCgHalo - H.verts;
+    auto source = [&](int i) {  // vertex of entry i of the block, -1 beyond the last vertex
+        const int v = i < H.verts ? v0 + i : halo[i];
+        return v < nv ? v : -1;
+    };
+    // (the list goes on with -1, so the first entry waits for no length)
+    const int mine = source(tid);
+    const bool own = tid < H.verts && mine >= 0;
+    constexpr int U = 6;
     int32_t col[U];
-    double2 top[U], bot[U], r[U], q[U], h[U];
 #pragma unroll
-    for (int j = 0; j < U; ++j) col[j] = j < H.width ? H.col[(int64_t)j * lanes + gid] : -1;
+    for (int j = 0; j < U; ++j) col[j] = j < H.width ? H.col[(int64_t)j * lanes + gid] : kNoCol;
+    double2 r{0, 0}, q{0, 0}, h{0, 0}, x{0, 0};
+    if (mine >= 0) {
+        r = a.r0[mine];
+        q = a.q0[mine];
+        h = a.h0[mine];
+    }
+    if (own) x = a.x[mine];
+    double2 top[U], bot[U];
 #pragma unroll
     for (int j = 0; j < U; ++j) {
-        top[j] = bot[j] = r[j] = q[j] = h[j] = double2{0.0, 0.0};
-        if (col[j] >= 0) {
+        top[j] = bot[j] = double2{0.0, 0.0};
+        if (col[j] != kNoCol) {
             const int64_t o = (int64_t)j * lanes + gid;
-            r[j] = a.r0[col[j]];
-            q[j] = a.q0[col[j]];
-            h[j] = a.h0[col[j]];
             top[j] = H.top[o];
             bot[j] = H.bottom[o];
         }
     }
+    const int n_halo = H.n_halo[blk];
     CgState S = state[a.k2];
     if (S.done) {
         if (blockIdx.x == 0 && tid == 0) state[a.k2 ^ 1] = S;
@@ -1345,35 +1421,21 @@ __global__ __launch_bounds__(kBlock) void k_cg_step(HessRows H, int nv, CgState 
     }
     double alpha = 0.0, beta = 0.0;
     if (S.started) {
-        double4 s{0, 0, 0, 0};
-        auto add = [&](double4 x) {
-            s.x += x.x;
-            s.y += x.y;
-            s.z += x.z;
-            s.w += x.w;
-        };
-#pragma unroll
-        for (int u = 0; u < PU; ++u)
-            if (tid + u * kBlock < (int)gridDim.x) add(pre[u]);
-        for (int i = tid + PU * kBlock; i < (int)gridDim.x; i += kBlock) add(part[i]);
-        s.x = wave_sum(s.x);
-        s.y = wave_sum(s.y);
-        s.z = wave_sum(s.z);
-        s.w = wave_sum(s.w);
-        if ((tid & 63) == 0) {
-            double *d = sh + 4 * (tid >> 6);
-            d[0] = s.x;
-            d[1] = s.y;
-            d[2] = s.z;
-            d[3] = s.w;
+        if (tid < 256) {  // lanes 4 i + c of the wave: component c
+            const bool b0 = tid & 1, b1 = tid & 2;
+            const double u = (b0 ? pre.y : pre.x) + dpp_f64<kDppXor1>(b0 ? pre.x : pre.y);
+            const double w = (b0 ? pre.w : pre.z) + dpp_f64<kDppXor1>(b0 ? pre.z : pre.w);
+            const double s = quads_sum((b1 ? w : u) + dpp_f64<kDppXor2>(b1 ? u : w));
+            if ((tid & 63) < 4) sh[4 * (tid >> 6) + (tid & 3)] = s;
         }
         __syncthreads();
         auto tot = [&](int i) { return (sh[i] + sh[4 + i]) + (sh[8 + i] + sh[12 + i]); };
         const double qh = tot(0), rr = tot(1), rh = tot(2), hh = tot(3);
-        __syncthreads();
-        if (S.it == 0) S.rr0 = rr;
-        S.rel_res = S.rr0 > 0.0 ? sqrt(rr / S.rr0) : 0.0;
-        if (sqrt(rr) <= a.tol * sqrt(S.rr0)) {
+        if (S.it == 0) {
+            S.rr0 = rr;
+            S.stop = a.tol * sqrt(rr);
+        }
+        if (sqrt(rr) <= S.stop) {
             S.done = 1;
             S.status = VTX_CONVERGED;
         } else if (S.it >= a.max_iter) {
@@ -1388,6 +1450,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_step(HessRows H, int nv, CgState 
             beta = rn > 0.0 ? rn / rr : 0.0;
             S.it += 1;
         }
+        if (blockIdx.x == 0 && tid == 0) S.rel_res = S.rr0 > 0.0 ? sqrt(rr / S.rr0) : 0.0;
     }
     if (blockIdx.x == 0 && tid == 0) {
         CgState N = S;
@@ -1395,55 +1458,61 @@ __global__ __launch_bounds__(kBlock) void k_cg_step(HessRows H, int nv, CgState 
         state[a.k2 ^ 1] = N;
     }
     if (S.done) return;
-    double yx = 0.0, yy = 0.0;
-    double2 rv, qv;
-    auto slot = [&](double2 t, double2 b, double2 r, double2 q, double2 h) {
-        rv = double2{fma(-alpha, h.x, r.x), fma(-alpha, h.y, r.y)};
-        qv = double2{fma(beta, q.x, rv.x), fma(beta, q.y, rv.y)};
-        yx = fma(t.x, qv.x, fma(t.y, qv.y, yx));
-        yy = fma(b.x, qv.x, fma(b.y, qv.y, yy));
+    auto new_r = [&](double2 r, double2 h) {
+        return double2{fma(-alpha, h.x, r.x), fma(-alpha, h.y, r.y)};
     };
-    slot(top[0], bot[0], r[0], q[0], h[0]);
-    const double2 qo = q[0], ro = rv, qn = qv;  // lane 3: the vertex's own
+    auto new_q = [&](double2 rn, double2 q) {
+        return double2{fma(beta, q.x, rn.x), fma(beta, q.y, rn.y)};
+    };
+    {
+        const double2 rn = new_r(r, h), qn = new_q(rn, q);
+        sq[tid] = qn;
+        if (tid < H.verts) sr[tid] = rn;
+        if (own) {
+            a.r1[mine] = rn;
+            a.q1[mine] = qn;
+            a.x[mine] = double2{fma(alpha, q.x, x.x), fma(alpha, q.y, x.y)};
+        }
+    }
+    for (int i = tid + nt, n = H.verts + n_halo; i < n; i += nt) {
+        const int v = source(i);
+        sq[i] = new_q(new_r(a.r0[v], a.h0[v]), a.q0[v]);
+    }
+    __syncthreads();
+    double yx = 0.0, yy = 0.0;
+    auto slot = [&](int32_t c, double2 t, double2 b) {
+        const double2 p = c >= 0 ? sq[c] : new_q(new_r(a.r0[~c], a.h0[~c]), a.q0[~c]);
+        yx = fma(t.x, p.x, fma(t.y, p.y, yx));
+        yy = fma(b.x, p.x, fma(b.y, p.y, yy));
+    };
 #pragma unroll
-    for (int j = 1; j < U; ++j) slot(top[j], bot[j], r[j], q[j], h[j]);
+    for (int j = 0; j < U; ++j)
+        if (col[j] != kNoCol) slot(col[j], top[j], bot[j]);
     for (int j = U; j < H.width; ++j) {
         const int64_t o = (int64_t)j * lanes + gid;
         const int32_t c = H.col[o];
-        if (c >= 0) slot(H.top[o], H.bottom[o], a.r0[c], a.q0[c], a.h0[c]);
+        if (c != kNoCol) slot(c, H.top[o], H.bottom[o]);
     }
     yx += dpp_f64<kDppXor1>(yx);
     yy += dpp_f64<kDppXor1>(yy);
     yx += dpp_f64<kDppXor2>(yx);
     yy += dpp_f64<kDppXor2>(yy);
-    double4 s{0, 0, 0, 0};
-    if (v < nv && (tid & 3) == 3) {
-        a.r1[v] = ro;
-        a.q1[v] = qn;
-        a.h1[v] = double2{yx, yy};
-        const double2 x = a.x[v];
-        a.x[v] = double2{fma(alpha, qo.x, x.x), fma(alpha, qo.y, x.y)};
-        s.x = fma(qn.x, yx, qn.y * yy);
-        s.y = fma(ro.x, ro.x, ro.y * ro.y);
-        s.z = fma(ro.x, yx, ro.y * yy);
-        s.w = fma(yx, yx, yy * yy);
-    }
-    s.x = wave_sum(s.x);
-    s.y = wave_sum(s.y);
-    s.z = wave_sum(s.z);
-    s.w = wave_sum(s.w);
-    if ((tid & 63) == 0) {
-        double *d = sh + 4 * (tid >> 6);
-        d[0] = s.x;
-        d[1] = s.y;
-        d[2] = s.z;
-        d[3] = s.w;
-    }
+    // every lane of the quad has the product: lane c takes sum c
+    const double2 qn = sq[tid >> 2], rn = sr[tid >> 2];
+    const int c = tid & 3;
+    const double2 f = c == 0 ? qn : c == 3 ? double2{yx, yy} : rn;
+    const double2 g = c == 1 ? rn : double2{yx, yy};
+    if (c == 3 && (gid >> 2) < nv) a.h1[gid >> 2] = double2{yx, yy};
+    const double s = quads_sum(fma(f.x, g.x, f.y * g.y));
+    if ((tid & 63) < 4) sh[4 * (tid >> 6) + c] = s;
     __syncthreads();
-    if (tid == 0) {
-        auto tot = [&](int i) { return (sh[i] + sh[4 + i]) + (sh[8 + i] + sh[12 + i]); };
-        a.part[(int64_t)(a.k2 ^ 1) * gridDim.x + blockIdx.x] =
-            double4{tot(0), tot(1), tot(2), tot(3)};
+    if (tid < 4) {
+        double d[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int w = 0; w < nt / 64; w += 4)
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (w + u < nt / 64) d[u] += sh[4 * (w + u) + tid];
+        a.part[4 * ((int64_t)(a.k2 ^ 1) * nb + blk) + tid] = (d[0] + d[1]) + (d[2] + d[3]);
     }
 }
 
@@ -2045,7 +2114,12 @@ void launch_cg_iter(const DevTissue &t, const Workspace &w, int mode, const void
     hipLaunchKernelGGL(k_cg_dir, dim3(gv), dim3(kBlock), 0, s, (const double *)r, q, nv, w.ctl);
 }
 
-int64_t hess_lanes(int64_t n_vert) { return (int64_t)blocks_for(4 * n_vert) * kBlock; }
+void hess_plan(int64_t n_vert, HessRows &H) {
+    // one workgroup per CU of at least four waves, in whole waves
+    const int64_t v = (n_vert + kCgBlocks - 1) / kCgBlocks;
+    H.verts = (int32_t)std::max<int64_t>(64, (v + 15) / 16 * 16);
+    H.blocks = (int32_t)((n_vert + H.verts - 1) / H.verts);
+}
 
 void launch_max_sides(const DevTissue &t, const Workspace &w, hipStream_t s) {
     hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(1), 0, s, w.max_sides);
@@ -2055,8 +2129,10 @@ void launch_max_sides(const DevTissue &t, const Workspace &w, hipStream_t s) {
 
 void launch_hess_rows(const DevTissue &t, const Workspace &w, const HessRows &H, const void *X,
                       const ParamsRaw &p, hipStream_t s) {
-    hipLaunchKernelGGL(k_hess_rows, dim3(blocks_for(4 * (int64_t)t.n_vert)), dim3(kBlock), 0, s, t,
-                       (const double *)X, dev_params<double>(p), (const double *)w.cap, H);
+    hipLaunchKernelGGL(k_hess_rows, dim3(blocks_for(4 * (int64_t)H.verts * H.blocks)),
+                       dim3(kBlock), 0, s, t, (const double *)X, dev_params<double>(p),
+                       (const double *)w.cap, H);
+    hipLaunchKernelGGL(k_hess_halo, dim3(H.blocks), dim3(4 * H.verts), 0, s, H);
 }
 
 // Vectors of the one-launch step: the solution, then (r, q, h) of even and of
@@ -2088,9 +2164,9 @@ void launch_cg_step(const DevTissue &t, const Workspace &w, const HessRows &H, d
     cg_step_vecs(w, t.n_vert, x, v[0], v[1]);
     const int k2 = k & 1;
     const CgStepArgs a{tol,       max_iter,      v[k2][0],      v[k2][1],      v[k2][2], x,
-                       v[k2 ^ 1][0], v[k2 ^ 1][1], v[k2 ^ 1][2], (double4 *)w.step_part, k2};
-    hipLaunchKernelGGL(k_cg_step, dim3(blocks_for(4 * (int64_t)t.n_vert)), dim3(kBlock), 0, s, H,
-                       t.n_vert, w.cg_state, a);
+                       v[k2 ^ 1][0], v[k2 ^ 1][1], v[k2 ^ 1][2], w.step_part, k2};
+    hipLaunchKernelGGL(k_cg_step, dim3(H.blocks), dim3(4 * H.verts), 0, s, H, t.n_vert, w.cg_state,
+                       a);
 }
 
 static MinresVecs minres_vecs(const Workspace &w, int nv) {

@@ -80,7 +80,8 @@ void launch_hess_rows(const DevTissue &t, const Workspace &w, const HessRows &H,
 void launch_cg_step_init(const Workspace &w, int nv, const double *b, hipStream_t s);
 void launch_cg_step(const DevTissue &t, const Workspace &w, const HessRows &H, double tol,
                     int64_t max_iter, int k, hipStream_t s);
-int64_t hess_lanes(int64_t n_vert);
+// Workgroups of the rows, and the vertices of each.
+void hess_plan(int64_t n_vert, HessRows &H);
 // Bytes of Workspace::one.
 constexpr size_t kOneBytes = 1024;
 // Relaxation of a tissue that fits one workgroup's LDS (vtx_batch.hip):

@@ -241,3 +241,31 @@ def test_one_launch_cg_matches_the_oracle(vtx, oracle, make, theta):
     Pn = V.Params(KA=1.0, A0=1.0, KP=1.0, P0=6.0, lam=-1.0)
     _, i2 = T.param_grad(_dev(t.X), Pn, dC_dX=_dev(b), theta=theta, cg_tol=1e-12)
     assert i2["status"] == V.CG_NEG_CURVATURE
+
+
+@pytest.mark.parametrize("rows", [40, 96, 132])
+def test_one_launch_cg_takes_any_vertex_numbering(vtx, rows):
+    """A workgroup of the CG step keeps the columns that it reads of other
+    workgroups in LDS, up to 1024: vertices numbered at random need 625 to 715
+    of them at 64 vertices a workgroup (several per thread), up to 956 at 80
+    and 1638 or more at 144, beyond the room there is.  The gradient is that of the tissue numbered in
+    space; both solve to a residual of 1e-12."""
+    V = vtx
+    rng = np.random.default_rng(rows)
+    t = g.hex_lattice(rows, rows, float(np.sqrt(2.0 / (3.0 * np.sqrt(3.0)))))
+    X = t.X + 0.02 * rng.normal(size=t.X.shape)
+    b, lam = rng.normal(size=X.shape), rng.uniform(0.9, 1.1, t.n_edge)
+    to = rng.permutation(t.n_vert)
+    he = t.he.copy()
+    for col in (g.HE_SRC, g.HE_TGT):
+        he[:, col] = to[he[:, col]]
+    back = np.argsort(to)
+    P = V.Params(KA=0.02, A0=1.0, KP=1.0, P0=0.5, lam=_dev(lam))
+    out = []
+    for tis, x, rhs in ((t, X, b), (g.Tissue(he, X[back], t.Lx, t.Ly), X[back], b[back])):
+        T = V.Tissue.from_tissue(tis)
+        got, info = T.param_grad(_dev(x), P, dC_dX=_dev(rhs), theta="lambda", cg_tol=1e-12)
+        assert info["status"] == V.CONVERGED
+        out.append((got.cpu().numpy(), info["cg_iters"]))
+    assert abs(out[0][1] - out[1][1]) <= 0.02 * out[0][1] + 1
+    assert np.abs(out[0][0] - out[1][0]).max() / np.abs(out[0][0]).max() < 1e-9
