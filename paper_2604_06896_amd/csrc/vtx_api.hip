@@ -249,7 +249,7 @@ void free_tissue(vtx_tissue t) {
                     d.cell_he, d.star, d.star_he, t->w.xbuf,
                     t->w.cap, t->w.cell_aux, t->w.partials, t->w.partials2, t->w.mpart,
                     t->w.t1_list,
-                    t->w.ctl, t->w.cg, t->w.scal, t->w.one, t->w.step, t->w.step_part,
+                    t->w.ctl, t->w.cg, t->w.scal, t->w.one, t->w.step, t->w.step_part, t->w.step_tab,
                     t->w.cg_state, t->w.max_sides, t->hess.col, t->hess.top, t->hess.bottom,
                     t->hess.halo, t->hess.n_halo,
                     t->ep_buf,
@@ -330,6 +330,9 @@ int relax_steps(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_
                 const RelaxArgs &ra, hipStream_t s, vtx_relax_result &r, int &overflow) {
     StepCtl &h = *t->w.step_host;
     h = StepCtl{};
+    if (!t->w.step_tab)  // three int4 for each of four lanes a vertex, in whole blocks
+        HIPCHK(hipMalloc((void **)&t->w.step_tab,
+                         3 * 16 * (size_t)kBlock * ((4 * (size_t)t->n_vert + kBlock - 1) / kBlock)));
     h.s[0].status = VTX_NOT_CONVERGED;
     HIPCHK(hipMemcpyAsync(t->w.step, &h, sizeof h, hipMemcpyHostToDevice, s));
     HIPCHK(hipStreamSynchronize(s));

@@ -169,6 +169,7 @@ struct StepState {
     int32_t pending;     // the launch before computed a step from `cur`
     int32_t det;         // ... and listed the short edges it saw
     int32_t redo;        // the step takes its coefficients from `cap` (after a T1 pass)
+    int32_t table;       // the lanes' topology in Workspace::step_tab is current
     int32_t done, status, result_buf, t1_overflow;
 };
 struct StepCtl {
@@ -217,6 +218,7 @@ struct Workspace {
     double *cg;          // CG vectors: x, r, p, Ap (double [4][n_vert][2])
     double *scal;        // device scalars
     StepCtl *step;       // device
+    int4 *step_tab;      // topology of each lane of a step, [3][lanes]; from the first use on
     double *step_part;   // max |F| of each block of a step, [2][blocks]
     StepCtl *step_host;  // pinned host mirror
     CgState *cg_state;   // device [2]
