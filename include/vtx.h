@@ -130,8 +130,9 @@ typedef struct {
     double beta;
     const void *X_target;
     const void *g_lin;
-    int32_t chunk;   /* iterations per captured graph launch (0 = 256); not used where
-                        the whole loop runs in one workgroup */
+    int32_t chunk;   /* iterations per captured graph launch and status read (0: graphs of
+                        60, a status read when the rest could be done, at most every
+                        252); not used where the whole loop runs in one workgroup */
 } vtx_relax_opts;
 
 typedef struct {
@@ -248,7 +249,7 @@ int vtx_edge_lengths(vtx_tissue t, int32_t mode, const void *X, double *len_dev,
  * engine").  A tissue of at most 1024 cells whose position buffers, cell
  * coefficients and corner rows fit a workgroup's LDS runs its whole loop in
  * one workgroup; larger ones run on the whole GPU in captured graphs of
- * `chunk` iterations, and the host reads a status between chunks.  T1
+ * `chunk` iterations, and the host reads a status between them.  T1
  * mutates the tissue's topology.  `res` is a host struct; synchronises. */
 int vtx_relax(vtx_tissue t, int32_t mode, void *X, const vtx_params *p,
               const vtx_relax_opts *o, vtx_relax_result *res, void *stream);

@@ -93,7 +93,7 @@ ParamsRaw raw(const vtx_params *p) {
 // Largest tissue of the one-launch relaxation step, and its launches per
 // captured graph.
 constexpr int64_t kStepMaxVerts = 131072;
-constexpr int kStepChunk = 252;
+constexpr int kStepChunk = 60;
 
 // The same for the one-launch CG step (even, so that every replay starts on
 // the same vectors).
@@ -287,26 +287,44 @@ size_t pos_bytes(vtx_tissue t, int mode) {
     return (size_t)t->n_vert * 2 * (mode == VTX_F32 ? sizeof(float) : sizeof(double));
 }
 
-// Device loop driver: capture `chunk` steps of `body` once, replay until the
-// control block (copied by `read` into host memory, then asked by `done`)
-// reports done.
-template <typename Body, typename Read, typename Done>
+// Device loop driver: runs steps of `body` on the device until the control
+// block (copied by `read` into host memory, then asked by `done`) reports
+// done, looked at after every look() steps.  Steps run as replays of a graph
+// of `chunk` of them, captured when it is first needed, and what is left
+// before a look, if less than two thirds of it, by direct launches, a
+// multiple of 6 (k counts from 0 in both: for bodies that depend on k mod 2
+// and 3).
+template <typename Body, typename Read, typename Done, typename Look>
 int run_loop(vtx_tissue t, int chunk, int64_t max_steps, hipStream_t s, Body body, Read read,
-             Done done) {
+             Done done, Look look) {
     hipGraph_t g = nullptr;
     hipGraphExec_t ge = nullptr;
-    HIPCHK(hipStreamBeginCapture(t->w.cap_stream, hipStreamCaptureModeThreadLocal));
-    for (int k = 0; k < chunk; ++k) body(k, t->w.cap_stream);
-    hipError_t ce = hipStreamEndCapture(t->w.cap_stream, &g);
-    if (ce != hipSuccess) return fail(VTX_E_HIP, "graph capture: %s", hipGetErrorString(ce));
-    ce = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
-    if (ce != hipSuccess) {
-        (void)hipGraphDestroy(g);
-        return fail(VTX_E_HIP, "graph instantiate: %s", hipGetErrorString(ce));
-    }
+    auto replay = [&]() {
+        hipError_t e = hipSuccess;
+        if (!ge) {
+            e = hipStreamBeginCapture(t->w.cap_stream, hipStreamCaptureModeThreadLocal);
+            if (e != hipSuccess) return e;
+            for (int k = 0; k < chunk; ++k) body(k, t->w.cap_stream);
+            e = hipStreamEndCapture(t->w.cap_stream, &g);
+            if (e == hipSuccess) e = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
+        }
+        return e == hipSuccess ? hipGraphLaunch(ge, s) : e;
+    };
     int rc = VTX_OK;
-    for (int64_t done_steps = 0;; done_steps += chunk) {
-        hipError_t e = hipGraphLaunch(ge, s);
+    for (int64_t queued = 0;;) {
+        hipError_t e = hipSuccess;
+        int64_t left = look();
+        for (; left > 0 && e == hipSuccess; left -= chunk) {
+            if (3 * left < 2 * (int64_t)chunk) {
+                const int n = (int)(left + 5) / 6 * 6;
+                for (int k = 0; k < n; ++k) body(k, s);
+                e = hipGetLastError();
+                queued += n;
+                break;
+            }
+            e = replay();
+            queued += chunk;
+        }
         if (e == hipSuccess) e = read();
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) {
@@ -314,14 +332,26 @@ int run_loop(vtx_tissue t, int chunk, int64_t max_steps, hipStream_t s, Body bod
             break;
         }
         if (done()) break;
-        if (done_steps + chunk >= max_steps + 2 * (int64_t)chunk) {
+        if (queued >= max_steps + 2 * (int64_t)chunk) {
             rc = fail(VTX_E_HIP, "device loop did not report completion");
             break;
         }
     }
-    (void)hipGraphExecDestroy(ge);
-    (void)hipGraphDestroy(g);
+    if (ge) (void)hipGraphExecDestroy(ge);
+    if (g) (void)hipGraphDestroy(g);
     return rc;
+}
+
+// Steps before the next look at a relaxation: those that it takes unless it
+// converges, up to kLook.  Capturing a step costs as much as launching it
+// (1.7 us), so the graph is short; replays follow each other without a gap
+// that would show (500 steps of 3000 cells: 3.06 ms with graphs of 252 and a
+// look after each, 2.59 with graphs of 60, 2.64 with direct launches only,
+// which are bound by the host).
+constexpr int64_t kLook = 252;
+int64_t relax_look(const vtx_relax_opts *o, int chunk, int64_t iters) {
+    if (o->chunk > 0) return chunk;
+    return std::max<int64_t>(6, std::min(kLook, o->max_iter - iters + 1));
 }
 
 // The loop of one-launch steps (k_relax_step): no nudge, tissues of up to
@@ -347,7 +377,7 @@ int relax_steps(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_
                               o->max_iter, k, cs);
         },
         [&]() { return hipMemcpyAsync(&h, t->w.step, sizeof h, hipMemcpyDeviceToHost, s); },
-        [&]() { return h.s[0].done != 0; });
+        [&]() { return h.s[0].done != 0; }, [&]() { return relax_look(o, chunk, h.s[0].iter); });
     const StepState &f = h.s[0];
     // (a loop without an exchange, and without an error, left the topology)
     if (ra.t1_enable && (rc || f.n_t1 > 0 || f.t1_overflow)) {
@@ -385,13 +415,14 @@ int relax_grid(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_r
         launch_mean_pos(t->w, VTX_F64, (int)t->n_vert, o->g_lin, mean, s);
         if ((rc = check_launch("nudge mean"))) return rc;
     }
-    int chunk = o->chunk > 0 ? o->chunk : 256;
-    chunk += chunk & 1;  // even: every replay starts on the caller's buffer
+    const int chunk = o->chunk > 0 ? o->chunk + (o->chunk & 1) : kStepChunk;  // (even: every
+                                            // replay starts on the caller's buffer)
     void *bufs[2] = {X, t->w.xbuf};
     rc = run_loop(t, chunk, o->max_iter, s, [&](int k, hipStream_t cs) {
         const int cur = k & 1;
         launch_relax_iter(t->d, t->w, mode, bufs[cur], bufs[cur ^ 1], cur, raw(p), ra, cs);
-    }, [&]() { return fetch_ctl(t, s); }, [&]() { return t->w.ctl_host[0].done != 0; });
+    }, [&]() { return fetch_ctl(t, s); }, [&]() { return t->w.ctl_host[0].done != 0; },
+       [&]() { return relax_look(o, chunk, t->w.ctl_host[0].iter); });
     const LoopCtl &h = t->w.ctl_host[0];
     // (a loop without an exchange, and without an error, left the topology)
     if (ra.t1_enable && (rc || h.n_t1 > 0 || h.t1_overflow)) {
@@ -823,7 +854,7 @@ static int cg_steps(vtx_tissue t, const void *X, const vtx_params *p, const doub
         t, kCgChunk, max_iter + 2, s,
         [&](int k, hipStream_t cs) { launch_cg_step(t->d, t->w, use, tol, max_iter, k, cs); },
         [&]() { return hipMemcpyAsync(&h, t->w.cg_state, sizeof h, hipMemcpyDeviceToHost, s); },
-        [&]() { return h.done != 0; });
+        [&]() { return h.done != 0; }, []() { return (int64_t)kCgChunk; });
     if (rc) return rc;
     r->cg_iters = h.it;
     r->cg_rel_res = h.rel_res;
@@ -868,7 +899,8 @@ static int solve_hessian(vtx_tissue t, int mode, const void *X, const vtx_params
         rc = run_loop(t, 32, max_iter, s, [&](int, hipStream_t cs) {
             if (minres) launch_minres_iter(t->d, t->w, mode, X, raw(p), cs);
             else launch_cg_iter(t->d, t->w, mode, X, raw(p), cs);
-        }, [&]() { return fetch_ctl(t, s); }, [&]() { return t->w.ctl_host[0].done != 0; });
+        }, [&]() { return fetch_ctl(t, s); }, [&]() { return t->w.ctl_host[0].done != 0; },
+           []() { return (int64_t)32; });
         if (rc) return rc;
     }
     const LoopCtl &h = t->w.ctl_host[0];

@@ -269,3 +269,28 @@ def test_one_launch_cg_takes_any_vertex_numbering(vtx, rows):
         out.append((got.cpu().numpy(), info["cg_iters"]))
     assert abs(out[0][1] - out[1][1]) <= 0.02 * out[0][1] + 1
     assert np.abs(out[0][0] - out[1][0]).max() / np.abs(out[0][0]).max() < 1e-9
+
+
+@pytest.mark.parametrize("steps", [1, 6, 39, 40, 61, 253, 292])
+@pytest.mark.parametrize("path", ["t1", "plain", "nudged"])
+def test_relaxation_steps_queued_before_a_status_read(vtx, path, steps):
+    """Without a `chunk` the loop queues as many steps as are left (graphs of
+    60, the last third of one launched directly, a status read after 252 at
+    most); the result is that of graphs of 7 with a read after each, bit for
+    bit, and T1 iterations, which take more launches, are all made."""
+    V = vtx
+    t = g.random_tissue(1400, seed=3)
+    rng = np.random.default_rng(steps)
+    P = V.Params(KA=1.0, A0=1.0, KP=1.0, P0=3.75, lam=_dev(rng.uniform(0.05, 0.15, t.n_edge)))
+    kw = dict(eta=0.01, tol=0.0, patience=1, max_iter=steps)
+    if path == "t1":
+        kw.update(t1_enable=True, l_min=0.05, l_new=0.06)
+    if path == "nudged":
+        kw.update(beta=0.01, X_target=_dev(t.X + 0.01 * rng.normal(size=t.X.shape)))
+    out = []
+    for chunk in (0, 7):
+        T, X = V.Tissue.from_tissue(t), _dev(t.X)
+        info = T.relax(X, P, chunk=chunk, **kw)
+        out.append((X.cpu().numpy(), info["iters"], info["n_t1"], info["status"]))
+    assert out[0][1] == steps and out[0][1:] == out[1][1:]
+    assert np.array_equal(out[0][0], out[1][0])
