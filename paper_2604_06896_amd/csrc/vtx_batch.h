@@ -27,6 +27,7 @@ struct BatchItem {
     void *xbuf;
     void *cap;
     int32_t *t1_list;
+    void *scratch;      // 96 bytes per vertex (the Krylov vectors)
     ParamsRaw p;
     // nudge (equilibrium propagation): beta * C with C the v2v cost to Xt or
     // the linear cost g_lin . X; the mean of grad C is removed

@@ -1360,10 +1360,36 @@ __global__ __launch_bounds__(kRelaxLdsThreads) void k_batch_relax_lds(
 // convergence control; the arithmetic and the order of every step equal
 // those of the single-tissue kernels, so results are bit-identical to
 // vtx_relax.  The returned state is copied back into the caller's buffer.
+//
+// A tissue too large for k_batch_relax_lds keeps its positions (one buffer,
+// the new ones wait in registers until every vertex has read the old) in the
+// launch's dynamic LDS where they fit: eight vertices a thread, 8192 at 1024
+// threads (131 KB in FP64 and MIXED, beside 21 of T1 buffers).  What else a step reads is then in order: the stars, and,
+// laid out in scratch memory by this kernel and again after an exchange, each
+// vertex's three tensions and each cell's corners (a row's start, length and
+// corners are two loads that wait for each other).  15 of the 18 gathers per
+// vertex and step come from LDS.  256 tissues of 4000 cells, MIXED: 28 us a
+// step, 53 with everything in global memory, which moved 4 TB/s and left a
+// 32-CU XCD's 4 MB L2 with six times its size; 64 of 2000, FP64: 16.7, was 22.2.
+// Larger and nudged tissues keep everything in global memory.
+constexpr int kFarImage = 1 << 30;
+constexpr int kRelaxBigKV = 8;   // vertices per thread whose new positions wait
+template <typename PosT>
+__host__ __device__ inline int64_t relax_big_lds_bytes(int64_t n_vert) {
+    return 2 * n_vert * (int64_t)sizeof(PosT);
+}
+template <typename PosT>
+__host__ __device__ inline bool relax_big_fits(int64_t n_vert, int threads, int64_t lds_bytes) {
+    return n_vert <= kRelaxBigKV * (int64_t)threads &&
+           relax_big_lds_bytes<PosT>(n_vert) <= lds_bytes;
+}
+
 template <typename PosT, typename M>
 __global__ __launch_bounds__(1024) void k_batch_relax(const BatchItem *__restrict__ items,
                                                       const int32_t *__restrict__ order,
-                                                      BatchOpts o, vtx_relax_result *res) {
+                                                      BatchOpts o, vtx_relax_result *res,
+                                                      int lds_bytes) {
+    extern __shared__ __align__(16) unsigned char lds_dyn[];
     __shared__ int32_t sort_buf[kT1SortCap];
     __shared__ int32_t extra[kT1Extra];
     __shared__ int32_t scan[1024];
@@ -1380,6 +1406,165 @@ __global__ __launch_bounds__(1024) void k_batch_relax(const BatchItem *__restric
         M *cap = (M *)B.cap;
         int cur = 0;
         if (threadIdx.x == 0) st = RelaxState{0, 0, 0, 0, 0.0, VTX_NOT_CONVERGED, 0, 0, 0, 0};
+        const bool in_lds = B.beta == 0.0 &&
+                            relax_big_fits<PosT>(t.n_vert, (int)blockDim.x, lds_bytes);
+        if (in_lds) {
+            PosT *Xl = (PosT *)lds_dyn;
+            const int nv = t.n_vert, nc = t.n_cell, bd = blockDim.x;
+            for (int k = threadIdx.x; k < 2 * nv; k += bd) Xl[k] = ((const PosT *)B.X)[k];
+            M *lamv = (M *)B.scratch;                         // [3][n_vert]
+            int4 *rows = (int4 *)((char *)B.scratch + 48 * (int64_t)nv);
+            int2 *more = (int2 *)(rows + 2 * (int64_t)nc);
+            auto load_tables = [&]() {
+                for (int v = threadIdx.x; v < nv; v += bd)
+#pragma unroll
+                    for (int k = 0; k < 3; ++k)
+                        lamv[k * (int64_t)nv + v] = (M)p.lm(t.star[star_edge_at(nv, k, v)]);
+                // corners 0 to 6, sides (and a bit: an image in the rest of the
+                // row); row start, corner 7; corner 0 again beyond the last
+                for (int c = threadIdx.x; c < nc; c += bd) {
+                    const int rb = t.row_ptr[c], nn = t.nsides[c];
+                    auto corner = [&](int j) { return t.corner[rb + (j < nn ? j : 0)]; };
+                    rows[c] = int4{corner(0), corner(1), corner(2), corner(3)};
+                    int far = 0;
+                    for (int j = 7; j < nn; ++j)
+                        far |= ((uint32_t)corner(j) >> kIdBits) != kZeroImage ? kFarImage : 0;
+                    rows[nc + c] = int4{corner(4), corner(5), corner(6), nn | far};
+                    more[c] = int2{rb, corner(7)};
+                }
+            };
+            load_tables();
+            if (threadIdx.x == 0) s_cnt = 0u;
+            __syncthreads();
+            for (;;) {
+                // (an index that the compiler cannot see through: the
+                // addresses of eight vertices do not change from step to
+                // step, and kept in registers would cost 90 spilled ones)
+                uint32_t tid = threadIdx.x;
+                asm volatile("" : "+v"(tid));
+                const PosT lmin2p = (PosT)first_lane_f64((double)(PosT)lmin2);
+                // cell pass
+                for (uint32_t c = tid; c < (uint32_t)nc; c += bd) {
+                    const int4 ra = rows[c], rc = rows[(uint32_t)nc + c];
+                    const int2 rd = more[c];
+                    const int rb = rd.x, nn = rc.w & ~kFarImage;
+                    const int32_t w[7] = {ra.x, ra.y, ra.z, ra.w, rc.x, rc.y, rc.z};
+                    uint32_t img = 0;
+#pragma unroll
+                    for (int j = 0; j < 7; ++j) img |= (uint32_t)w[j] ^ (kZeroImage << kIdBits);
+                    auto head = [&](int j) { return w[j]; };
+                    auto tail = [&](int j) {
+                        return j == 7 ? rd.y : j < nn ? t.corner[rb + j] : w[0];
+                    };
+                    const PosT ka = p.ka(c), a0 = p.a0(c), kp = p.kp(c), p0 = p.p0(c);
+                    PosT A, P;
+                    if (__builtin_amdgcn_ballot_w64((img >> kIdBits) != 0 ||
+                                                    (rc.w & kFarImage)) != 0)
+                        cell_geom_flat<PosT, false>(t, Xl, nn, head, tail, rb, A, P,
+                                                    o.t1_enable != 0, lmin2p, B.t1_list, &s_cnt);
+                    else
+                        cell_geom_flat<PosT, true>(t, Xl, nn, head, tail, rb, A, P,
+                                                   o.t1_enable != 0, lmin2p, B.t1_list, &s_cnt);
+                    st2(cap, c, (M)((PosT)2 * ka * (A - a0)), (M)((PosT)2 * kp * (P - p0)));
+                }
+                __syncthreads();
+                const int ncand = (int)s_cnt;
+                if (ncand > 0) {
+                    const int64_t swaps0 = st.n_t1;
+                    batch_t1_pass<PosT, M>(&B, Xl, ncand, o.l_min, o.l_new, sort_buf, extra, scan,
+                                           &st);
+                    if (st.n_t1 != swaps0) load_tables();
+                    if (threadIdx.x == 0) s_cnt = 0u;
+                    __syncthreads();
+                }
+                // vertex pass: the new positions wait in registers
+                double mf = 0.0;
+                PosT nx[kRelaxBigKV], ny[kRelaxBigKV];
+#pragma unroll
+                for (int j = 0; j < kRelaxBigKV; ++j) {
+                    const uint32_t v = tid + (uint32_t)(j * bd);
+                    nx[j] = ny[j] = 0;
+                    if (v < (uint32_t)nv) {
+                        StarLoad<PosT, M> L;
+                        const int4 a = reinterpret_cast<const int4 *>(t.star)[v];
+                        const int2 b = *reinterpret_cast<const int2 *>(
+                            t.star + 4 * (int64_t)nv + 4 * v);
+                        L.w[0] = a.x;
+                        L.w[1] = a.y;
+                        L.w[2] = a.z;
+                        L.c[0] = a.w;
+                        L.c[1] = b.x;
+                        L.c[2] = b.y;
+                        L.pi = ld2(Xl, v);
+                        M lam[3];
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) {
+                            lam[k] = lamv[(uint32_t)(k * nv) + v];
+                            L.lam[k] = 0;
+                            L.q[k] = ld2(Xl, id_of(L.w[k]));
+                            L.cc[k] = ld2(cap, L.c[k]);
+                        }
+                        const uint32_t z = kZeroImage << kIdBits;
+                        const uint32_t img = ((uint32_t)a.x ^ z) | ((uint32_t)a.y ^ z) |
+                                             ((uint32_t)a.z ^ z);
+                        Star<PosT, M> s;
+                        PosT xi, yi;
+                        if (__builtin_amdgcn_ballot_w64((img >> kIdBits) != 0) != 0)
+                            star_math<PosT, M, false>(t, L, s, xi, yi);
+                        else
+                            star_math<PosT, M, true>(t, L, s, xi, yi);
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) s.lam[k] = lam[k];
+                        M fx, fy;
+                        star_force<PosT, M>(s, fx, fy);
+                        const double gx = fx, gy = fy;
+                        mf = fmax(mf, fmax(fabs(gx), fabs(gy)));
+                        if (!(gx == gx) || !(gy == gy)) mf = INFINITY;
+                        nx[j] = (PosT)((double)xi + o.eta * gx);
+                        ny[j] = (PosT)((double)yi + o.eta * gy);
+                    }
+                }
+                const double m = block_max(mf, sh);  // its barriers follow every read of Xl
+                if (threadIdx.x == 0) {
+                    st.iter += 1;
+                    st.last_mf = m;
+                    st.changed = 1;  // take the step
+                    if (st.bad_t1) {
+                        st.done = 1;
+                        st.status = VTX_E_CAPACITY;
+                        st.changed = 0;
+                    } else if (!(m <= 1.7976931348623157e308)) {
+                        st.done = 1;
+                        st.status = VTX_E_NONFINITE;
+                        st.changed = 0;
+                    } else {
+                        st.count = m < o.tol ? st.count + 1 : 0;
+                        if (st.count >= o.patience) {
+                            st.done = 1;
+                            st.status = VTX_CONVERGED;
+                            st.changed = 0;
+                        } else if (st.iter >= o.max_iter) {
+                            st.done = 1;
+                            st.status = VTX_NOT_CONVERGED;
+                        }
+                    }
+                }
+                __syncthreads();
+                const int done = st.done;
+                if (st.changed)
+#pragma unroll
+                    for (int j = 0; j < kRelaxBigKV; ++j) {
+                        const int v = (int)threadIdx.x + j * bd;
+                        if (v < nv) st2(Xl, v, nx[j], ny[j]);
+                    }
+                __syncthreads();
+                if (done) break;
+            }
+            for (int k = threadIdx.x; k < 2 * nv; k += bd) ((PosT *)B.X)[k] = Xl[k];
+            __syncthreads();
+            batch_relax_result<PosT>(B, t, p, st, sh, res, idx);
+            return;
+        }
         for (;;) {
             // buffer selector and threshold as wave-uniform values (scalar
             // registers), so they need no vector register across the T1 call
@@ -1737,14 +1922,37 @@ void launch_relax_lds(int mode, bool t1, const BatchItem *it, const int32_t *ord
                 k_batch_relax_lds<double, float, false, 4>);
 }
 
-void launch_batch_relax(int mode, const BatchItem *it, const int32_t *order, int n, int threads,
-                        const BatchOpts &bo, vtx_relax_result *res, hipStream_t s) {
-    auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(n), dim3(threads), 0, s, it, order, bo, res);
-    };
-    if (mode == VTX_F32) go(k_batch_relax<float, float>);
-    else if (mode == VTX_F64) go(k_batch_relax<double, double>);
-    else go(k_batch_relax<double, float>);
+// The general kernel, with dynamic LDS for the largest of the batch's tissues
+// whose positions fit there.
+template <typename PosT, typename M>
+int launch_batch_relax_t(vtx_batch b, const BatchItem *it, const int32_t *order, int n,
+                         int threads, const BatchOpts &bo, hipStream_t s) {
+    const void *kern = reinterpret_cast<const void *>(&k_batch_relax<PosT, M>);
+    int dev = 0, lds_max = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess)
+        e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+    hipFuncAttributes fa{};
+    if (e == hipSuccess) e = hipFuncGetAttributes(&fa, kern);
+    if (e != hipSuccess) return hip_fail(e);
+    const int64_t budget = (int64_t)lds_max - (int64_t)fa.sharedSizeBytes;
+    int64_t lds = 0;
+    for (vtx_tissue t : b->ts)
+        if (relax_big_fits<PosT>(tissue_size(t), threads, budget))
+            lds = std::max(lds, relax_big_lds_bytes<PosT>(tissue_size(t)));
+    e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return hip_fail(e);
+    hipLaunchKernelGGL((k_batch_relax<PosT, M>), dim3(n), dim3(threads), (size_t)lds, s, it, order,
+                       bo, b->res_d, (int)lds);
+    return launched();
+}
+
+int launch_batch_relax(vtx_batch b, int mode, const BatchItem *it, const int32_t *order, int n,
+                       int threads, const BatchOpts &bo, hipStream_t s) {
+    if (mode == VTX_F32) return launch_batch_relax_t<float, float>(b, it, order, n, threads, bo, s);
+    if (mode == VTX_F64)
+        return launch_batch_relax_t<double, double>(b, it, order, n, threads, bo, s);
+    return launch_batch_relax_t<double, float>(b, it, order, n, threads, bo, s);
 }
 
 // The split schedule: each tissue over K cooperating workgroups
@@ -1782,8 +1990,7 @@ int relax_split(vtx_batch b, int mode, const BatchItem *it, const BatchOpts &bo,
                        hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return hip_fail(e);
     const int m = (int)rest.size();
-    launch_batch_relax(mode, it, b->order2_d, m, 1024, bo, b->res_d, s);
-    return launched();
+    return launch_batch_relax(b, mode, it, b->order2_d, m, 1024, bo, s);
 }
 
 // The batch's items for positions X (nudge beta towards Xt, or along g_lin)
@@ -1800,6 +2007,7 @@ int make_items(vtx_batch b, void *const *X, const vtx_params *p, const void *con
         it.xbuf = w.xbuf;
         it.cap = w.cap;
         it.t1_list = w.t1_list;
+        it.scratch = w.cg;
         it.p = raw_params(p[i]);
         it.Xt = Xt ? Xt[i] : nullptr;
         it.g_lin = g_lin ? g_lin[i] : nullptr;
@@ -1856,12 +2064,13 @@ int batch_relax_run(vtx_batch b, int mode, void *const *X, const vtx_params *p,
     if (block_threads == 0) block_threads = 1024;
     int rc = VTX_OK;
     if (split_K == 0) {
-        if (lds > 0)
+        if (lds > 0) {
             launch_relax_lds(mode, t1, it, b->order_d, n, largest(b), beta != 0.0, lds, bo,
                              b->res_d, s);
-        else
-            launch_batch_relax(mode, it, b->order_d, n, block_threads, bo, b->res_d, s);
-        rc = launched();
+            rc = launched();
+        } else {
+            rc = launch_batch_relax(b, mode, it, b->order_d, n, block_threads, bo, s);
+        }
     }
     if (rc) return rc;
     // The fused evaluation's tables of the tissues that made exchanges, in
@@ -1968,7 +2177,7 @@ int relax_one(const DevTissue &t, const Workspace &w, int mode, void *X, const P
     const int rc = relax_lds_plan(mode, t1, &tp, 1, &lds);
     if (rc || lds == 0) return rc;
     OneSlot *slot = (OneSlot *)w.one;
-    const BatchItem item{t, X, w.xbuf, w.cap, w.t1_list, p, ra.nudge == 1 ? ra.X_target : nullptr,
+    const BatchItem item{t, X, w.xbuf, w.cap, w.t1_list, w.cg, p, ra.nudge == 1 ? ra.X_target : nullptr,
                          ra.nudge == 2 ? (const double *)ra.g_lin : nullptr,
                          ra.nudge ? ra.beta : 0.0};
     hipLaunchKernelGGL(k_put_item<BatchItem>, dim3(1), dim3(64), 0, s, item, &slot->item);

@@ -294,3 +294,28 @@ def test_relaxation_steps_queued_before_a_status_read(vtx, path, steps):
         out.append((X.cpu().numpy(), info["iters"], info["n_t1"], info["status"]))
     assert out[0][1] == steps and out[0][1:] == out[1][1:]
     assert np.array_equal(out[0][0], out[1][0])
+
+
+@pytest.mark.parametrize("mode", ["f32", "mixed", "f64"])
+@pytest.mark.parametrize("cells,threads", [((1025, 2048), 512), ((2049, 1100), 512),
+                                           ((4096, 1300), 1024), ((4097, 1300), 1024)])
+def test_batched_positions_in_lds_equal_the_grid(vtx, mode, cells, threads):
+    """The general batched kernel keeps the positions of up to eight vertices
+    per thread in LDS and those of larger tissues in global memory: iterates,
+    counts and topology of both, through exchanges that move rows and change
+    images, are those of Tissue.relax bit for bit."""
+    V = vtx
+    dt = V.pos_dtype(mode)
+    ts = [g.random_tissue(n, seed=90 + n) for n in cells]
+    rng = np.random.default_rng(cells[0])
+    Ps = [V.Params(KA=1.0, A0=_dev(rng.uniform(0.9, 1.1, t.n_cell), dt), KP=1.0, P0=3.75,
+                   lam=_dev(rng.uniform(0.05, 0.15, t.n_edge), dt)) for t in ts]
+    opts = dict(eta=3e-3, t1_enable=True, l_min=0.03, tol=0.0, max_iter=120)
+    A, B = ([V.Tissue.from_tissue(t) for t in ts] for _ in range(2))
+    XA, XB = ([_dev(t.X, dt) for t in ts] for _ in range(2))
+    got = V.Batch(A).relax(XA, Ps, mode=mode, block_threads=threads, **opts)
+    for i, t in enumerate(ts):
+        ref = B[i].relax(XB[i], Ps[i], mode=mode, **opts)
+        keys = ("iters", "n_t1", "n_stretch", "status", "max_f")
+        assert [got[i][k] for k in keys] == [ref[k] for k in keys] and ref["n_t1"] > 50
+        assert torch.equal(XA[i], XB[i]) and np.array_equal(A[i].topology(), B[i].topology())
