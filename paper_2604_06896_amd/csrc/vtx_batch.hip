@@ -1406,7 +1406,9 @@ __global__ __launch_bounds__(1024) void k_batch_relax(const BatchItem *__restric
         M *cap = (M *)B.cap;
         int cur = 0;
         if (threadIdx.x == 0) st = RelaxState{0, 0, 0, 0, 0.0, VTX_NOT_CONVERGED, 0, 0, 0, 0};
-        const bool in_lds = B.beta == 0.0 &&
+        // (the tables take 48 bytes a vertex and 40 a cell of the 96 a vertex;
+        // on a torus there are half as many cells as vertices)
+        const bool in_lds = B.beta == 0.0 && t.n_cell <= t.n_vert &&
                             relax_big_fits<PosT>(t.n_vert, (int)blockDim.x, lds_bytes);
         if (in_lds) {
             PosT *Xl = (PosT *)lds_dyn;
