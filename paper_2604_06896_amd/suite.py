@@ -7,7 +7,7 @@ and lambda, T1 at 0.01) workloads to max |F| < 1e-6.
 batched_relax: the 512-tissue workload (N ~ U{64..4096}, one P0 ~ U[3.6,3.9]
 per tissue, lambda ~ U[0,0.2]) relaxed with T1 (l_min 0.01) towards
 max |F| < 1e-6 in one persistent launch, against the single-tissue path
-(captured graph chunks) on a stratified sample of the same tissues, all of
+(one workgroup for a small tissue, else captured graphs) on a stratified sample of the same tissues, all of
 whose solves are timed.
 
 param_gradients: tissues of 1000 cells, P0 = 3.75, hidden tensions lambda*
@@ -53,8 +53,8 @@ def single_100(log=print):
         log(f"100 cells {name}: status {r['status']}, {r['iters']} steps, T1 {r['n_t1']}, "
             f"max|F| {r['max_f']:.2e}, {dt:.2f}s")
         if t1:
-            # the same relaxation as a batch of one: the whole loop in one
-            # workgroup (LDS-resident kernel) instead of three launches a step
+            # the same relaxation as a batch of one: the same kernel (the
+            # whole loop in one workgroup)
             T2 = V.Tissue.from_tissue(t)
             X2 = torch.as_tensor(t.X, dtype=torch.float64, device="cuda")
             B = V.Batch([T2])
