@@ -518,12 +518,36 @@ __global__ __launch_bounds__(kTileV) void k_eval_fused(DevTissue t, const PosT *
     __shared__ double sh[2 * (kTileV / 64)];
     const int tid = threadIdx.x;
     const int tile = xcd_block();
-    const int4 info = tt.info[tile];
-    const int nc = info.x, nh = info.y, ncorner = info.w;
-    const bool local = info.z == 0;
     const int nv = t.n_vert;
     const int v = tile * kTileV + tid;
     const bool live = v < nv;
+    // The tile's lists, without waiting for their lengths (a block is bound
+    // by the chain of its loads, lengths, list, positions, not by bytes): the
+    // first kAhead entries and kAheadCorner * 8 corner references (a tile has
+    // about 170 cells, 160 halo vertices and 1020 references); the tables
+    // hold that many slots, used or not.  10^6 cells, FP32: 42.3 -> 36.6 us
+    // an evaluation where the states alternate, 37.8 -> 33.2 with two.
+    constexpr int kAhead = 192, kAheadCorner = 128;
+    static_assert(kAhead <= kTileCap && kAhead <= kHaloCap && kAheadCorner <= kCornerCap / 8,
+                  "slots of a tile");
+    const int32_t *cl = tt.cells + (int64_t)tile * kTileCap;
+    const int32_t *hl = tt.halo + (int64_t)tile * kHaloCap;
+    const uint4 *src = reinterpret_cast<const uint4 *>(tt.corners + (int64_t)tile * kCornerCap);
+    const uint16_t *cs = tt.cstart + (int64_t)tile * kCstartPad;
+    int32_t x0 = 0, h0 = 0;
+    uint16_t r0 = 0;
+    uint4 c0{0, 0, 0, 0};
+    if (tid < kAhead) {
+        h0 = hl[tid];
+        x0 = cl[tid];
+        r0 = cs[tid];
+    }
+    if (tid < kAheadCorner) c0 = src[tid];
+    V2 xv{0, 0};
+    if (live) xv = ld2(X, v);
+    const int4 info = tt.info[tile];
+    const int nc = info.x, nh = info.y, ncorner = info.w;
+    const bool local = info.z == 0;
     const PosT *Xl = reinterpret_cast<const PosT *>(sh_x);
     const uint16_t *crn = reinterpret_cast<const uint16_t *>(sh_corner);
     StarLoad<PosT, M> L;
@@ -545,7 +569,7 @@ __global__ __launch_bounds__(kTileV) void k_eval_fused(DevTissue t, const PosT *
             L.w[0] = s4.x;
             L.w[1] = s4.y;
             L.w[2] = s4.z;
-            L.pi = ld2(X, v);
+            L.pi = xv;
 #pragma unroll
             for (int k = 0; k < 3; ++k) L.q[k] = ld2(X, id_of(L.w[k]));
         }
@@ -558,16 +582,19 @@ __global__ __launch_bounds__(kTileV) void k_eval_fused(DevTissue t, const PosT *
         }
     }
     // the thread's first cell (tiles rarely have more than kTileV cells)
-    const int32_t *cl = tt.cells + (int64_t)tile * kTileCap;
-    const int32_t x0 = tid < nc ? cl[tid] : 0;
+    if (tid >= kAhead && tid < nc) x0 = cl[tid];
     if (local) {
-        if (live) sh_x[tid] = ld2(X, v);
-        const int32_t *hl = tt.halo + (int64_t)tile * kHaloCap;
-        for (int j = tid; j < nh; j += kTileV) sh_x[kTileV + j] = ld2(X, hl[j]);
-        const uint4 *src = reinterpret_cast<const uint4 *>(tt.corners + (int64_t)tile * kCornerCap);
-        for (int j = tid; j < (ncorner + 7) / 8; j += kTileV) sh_corner[j] = src[j];
-        const uint16_t *cs = tt.cstart + (int64_t)tile * kCstartPad;
-        for (int j = tid; j <= nc; j += kTileV) sh_cstart[j] = cs[j];
+        if (live) sh_x[tid] = xv;
+        const int nq = (ncorner + 7) / 8;
+        if (tid < kAhead && tid < nh) sh_x[kTileV + tid] = ld2(X, h0);
+        for (int j = tid < kAhead ? tid + kTileV : tid; j < nh; j += kTileV)
+            sh_x[kTileV + j] = ld2(X, hl[j]);
+        if (tid < kAheadCorner && tid < nq) sh_corner[tid] = c0;
+        for (int j = tid < kAheadCorner ? tid + kTileV : tid; j < nq; j += kTileV)
+            sh_corner[j] = src[j];
+        if (tid < kAhead && tid <= nc) sh_cstart[tid] = r0;
+        for (int j = tid < kAhead ? tid + kTileV : tid; j <= nc; j += kTileV)
+            sh_cstart[j] = cs[j];
     }
     __syncthreads();
     double ec = 0.0;
