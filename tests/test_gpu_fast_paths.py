@@ -319,3 +319,32 @@ def test_batched_positions_in_lds_equal_the_grid(vtx, mode, cells, threads):
         keys = ("iters", "n_t1", "n_stretch", "status", "max_f")
         assert [got[i][k] for k in keys] == [ref[k] for k in keys] and ref["n_t1"] > 50
         assert torch.equal(XA[i], XB[i]) and np.array_equal(A[i].topology(), B[i].topology())
+
+
+@pytest.mark.parametrize("mode", ["f32", "mixed", "f64"])
+@pytest.mark.parametrize("window", [1, 300, 400, 512])
+def test_fused_evaluation_lists_of_any_length(vtx, mode, window):
+    """A tile reads the first 192 cells and halo vertices and 1024 corner
+    references of its lists ahead of their lengths.  Vertices numbered at
+    random within a window give lists of 118 to 171 cells (1), to 316 cells and
+    515 halo vertices (300), always beyond 192 and 1024 (512), and some tiles
+    that fit no list (400): forces and max |F| are those of the two passes, bit
+    for bit, with per-cell and per-edge parameters."""
+    V = vtx
+    dt = V.pos_dtype(mode)
+    t = g.random_tissue(1500, seed=8)
+    rng = np.random.default_rng(window)
+    to = np.arange(t.n_vert)
+    for a in range(0, t.n_vert, window):
+        to[a:a + window] = a + rng.permutation(min(window, t.n_vert - a))
+    he = t.he.copy()
+    for col in (g.HE_SRC, g.HE_TGT):
+        he[:, col] = to[he[:, col]]
+    t = g.Tissue(he, t.X[np.argsort(to)], t.Lx, t.Ly)
+    T, X = V.Tissue.from_tissue(t), _dev(t.X, dt)
+    assert (T.tile_stats()["global_tiles"] > 0) == (window == 400)
+    P = V.Params(KA=1.0, A0=1.0, KP=1.0, P0=_dev(rng.uniform(3.6, 3.9, t.n_cell), dt),
+                 lam=_dev(rng.uniform(0.05, 0.15, t.n_edge), dt))
+    _, F, maxf = T.energy_forces(X, P, mode=mode, want_maxf=True)
+    F2, maxf2 = T.vertex_forces(X, P, T.cell_coeffs(X, P, mode=mode), mode=mode, want_maxf=True)
+    assert torch.equal(F, F2) and float(maxf) == float(maxf2)
