@@ -601,6 +601,9 @@ __global__ __launch_bounds__(kTileV) void k_eval_fused(DevTissue t, const PosT *
     for (int i = tid; i < nc; i += kTileV) {
         const int32_t x = i == tid ? x0 : cl[i];
         const int c = (int)((uint32_t)x & kIdMask);
+        // read ahead of the geometry (per-cell P0, MIXED: 18.4 -> 17.9 us at
+        // 250000 cells, 13.8 -> 13.2 at 100000 in FP64)
+        const PosT ka = p.ka(c), kp = p.kp(c), a0 = p.a0(c), p0 = p.p0(c);
         PosT A, P;
         if (local) {
             const int rb = sh_cstart[i], n = (int)sh_cstart[i + 1] - rb;
@@ -618,8 +621,7 @@ __global__ __launch_bounds__(kTileV) void k_eval_fused(DevTissue t, const PosT *
                 t, X, n, [&](int k) { return t.corner[rb + k]; }, rb, A, P, false, (PosT)0,
                 (int32_t *)nullptr, (unsigned int *)nullptr);
         }
-        const PosT ka = p.ka(c), kp = p.kp(c);
-        const PosT da = A - p.a0(c), dp = P - p.p0(c);
+        const PosT da = A - a0, dp = P - p0;
         typename Vec2<M>::type cc;
         cc.x = (M)((PosT)2 * ka * da);
         cc.y = (M)((PosT)2 * kp * dp);
