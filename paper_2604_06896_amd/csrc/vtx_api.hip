@@ -482,9 +482,11 @@ int relax_impl(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_r
     if (one) HIPCHK(hipMemcpyAsync(&r, one, sizeof r, hipMemcpyDeviceToHost, s));
     HIPCHK(hipMemcpyAsync(e, t->w.scal + 4, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    if (one && ra.t1_enable && (r.n_t1 > 0 || r.status == VTX_E_CAPACITY) &&
-        (rc = vtx::tissue_topology_changed(t, s)))
-        return rc;
+    // (waited for: the next call on the tissue may come on another stream)
+    if (one && ra.t1_enable && (r.n_t1 > 0 || r.status == VTX_E_CAPACITY)) {
+        if ((rc = vtx::tissue_topology_changed(t, s))) return rc;
+        HIPCHK(hipStreamSynchronize(s));
+    }
     if (r.status == VTX_E_CAPACITY) overflow = 3;
     const bool nonfinite = r.status == VTX_E_NONFINITE;
     r.energy = e[0] + (ra.nudge ? o->beta * e[1] : 0.0);
