@@ -277,7 +277,9 @@ int vtx_hvp(vtx_tissue t, int32_t mode, const void *X, const vtx_params *p, cons
  *     solver, Methods, ID), which needs H symmetric only; cg_tol bounds the
  *     recursive residual |P b - H mu| / |P b|.  With either solver an FP64
  *     tissue of at most 1024 cells is solved by one workgroup, others by
- *     launches on the whole GPU.
+ *     launches on the whole GPU.  A dC_dX that is not finite, or whose squared
+ *     norm overflows, is not solved for: VTX_CG_MAXITER after 0 iterations,
+ *     cg_rel_res NaN, a zero gradient.
  *   EP_CENTRED: relaxes E + (beta/2) C and E - (beta/2) C from X_star and
  *     returns (dE/dtheta(X+) - dE/dtheta(X-)) / beta, where C is the v2v
  *     cost to X_target when given (device, element type of X) and the

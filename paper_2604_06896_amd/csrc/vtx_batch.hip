@@ -206,9 +206,10 @@ __device__ __forceinline__ int batch_cg_fast(const DevTissue &t, const DevParams
     }
     rr = block_allsum(rr, sh);  // its barriers also publish q and the rows
     const double rr0 = rr;
-    int status = rr0 > 0.0 ? VTX_CG_MAXITER : VTX_CONVERGED;
+    const bool solve = krylov_iterates(rr0);
+    int status = rr0 == 0.0 ? VTX_CONVERGED : VTX_CG_MAXITER;
     int64_t it = 0;
-    while (status == VTX_CG_MAXITER && it < o.max_iter) {
+    while (solve && status == VTX_CG_MAXITER && it < o.max_iter) {
         if (sqrt(rr) <= o.tol * sqrt(rr0)) {
             status = VTX_CONVERGED;
             break;
@@ -273,8 +274,8 @@ __device__ __forceinline__ int batch_cg_fast(const DevTissue &t, const DevParams
         }
         __syncthreads();
     }
-    if (status == VTX_CG_MAXITER && sqrt(rr) <= o.tol * sqrt(rr0)) status = VTX_CONVERGED;
-    rel_out = rr0 > 0.0 ? sqrt(rr / rr0) : 0.0;
+    if (solve && status == VTX_CG_MAXITER && sqrt(rr) <= o.tol * sqrt(rr0)) status = VTX_CONVERGED;
+    rel_out = rr0 == 0.0 ? 0.0 : sqrt(rr / rr0);
     it_out = it;
 #pragma unroll
     for (int j = 0; j < KV; ++j) {
@@ -374,8 +375,9 @@ __global__ __launch_bounds__(MAXT) void k_batch_cg(const GradItem *__restrict__ 
             }
             rr = block_allsum(rr, sh);
             const double rr0 = rr;
-            status = rr0 > 0.0 ? VTX_CG_MAXITER : VTX_CONVERGED;
-            while (status == VTX_CG_MAXITER && it < o.max_iter) {
+            const bool solve = krylov_iterates(rr0);
+            status = rr0 == 0.0 ? VTX_CONVERGED : VTX_CG_MAXITER;
+            while (solve && status == VTX_CG_MAXITER && it < o.max_iter) {
                 if (sqrt(rr) <= o.tol * sqrt(rr0)) {
                     status = VTX_CONVERGED;
                     break;
@@ -413,8 +415,9 @@ __global__ __launch_bounds__(MAXT) void k_batch_cg(const GradItem *__restrict__ 
                 }
                 __syncthreads();
             }
-            if (status == VTX_CG_MAXITER && sqrt(rr) <= o.tol * sqrt(rr0)) status = VTX_CONVERGED;
-            rel_res = rr0 > 0.0 ? sqrt(rr / rr0) : 0.0;
+            if (solve && status == VTX_CG_MAXITER && sqrt(rr) <= o.tol * sqrt(rr0))
+                status = VTX_CONVERGED;
+            rel_res = rr0 == 0.0 ? 0.0 : sqrt(rr / rr0);
         } else {
             // MINRES (the recurrences of k_mr_lanczos / k_mr_update): Lanczos
             // vectors mq (current), mqp (previous), mz (next); search
@@ -438,8 +441,9 @@ __global__ __launch_bounds__(MAXT) void k_batch_cg(const GradItem *__restrict__ 
             }
             __syncthreads();
             double beta = 0.0, c1 = 1.0, s1 = 0.0, c2 = 1.0, s2 = 0.0, phibar = beta1;
-            status = beta1 > 0.0 ? VTX_CG_MAXITER : VTX_CONVERGED;
-            while (status == VTX_CG_MAXITER && it < o.max_iter) {
+            const bool solve = krylov_iterates(beta1);
+            status = beta1 == 0.0 ? VTX_CONVERGED : VTX_CG_MAXITER;
+            while (solve && status == VTX_CG_MAXITER && it < o.max_iter) {
                 for (int c = threadIdx.x; c < t.n_cell; c += blockDim.x)
                     hvp_cell_one<PosT, M>(t, Xh, p, mq, aux, c);
                 __syncthreads();
@@ -484,7 +488,7 @@ __global__ __launch_bounds__(MAXT) void k_batch_cg(const GradItem *__restrict__ 
                 if (fabs(phibar) <= o.tol * beta1) status = VTX_CONVERGED;
                 else if (!(beta_next > 0.0)) break;
             }
-            rel_res = beta1 > 0.0 ? fabs(phibar) / beta1 : 0.0;
+            rel_res = beta1 == 0.0 ? 0.0 : fabs(phibar) / beta1;
         }
         // project the solution to zero mean
         sx = 0.0;
@@ -752,13 +756,14 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_lds(const GradItem *__r
     // by their own thread, off the step's chain: they stay in global memory.
     double2 *xg = (double2 *)G.cg;
     for (int v = tid; v < nv; v += bd) xg[v] = double2{0.0, 0.0};
-    int status = rr0 > 0.0 ? VTX_CG_MAXITER : VTX_CONVERGED;
+    const bool solve = krylov_iterates(rr0);
+    int status = rr0 == 0.0 ? VTX_CONVERGED : VTX_CG_MAXITER;
     int64_t it = 0;
     double rel_res = 0.0;
     double hx[KV], hy[KV];
     if (!MINRES) {
         const double stop = o.tol * sqrt(rr0);
-        while (status == VTX_CG_MAXITER && it < o.max_iter) {
+        while (solve && status == VTX_CG_MAXITER && it < o.max_iter) {
             if (__builtin_amdgcn_readfirstlane(sqrt(rr) <= stop ? 1 : 0)) {
                 status = VTX_CONVERGED;
                 break;
@@ -790,8 +795,8 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_lds(const GradItem *__r
                 }
             }
         }
-        if (status == VTX_CG_MAXITER && sqrt(rr) <= stop) status = VTX_CONVERGED;
-        rel_res = rr0 > 0.0 ? sqrt(rr / rr0) : 0.0;
+        if (solve && status == VTX_CG_MAXITER && sqrt(rr) <= stop) status = VTX_CONVERGED;
+        rel_res = rr0 == 0.0 ? 0.0 : sqrt(rr / rr0);
     } else {
         // the recurrences of k_batch_cg; `ql` holds the current Lanczos
         // vector, bx, by the previous one
@@ -807,7 +812,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_lds(const GradItem *__r
             bx[j] = by[j] = 0.0;
         }
         double beta = 0.0, c1 = 1.0, s1 = 0.0, c2 = 1.0, s2 = 0.0, phibar = beta1;
-        while (status == VTX_CG_MAXITER && it < o.max_iter) {
+        while (solve && status == VTX_CG_MAXITER && it < o.max_iter) {
             const double alpha = solve_sum(hess(hx, hy), sh_a);
             double zz = 0.0;
 #pragma unroll
@@ -857,7 +862,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_lds(const GradItem *__r
             if (fabs(phibar) <= o.tol * beta1) status = VTX_CONVERGED;
             else if (!(beta_next > 0.0)) break;
         }
-        rel_res = beta1 > 0.0 ? fabs(phibar) / beta1 : 0.0;
+        rel_res = beta1 == 0.0 ? 0.0 : fabs(phibar) / beta1;
     }
     // project the solution to zero mean
     __syncthreads();  // a step that ended the loop early may still read sh_a

@@ -368,11 +368,12 @@ __global__ __launch_bounds__(kMbThreads) void k_batch_cg_mb(MbArgs a) {
         if (!sync.arrive(vals, 1, s_out, &s_flag)) break;
         rr = s_out[0];
         const double rr0 = rr;
-        int status = rr0 > 0.0 ? VTX_CG_MAXITER : VTX_CONVERGED;
+        const bool solve = krylov_iterates(rr0);
+        int status = rr0 == 0.0 ? VTX_CONVERGED : VTX_CG_MAXITER;
         int64_t it = 0;
         double *rx = G.cg + 2 * (int64_t)nv;   // r of every vertex, for the halo exchange
         bool alive = true;
-        while (status == VTX_CG_MAXITER && it < a.o.max_iter) {
+        while (solve && status == VTX_CG_MAXITER && it < a.o.max_iter) {
             if (sqrt(rr) <= a.o.tol * sqrt(rr0)) {
                 status = VTX_CONVERGED;
                 break;
@@ -475,7 +476,8 @@ __global__ __launch_bounds__(kMbThreads) void k_batch_cg_mb(MbArgs a) {
             __syncthreads();
         }
         if (!alive) break;
-        if (status == VTX_CG_MAXITER && sqrt(rr) <= a.o.tol * sqrt(rr0)) status = VTX_CONVERGED;
+        if (solve && status == VTX_CG_MAXITER && sqrt(rr) <= a.o.tol * sqrt(rr0))
+            status = VTX_CONVERGED;
         // project the solution to zero mean, publish it, contract
         sx = sy = 0.0;
 #pragma unroll
@@ -508,7 +510,7 @@ __global__ __launch_bounds__(kMbThreads) void k_batch_cg_mb(MbArgs a) {
         if (part == 0 && tid == 0) {
             vtx_grad_result gr{};
             gr.cg_iters = it;
-            gr.cg_rel_res = rr0 > 0.0 ? sqrt(rr / rr0) : 0.0;
+            gr.cg_rel_res = rr0 == 0.0 ? 0.0 : sqrt(rr / rr0);
             gr.status = status;
             a.res[idx] = gr;
         }

@@ -330,6 +330,14 @@ __device__ __forceinline__ double over_len_hvp(double num, double l2) {
     return num * inv_len_hvp(l2);
 }
 
+// Whether a Krylov solve iterates, by |P b| or its square: it is solved at 0,
+// and a right-hand side that is not finite, or whose square overflows, is left
+// unsolved (VTX_CG_MAXITER): a residual of infinity would pass every test
+// against a tolerance times infinity.
+__device__ __forceinline__ bool krylov_iterates(double rr0) {
+    return rr0 > 0.0 && rr0 < HUGE_VAL;
+}
+
 __device__ __forceinline__ double min_image(double d, double L) {
     return d - L * floor(d / L + 0.5);
 }

@@ -1104,10 +1104,10 @@ struct FinCgInit {
     __device__ void operator()(LoopCtl *ctl, double s) const {
         ctl->rr = s;
         ctl->rr0 = s;
-        ctl->rel_res = s > 0.0 ? 1.0 : 0.0;
-        if (!(s > 0.0)) {
+        ctl->rel_res = s == 0.0 ? 0.0 : s / s;
+        if (!krylov_iterates(s)) {
             ctl->done = 1;
-            ctl->status = VTX_CONVERGED;
+            ctl->status = s == 0.0 ? VTX_CONVERGED : VTX_CG_MAXITER;
         }
     }
 };
@@ -1473,7 +1473,10 @@ __global__ __launch_bounds__(4 * kCgVerts) void k_cg_step(HessRows H, int nv, Cg
             S.rr0 = rr;
             S.stop = a.tol * sqrt(rr);
         }
-        if (sqrt(rr) <= S.stop) {
+        if (!krylov_iterates(S.rr0)) {
+            S.done = 1;
+            S.status = S.rr0 == 0.0 ? VTX_CONVERGED : VTX_CG_MAXITER;
+        } else if (sqrt(rr) <= S.stop) {
             S.done = 1;
             S.status = VTX_CONVERGED;
         } else if (S.it >= a.max_iter) {
@@ -1488,7 +1491,7 @@ __global__ __launch_bounds__(4 * kCgVerts) void k_cg_step(HessRows H, int nv, Cg
             beta = rn > 0.0 ? rn / rr : 0.0;
             S.it += 1;
         }
-        if (blockIdx.x == 0 && tid == 0) S.rel_res = S.rr0 > 0.0 ? sqrt(rr / S.rr0) : 0.0;
+        if (blockIdx.x == 0 && tid == 0) S.rel_res = S.rr0 == 0.0 ? 0.0 : sqrt(rr / S.rr0);
     }
     if (blockIdx.x == 0 && tid == 0) {
         CgState N = S;
@@ -1760,10 +1763,10 @@ struct FinMrInit {
         ctl->mr_c1 = ctl->mr_c2 = 1.0;
         ctl->mr_s1 = ctl->mr_s2 = 0.0;
         ctl->mr_noop = 1;
-        ctl->rel_res = b1 > 0.0 ? 1.0 : 0.0;
-        if (!(b1 > 0.0)) {
+        ctl->rel_res = b1 == 0.0 ? 0.0 : b1 / b1;
+        if (!krylov_iterates(b1)) {
             ctl->done = 1;
-            ctl->status = VTX_CONVERGED;
+            ctl->status = b1 == 0.0 ? VTX_CONVERGED : VTX_CG_MAXITER;
         }
     }
 };

@@ -57,3 +57,43 @@ def test_tables_are_complete_when_a_call_with_exchanges_returns(vtx, n_cell, sch
         if schedule == "t1":  # shorten edges for the next pass
             T.relax(X, P, eta=3e-3, tol=0.0, max_iter=20)
     assert total > 0
+
+
+def _stiff(t, seed=0):
+    """Parameters under which H is positive definite on any tiling."""
+    rng = np.random.default_rng(seed)
+    return dict(KA=0.02, A0=1.0, KP=1.0, P0=0.5, lam=rng.uniform(0.9, 1.1, t.n_edge))
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, 1e200])
+@pytest.mark.parametrize("method", ["adjoint", "adjoint_minres"])
+@pytest.mark.parametrize("mode,n_cell", [("f64", 1000), ("f64", 1025), ("mixed", 200)])
+def test_a_right_side_that_is_not_finite_is_not_solved(vtx, mode, n_cell, method, bad):
+    """One NaN or infinity in dC/dX, or a norm whose square overflows: no solver
+    reports convergence (one workgroup, one launch per step, the general
+    loops, batches of each form).  A scale that stays in range scales the
+    gradient."""
+    V = vtx
+    t = g.random_tissue(n_cell, seed=5)
+    kw = _stiff(t)
+    lam = kw.pop("lam")
+    P = V.Params(lam=_dev(lam), **kw)
+    T, X = V.Tissue.from_tissue(t), _dev(t.X)
+    rng = np.random.default_rng(1)
+    unit = rng.normal(size=(t.n_vert, 2))
+    b = unit * bad if bad == 1e200 else unit.copy()
+    b[7, 1] *= bad if bad != 1e200 else 1.0
+    opts = dict(mode=mode, method=method, cg_tol=1e-10)
+    got = [T.param_grad(X, P, dC_dX=_dev(b), **opts)]
+    for threads in (0, 1024) + ((-2,) if mode == "f64" and method == "adjoint" else ()):
+        out, info = V.Batch([T]).param_grad([X], [P], dC_dX=[_dev(b)], block_threads=threads, **opts)
+        got.append((out[0], info[0]))
+    for grad, info in got:
+        assert (info["status"], info["cg_iters"]) == (V.CG_MAXITER, 0)
+        assert np.isnan(info["cg_rel_res"]) and float(grad.abs().max()) == 0.0
+    if bad == 1e200 and mode == "f64":
+        ref, info = T.param_grad(X, P, dC_dX=_dev(unit), **opts)
+        for scale in (1e140, 1e-140):
+            big, i2 = T.param_grad(X, P, dC_dX=_dev(unit * scale), **opts)
+            assert info["status"] == i2["status"] == V.CONVERGED
+            assert float((big / scale - ref).abs().max() / ref.abs().max()) < 1e-7
