@@ -103,6 +103,14 @@ constexpr int kStepChunk = 60;
 // cells, 54 and 91 at 32000.
 constexpr int64_t kCgStepMaxVerts = 65536;
 constexpr int kCgChunk = 256;
+// Every vertex's rows have as many slots per lane as the largest cell needs
+// (its sides - 2), and a step reads the columns of all of them (16 B a vertex
+// and slot, 144 B of memory): limited to 1.5 million in all (24 MB, 216 MB).
+// Against the six-launch step, a us per iteration with one cell of many sides:
+// 20.5 and 23.7 (32000 cells, 24 sides: 1.4 million), 26.9 and 25.5 (32 sides:
+// 1.9), 26.0 and 28.2 (20000 cells, 40 sides: 1.5), 39.2 and 34.8 (64: 2.5),
+// 42.2 and 45.5 (5000 cells, 100 sides: 1.0).
+constexpr int64_t kCgStepMaxSlots = 1500000;
 static_assert(kCgStepMaxVerts <= (int64_t)kCgBlocks * kCgVerts, "vertices of a workgroup");
 
 // Host copy of the staged layouts.
@@ -823,11 +831,41 @@ int vtx_v2v(vtx_tissue t, int32_t mode, const void *X, const void *X_target, dou
     return check_launch("vtx_v2v");
 }
 
+// Memory for rows of `width` slots per lane: kept for later solves, grown when
+// a larger cell appears.  False, with none held, where the device has no room.
+static bool hess_reserve(vtx_tissue t, int width) {
+    HessRows &H = t->hess;
+    if (width <= H.width) return true;
+    void *old[] = {H.col, H.top, H.bottom, H.halo, H.n_halo};
+    H = HessRows{};
+    for (void *q : old)
+        if (q) (void)hipFree(q);
+    hess_plan(t->n_vert, H);
+    width = std::max(width, 6);  // six: cells of up to eight sides
+    const size_t n = 4 * (size_t)width * (size_t)H.verts * (size_t)H.blocks;
+    hipError_t e = hipMalloc((void **)&H.col, 4 * n);
+    if (e == hipSuccess) e = hipMalloc((void **)&H.top, 16 * n);
+    if (e == hipSuccess) e = hipMalloc((void **)&H.bottom, 16 * n);
+    if (e == hipSuccess) e = hipMalloc((void **)&H.halo, 4 * (size_t)kCgHalo * (size_t)H.blocks);
+    if (e == hipSuccess) e = hipMalloc((void **)&H.n_halo, 4 * (size_t)H.blocks);
+    if (e == hipSuccess) {
+        H.width = width;
+        return true;
+    }
+    (void)hipGetLastError();  // not an error of the call, which takes the other loop
+    for (void *q : {(void *)H.col, (void *)H.top, (void *)H.bottom, (void *)H.halo,
+                    (void *)H.n_halo})
+        if (q) (void)hipFree(q);
+    H = HessRows{};
+    return false;
+}
+
 // CG by one launch per iteration (k_cg_step) on the rows of the Hessian,
-// FP64; the solution is left in w.cg, not yet projected.  The rows' memory is
-// the tissue's, kept for later solves, and grows with the largest cell.
+// FP64; the solution is left in w.cg, not yet projected.  *taken is false, and
+// nothing done, where the rows would be too wide or have no room.
 static int cg_steps(vtx_tissue t, const void *X, const vtx_params *p, const double *b, double tol,
-                    int64_t max_iter, hipStream_t s, vtx_grad_result *r) {
+                    int64_t max_iter, hipStream_t s, vtx_grad_result *r, bool *taken) {
+    *taken = false;
     CgState &h = t->w.cg_host[0];
     launch_max_sides(t->d, t->w, s);
     int rc;
@@ -837,24 +875,12 @@ static int cg_steps(vtx_tissue t, const void *X, const vtx_params *p, const doub
     int32_t sides = 0;
     HIPCHK(hipMemcpyAsync(&sides, t->w.max_sides, sizeof sides, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    HessRows &H = t->hess;
-    if (sides - 2 > H.width) {
-        const int width = std::max(sides - 2, 6);  // six: cells of up to eight sides
-        void *old[] = {H.col, H.top, H.bottom, H.halo, H.n_halo};
-        H = HessRows{};
-        hess_plan(t->n_vert, H);
-        const size_t n = 4 * (size_t)width * (size_t)H.verts * (size_t)H.blocks;
-        for (void *q : old)
-            if (q) HIPCHK(hipFree(q));
-        HIPCHK(hipMalloc((void **)&H.col, 4 * n));
-        HIPCHK(hipMalloc((void **)&H.top, 16 * n));
-        HIPCHK(hipMalloc((void **)&H.bottom, 16 * n));
-        HIPCHK(hipMalloc((void **)&H.halo, 4 * (size_t)kCgHalo * (size_t)H.blocks));
-        HIPCHK(hipMalloc((void **)&H.n_halo, 4 * (size_t)H.blocks));
-        H.width = width;
-    }
+    const int width = sides - 2;
+    if (width * t->n_vert > kCgStepMaxSlots || !hess_reserve(t, width)) return VTX_OK;
+    *taken = true;
+    const HessRows &H = t->hess;
     HessRows use = H;
-    use.width = sides - 2;  // slots in use now
+    use.width = width;  // slots in use now
     launch_hess_rows(t->d, t->w, use, X, raw(p), s);
     launch_cg_step_init(t->w, (int)t->n_vert, b, s);
     if ((rc = check_launch("Hessian rows"))) return rc;
@@ -888,8 +914,11 @@ static int solve_hessian(vtx_tissue t, int mode, const void *X, const vtx_params
         return VTX_OK;
     }
     launch_cell_coeffs(t->d, t->w, mode, X, raw(p), s);
-    if (mode == VTX_F64 && !minres && t->n_vert <= kCgStepMaxVerts) {
-        if ((rc = cg_steps(t, X, p, b, tol, max_iter, s, r))) return rc;
+    bool taken = false;
+    if (mode == VTX_F64 && !minres && t->n_vert <= kCgStepMaxVerts &&
+        (rc = cg_steps(t, X, p, b, tol, max_iter, s, r, &taken)))
+        return rc;
+    if (taken) {
         launch_project(t->w, nv, t->w.cg, s);
         if (g) launch_contract(t->d, mode, X, raw(p), theta, t->w.cg, g, s);
         return check_launch("CG solve");

@@ -97,3 +97,48 @@ def test_a_right_side_that_is_not_finite_is_not_solved(vtx, mode, n_cell, method
             big, i2 = T.param_grad(X, P, dC_dX=_dev(unit * scale), **opts)
             assert info["status"] == i2["status"] == V.CONVERGED
             assert float((big / scale - ref).abs().max() / ref.abs().max()) < 1e-7
+
+
+def _flower(n_cell, sides, seed=0):
+    """About n_cell random cells around one of `sides` sides."""
+    L, rng = np.sqrt(n_cell), np.random.default_rng([n_cell, sides, seed])
+    R = max(1.2, 0.3 * sides / (2.0 * np.pi))
+    a = 2.0 * np.pi * (np.arange(sides) + 0.3) / sides
+    out = rng.uniform(0.0, L, size=(n_cell, 2))
+    out = out[np.hypot(*(out - L / 2).T) > R + 0.6]
+    ring = L / 2 + R * np.stack([np.cos(a), np.sin(a)], 1)
+    t = g.periodic_voronoi(np.concatenate([[[L / 2, L / 2]], ring, out]), L, L)
+    assert np.bincount(t.he[:, g.HE_FACE]).max() == sides
+    return t
+
+
+@pytest.mark.parametrize("n_cell,sides", [(3000, 100), (6000, 118), (6000, 140), (9000, 100)])
+def test_cg_memory_with_a_cell_of_many_sides(vtx, n_cell, sides):
+    """The rows of the one-launch CG are as wide as the largest cell for every
+    vertex, 144 bytes a vertex and slot: beyond 1.5 million slots the solve
+    keeps the loop without them.  The memory a solve leaves held stays within
+    that (plus a megabyte of lists and rounding of four allocations to 2 MiB),
+    and its solution solves the system as the separate product has it."""
+    V = vtx
+    t = _flower(n_cell, sides)
+    kw = _stiff(t)
+    P = V.Params(lam=_dev(kw.pop("lam")), **kw)
+    T, X = V.Tissue.from_tissue(t), _dev(t.X)
+    rng = np.random.default_rng(3)
+    b = _dev(rng.normal(size=t.X.shape))
+    T.hvp(X, P, b)  # (what the first calls of a process allocate)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    d = _dev(rng.normal(size=t.n_edge))
+    _, w, info = T.param_sens(X, P, d, b, cg_tol=1e-10, want_dX=True)
+    held = free - torch.cuda.mem_get_info()[0]
+    slots = (sides - 2) * t.n_vert
+    assert held <= (144 * 1.02 * slots if slots <= 1500000 else 0) + 12e6, held
+    assert info["status"] == V.CONVERGED
+    # H w = -(d2E/dX dlambda) d, by the difference of the forces along d: F is
+    # linear in lambda, so the difference is exact up to rounding
+    F0 = T.energy_forces(X, P)[1]
+    F1 = T.energy_forces(X, V.Params(KA=0.02, A0=1.0, KP=1.0, P0=0.5, lam=P.lam + d))[1]
+    rhs = F1 - F0
+    res = T.hvp(X, P, w) - (rhs - rhs.mean(0))
+    assert float(res.norm() / rhs.norm()) < 1e-8
