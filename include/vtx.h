@@ -45,7 +45,13 @@
  *  - Every call returns VTX_OK (0) or a negative error code; the message of
  *    the last error of the calling thread is returned by vtx_last_error().
  *    Memory is owned by the caller except for tissue and batch handles,
- *    which own their topology and all workspaces (allocated at creation).
+ *    which own their topology and all workspaces, allocated at creation but
+ *    for two of a tissue beyond one workgroup, which the first synchronising
+ *    call that uses them allocates and the tissue keeps: 192 bytes a vertex
+ *    (relaxation of up to 131072 vertices) and, for FP64 CG of up to 65536
+ *    vertices, 144 bytes a vertex and side of the largest cell beyond two
+ *    (at least six, 216 MB in all; grown when a larger cell appears).  Where
+ *    the device has no room for them these calls take loops without them.
  */
 #ifndef VTX_H
 #define VTX_H

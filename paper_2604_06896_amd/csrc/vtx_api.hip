@@ -366,15 +366,24 @@ int64_t relax_look(const vtx_relax_opts *o, int chunk, int64_t iters) {
     return std::max<int64_t>(6, std::min(kLook, o->max_iter - iters + 1));
 }
 
+// The table of k_relax_step, kept from the first use on: three int4 for each of
+// four lanes a vertex, in whole blocks.  False where the device has no room.
+bool step_reserve(vtx_tissue t) {
+    if (t->w.step_tab) return true;
+    const size_t blocks = (4 * (size_t)t->n_vert + kBlock - 1) / kBlock;
+    if (hipMalloc((void **)&t->w.step_tab, 3 * 16 * (size_t)kBlock * blocks) == hipSuccess)
+        return true;
+    t->w.step_tab = nullptr;
+    (void)hipGetLastError();  // not an error of the call, which takes the other loop
+    return false;
+}
+
 // The loop of one-launch steps (k_relax_step): no nudge, tissues of up to
-// kStepMaxVerts vertices.
+// kStepMaxVerts vertices, their table reserved.
 int relax_steps(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_relax_opts *o,
                 const RelaxArgs &ra, hipStream_t s, vtx_relax_result &r, int &overflow) {
     StepCtl &h = *t->w.step_host;
     h = StepCtl{};
-    if (!t->w.step_tab)  // three int4 for each of four lanes a vertex, in whole blocks
-        HIPCHK(hipMalloc((void **)&t->w.step_tab,
-                         3 * 16 * (size_t)kBlock * ((4 * (size_t)t->n_vert + kBlock - 1) / kBlock)));
     h.s[0].status = VTX_NOT_CONVERGED;
     HIPCHK(hipMemcpyAsync(t->w.step, &h, sizeof h, hipMemcpyHostToDevice, s));
     HIPCHK(hipStreamSynchronize(s));
@@ -413,7 +422,7 @@ int relax_steps(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_
 // overflow code in `overflow`, and the final positions in X.
 int relax_grid(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_relax_opts *o,
                const RelaxArgs &ra, hipStream_t s, vtx_relax_result &r, int &overflow) {
-    if (!ra.nudge && t->n_vert <= kStepMaxVerts)
+    if (!ra.nudge && t->n_vert <= kStepMaxVerts && step_reserve(t))
         return relax_steps(t, mode, X, p, o, ra, s, r, overflow);
     LoopCtl c{};
     c.status = VTX_NOT_CONVERGED;
