@@ -1694,6 +1694,14 @@ int launched() {
 // Vertices of the batch's largest tissue.
 int64_t largest(vtx_batch b) { return tissue_size(b->ts[b->order[0]]); }
 
+// Lets a kernel take up to `budget` bytes of dynamic LDS.  The attribute is
+// the process's, so it is always set to all that a workgroup has beside the
+// kernel's static LDS and never to one launch's need: a thread that launches
+// for a small tissue then takes nothing from one that launches for a large.
+hipError_t allow_lds(const void *kern, int64_t budget) {
+    return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)budget);
+}
+
 // Launch of the batched adjoint with the dynamic LDS the largest tissue that
 // fits needs (tissues beyond the device's per-workgroup LDS keep their
 // arrays in global memory).  Workgroups of up to 512 threads run the kernel
@@ -1720,8 +1728,7 @@ int launch_batch_cg_t(vtx_batch b, const GradItem *gi, const int32_t *order, int
     }
     const int lds = (int)need;
     if (lds > 0) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_batch_cg<PosT, M, MAXT>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        e = allow_lds(reinterpret_cast<const void *>(&k_batch_cg<PosT, M, MAXT>), budget);
         if (e != hipSuccess) return hip_fail(e);
     }
     hipLaunchKernelGGL((k_batch_cg<PosT, M, MAXT>), dim3(n), dim3(block_threads), (size_t)lds, s,
@@ -1758,19 +1765,18 @@ int solve_lds_plan(const DevTissue *const *ts, size_t n, bool minres, int *lds) 
     if (e == hipSuccess)
         e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
     if (e != hipSuccess) return hip_fail(e);
+    const int64_t budget = (int64_t)lds_max - 1024;  // the kernel's static LDS stays below
     int64_t need = 0;
     for (size_t i = 0; i < n; ++i) {
         const DevTissue &d = *ts[i];
         const int64_t nb = solve_lds_bytes(d.n_vert, d.n_cell, d.n_he);
-        if (d.n_vert > kSolveMaxVerts || d.n_cell > kSolveK * kSolveThreads ||
-            nb > (int64_t)lds_max - 1024)  // the kernel's static LDS stays below
+        if (d.n_vert > kSolveMaxVerts || d.n_cell > kSolveK * kSolveThreads || nb > budget)
             return VTX_OK;
         need = std::max(need, nb);
     }
     const void *kern = minres ? reinterpret_cast<const void *>(&k_solve_lds<true>)
                               : reinterpret_cast<const void *>(&k_solve_lds<false>);
-    e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)need);
-    if (e != hipSuccess) return hip_fail(e);
+    if ((e = allow_lds(kern, budget)) != hipSuccess) return hip_fail(e);
     *lds = (int)need;
     return VTX_OK;
 }
@@ -1869,11 +1875,10 @@ int relax_lds_plan_t(const DevTissue *const *ts, size_t n, int *lds) {
         need = nb > need ? nb : need;
         nv_max = std::max<int64_t>(nv_max, d.n_vert);
     }
-    e = hipFuncSetAttribute(
-        nv_max <= kRelaxLdsThreads
-            ? reinterpret_cast<const void *>(&k_batch_relax_lds<PosT, M, T1, 1>)
-            : reinterpret_cast<const void *>(&k_batch_relax_lds<PosT, M, T1, 4>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)need);
+    e = allow_lds(nv_max <= kRelaxLdsThreads
+                      ? reinterpret_cast<const void *>(&k_batch_relax_lds<PosT, M, T1, 1>)
+                      : reinterpret_cast<const void *>(&k_batch_relax_lds<PosT, M, T1, 4>),
+                  budget);
     if (e != hipSuccess) return hip_fail(e);
     *lds = (int)need;
     return VTX_OK;
@@ -1947,7 +1952,7 @@ int launch_batch_relax_t(vtx_batch b, const BatchItem *it, const int32_t *order,
     for (vtx_tissue t : b->ts)
         if (relax_big_fits<PosT>(tissue_size(t), threads, budget))
             lds = std::max(lds, relax_big_lds_bytes<PosT>(tissue_size(t)));
-    e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    e = allow_lds(kern, budget);
     if (e != hipSuccess) return hip_fail(e);
     hipLaunchKernelGGL((k_batch_relax<PosT, M>), dim3(n), dim3(threads), (size_t)lds, s, it, order,
                        bo, b->res_d, (int)lds);

@@ -142,3 +142,54 @@ def test_cg_memory_with_a_cell_of_many_sides(vtx, n_cell, sides):
     rhs = F1 - F0
     res = T.hvp(X, P, w) - (rhs - rhs.mean(0))
     assert float(res.norm() / rhs.norm()) < 1e-8
+
+
+def test_calls_from_several_threads(vtx):
+    """Four threads, each with its own stream and tissues, relax and solve
+    tissues of different sizes at the same time: kernels of the same name with
+    different amounts of LDS.  Every result is that of the same calls made
+    alone."""
+    import threading
+    V = vtx
+    sizes = (60, 300, 700, 1000)
+
+    def work(n, rounds):
+        t = g.random_tissue(n, seed=n)
+        t2 = g.random_tissue(n + 1100, seed=n)
+        kw = _stiff(t)
+        P = V.Params(lam=_dev(kw.pop("lam")), **kw)
+        P2 = V.Params(KA=1.0, A0=1.0, KP=1.0, P0=3.7, lam=0.1)
+        b = _dev(np.random.default_rng(n).normal(size=t.X.shape))
+        T, T2 = V.Tissue.from_tissue(t), V.Tissue.from_tissue(t2)
+        B2 = V.Batch([T2])
+        out = []
+        for _ in range(rounds):
+            X, X2 = _dev(t.X), _dev(t2.X)
+            T.relax(X, P2, eta=3e-3, tol=0.0, max_iter=15)
+            B2.relax([X2], [P2], mode="f64", eta=3e-3, tol=0.0, max_iter=15)
+            grad = T.param_grad(X, P, dC_dX=b, cg_tol=1e-3)[0]
+            out.append((X, X2, grad))
+        torch.cuda.current_stream().synchronize()
+        return out
+
+    ref = {n: work(n, 1)[0] for n in sizes}
+    got, errors = {}, []
+
+    def run(n):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                got[n] = work(n, 25)
+        except Exception as e:  # reported by the test's own thread
+            errors.append((n, repr(e)))
+
+    threads = [threading.Thread(target=run, args=(n,)) for n in sizes]
+    torch.cuda.synchronize()
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    torch.cuda.synchronize()
+    assert not errors, errors
+    for n in sizes:
+        for r in got[n]:
+            assert all(torch.equal(a, c) for a, c in zip(r, ref[n]))
