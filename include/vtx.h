@@ -48,7 +48,7 @@
  *    which own their topology and all workspaces, allocated at creation but
  *    for two of a tissue beyond one workgroup, which the first synchronising
  *    call that uses them allocates and the tissue keeps: 192 bytes a vertex
- *    (relaxation of up to 131072 vertices) and, for FP64 CG of up to 65536
+ *    (relaxation of up to 131072 vertices, 98304 with T1) and, for FP64 CG of up to 65536
  *    vertices, 144 bytes a vertex and side of the largest cell beyond two
  *    (at least six, 216 MB in all; grown when a larger cell appears).  Where
  *    the device has no room for them these calls take loops without them.

@@ -91,10 +91,17 @@ ParamsRaw raw(const vtx_params *p) {
 }
 
 // Largest tissue of the one-launch relaxation step, which computes each cell
-// six times, and its launches per captured graph.  Against the two-launch
-// step, 300 FP64 steps without T1: 4.1 and 6.2 ms (30000 cells at 500 steps),
-// 4.2 and 4.7 (60000), 8.7 and 5.2 (120000).
-constexpr int64_t kStepMaxVerts = 131072;
+// six times, without T1 and with, and its launches per captured graph.  Us a
+// step of 300, against the loop of two launches (three with T1), in FP64, MIXED
+// and FP32:
+//   cells    without T1                             with T1 (no exchange)
+//    5000     6.4/14.1   6.2/13.3   6.2/13.5   10.5/18.5  10.3/18.6   9.6/17.3 (41 exchanges)
+//   20000     7.4/14.1   7.3/13.0   6.1/13.0    8.6/16.5   8.4/16.4   7.5/15.9
+//   48400    11.6/14.8  11.5/13.0   8.7/14.2   14.4/15.9  13.9/15.6  12.7/16.6
+//   53824    12.4/14.1  12.2/13.7  10.9/13.2   16.8/15.2  16.5/15.7  15.7/15.6
+//   65536    14.3/14.1  13.8/14.6  12.0/13.8   19.6/17.6  18.9/17.0  16.8/15.8
+// and 29/17 at 120000 cells without T1 in FP64.
+constexpr int64_t kStepMaxVerts = 131072, kStepMaxVertsT1 = 98304;
 constexpr int kStepChunk = 60;
 
 // The same for the one-launch CG step (an even number of launches, so that
@@ -422,7 +429,8 @@ int relax_steps(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_
 // overflow code in `overflow`, and the final positions in X.
 int relax_grid(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_relax_opts *o,
                const RelaxArgs &ra, hipStream_t s, vtx_relax_result &r, int &overflow) {
-    if (!ra.nudge && t->n_vert <= kStepMaxVerts && step_reserve(t))
+    if (!ra.nudge && t->n_vert <= (ra.t1_enable ? kStepMaxVertsT1 : kStepMaxVerts) &&
+        step_reserve(t))
         return relax_steps(t, mode, X, p, o, ra, s, r, overflow);
     LoopCtl c{};
     c.status = VTX_NOT_CONVERGED;
@@ -482,9 +490,11 @@ int relax_impl(vtx_tissue t, int mode, void *X, const vtx_params *p, const vtx_r
         return fail(VTX_E_ARG, "T1 needs l_min > 0 and l_new > 0");
     vtx_relax_result r{};
     int overflow = 0;
-    // A tissue that fits one workgroup's LDS runs its whole loop there (500
-    // FP64 steps with T1 against the one-launch step: 1.8 and 3.1 ms at 200
-    // cells, 2.4 and 3.4 at 500, 3.3 and 3.3 at 1000).
+    // A tissue that fits one workgroup's LDS runs its whole loop there.  Us a
+    // step of 500 against the one-launch step, FP64, MIXED and FP32: without T1
+    // 3.1/5.6, 2.8/5.7, 2.5/5.1 at 200 cells, 5.2/5.9, 4.5/5.9, 3.5/5.4 at 700,
+    // 6.0/6.0, 5.3/6.1, 4.2/5.4 at 1024; with T1 3.7/6.4, 3.5/6.3, 2.8/6.1, then
+    // 6.1/6.7, 5.5/6.8, 4.4/6.9, then 7.0/7.0, 6.2/7.0, 5.3/6.7.
     const vtx_relax_result *one = nullptr;
     int rc = relax_one(t->d, t->w, mode, X, raw(p), ra, o->tol, o->patience, o->max_iter, s, &one);
     if (rc) return rc;

@@ -193,3 +193,59 @@ def test_calls_from_several_threads(vtx):
     for n in sizes:
         for r in got[n]:
             assert all(torch.equal(a, c) for a, c in zip(r, ref[n]))
+
+
+def _hex(nx, ny, amp, seed=0):
+    """A hexagonal tiling of nx x ny cells of area 1, its vertices displaced."""
+    t = g.hex_lattice(nx, ny, float(np.sqrt(2.0 / (3.0 * np.sqrt(3.0)))))
+    rng = np.random.default_rng([nx, ny, seed])
+    return g.Tissue(t.he, t.X + amp * rng.normal(size=t.X.shape), t.Lx, t.Ly)
+
+
+@pytest.mark.parametrize("mode", ["f32", "mixed", "f64"])
+@pytest.mark.parametrize("nx,ny,t1", [(130, 130, True), (130, 130, False), (220, 222, True),
+                                      (222, 222, True), (256, 256, False), (256, 258, False)])
+def test_relaxation_on_both_sides_of_the_routes(vtx, mode, nx, ny, t1):
+    """Tissue.relax around the largest tissue of the one-launch step (98304
+    vertices with T1, 131072 without) and just above 32768 vertices, where a
+    thread adds up more than two of its blocks' maxima: iterates, counts and
+    topology are those of the batched loop bit for bit.  The first T1 pass of
+    the larger ones sorts more candidates (5600) than fit in LDS (4096)."""
+    V = vtx
+    dt = V.pos_dtype(mode)
+    t = _hex(nx, ny, 0.15)
+    rng = np.random.default_rng(2)
+    P = V.Params(KA=1.0, A0=1.0, KP=1.0, P0=_dev(rng.uniform(3.6, 3.9, t.n_cell), dt),
+                 lam=_dev(rng.uniform(0.05, 0.15, t.n_edge), dt))
+    A, B = V.Tissue.from_tissue(t), V.Tissue.from_tissue(t)
+    XA, XB = _dev(t.X, dt), _dev(t.X, dt)
+    opts = dict(eta=3e-3, tol=0.0, max_iter=9, t1_enable=t1, l_min=0.3, l_new=0.35)
+    ra = A.relax(XA, P, mode=mode, **opts)
+    rb = V.Batch([B]).relax([XB], [P], mode=mode, block_threads=1024, **opts)[0]
+    keys = ("iters", "n_t1", "n_stretch", "status", "max_f")
+    assert [ra[k] for k in keys] == [rb[k] for k in keys]
+    assert torch.equal(XA, XB) and np.array_equal(A.topology(), B.topology())
+    if t1:
+        first = V.Tissue.from_tissue(t).edge_lengths(_dev(t.X, dt), mode=mode) < 0.3
+        assert ra["n_t1"] > 50 and (int(first.sum()) > 4096 or nx == 130)
+
+
+@pytest.mark.parametrize("nx,ny", [(160, 126), (180, 180), (182, 182)])
+def test_cg_on_both_sides_of_the_route(vtx, nx, ny):
+    """FP64 CG with more than 144 vertices a workgroup, at its most (256; 64800
+    vertices) and beyond the one-launch step (66248): the solution solves the
+    system as the separate product has it."""
+    V = vtx
+    t = _hex(nx, ny, 0.02)
+    kw = _stiff(t)
+    P = V.Params(lam=_dev(kw.pop("lam")), **kw)
+    T, X = V.Tissue.from_tissue(t), _dev(t.X)
+    rng = np.random.default_rng(4)
+    d, b = _dev(rng.normal(size=t.n_edge)), _dev(rng.normal(size=t.X.shape))
+    dC, w, info = T.param_sens(X, P, d, b, cg_tol=1e-9, want_dX=True)
+    assert info["status"] == V.CONVERGED and info["cg_rel_res"] <= 1e-9
+    F0 = T.energy_forces(X, P)[1]
+    F1 = T.energy_forces(X, V.Params(KA=0.02, A0=1.0, KP=1.0, P0=0.5, lam=P.lam + d))[1]
+    rhs = (F1 - F0) - (F1 - F0).mean(0)  # -(d2E/dX dlambda) d, exact up to rounding
+    assert float((T.hvp(X, P, w) - rhs).norm() / rhs.norm()) < 1e-8
+    assert abs(float(dC) - float((b * w).sum())) <= 1e-12 * float((b * w).abs().sum())
