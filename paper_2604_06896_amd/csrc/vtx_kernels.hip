@@ -1390,7 +1390,13 @@ __device__ __forceinline__ double quads_sum(double v) {
 // Every block adds them up for itself (in the same order), takes the
 // stopping tests and the step length alpha = r.r / q.h, and knows the next
 // r.r before forming r: |r - alpha h|^2 = r.r - 2 alpha r.h + alpha^2 h.h,
-// hence beta; alpha itself always uses the r.r of the vector.  The new
+// hence beta; alpha itself and the stopping test always use the r.r of the
+// vector.  The difference cancels where a step cuts the residual sharply: it is
+// off by some eps r.r, which moves q by eps |r| against the new residual's
+// |r - alpha h|, so what q loses is a relative eps times that cut, rounding
+// until one step takes more than eight digits; a difference of 0 or less
+// starts again from the residual.  (An eigenvector with 1e-9 of all others
+// added, to 1e-13: 112 steps, as with the sum over the new residual.)  The new
 // q = (r - alpha h) + beta q goes to LDS for the block's vertices and for the
 // columns it reads of others, once each; each lane multiplies by its blocks
 // and the quad adds up.  (A vertex is a column of 13 rows: gathering r, q and
@@ -1398,8 +1404,11 @@ __device__ __forceinline__ double quads_sum(double v) {
 // took 8.75 us a step at 20000 cells; now 6.5, 5.1 at 5000.)  Vectors are
 // double buffered, so nothing but the kernel boundary orders the launches.
 // Up to 256 blocks, one per CU: the sums of the launch before are then one
-// load for a quarter of the threads at most.  The rows (416 B a vertex at
-// six sides) stay in the L2s: 2.1 MB of each 4 MB at 20000 cells.
+// load a thread at most (for a quarter of the threads where a block takes 256
+// vertices).  The rows are 32 B for each of a vertex's 13 blocks at six sides
+// and 16 B of columns for each slot, used or not: 512 B a vertex in a table
+// for up to eight sides (six slots), 576 for twelve, 2.6 to 2.9 of each XCD's
+// 4 MB of L2 at 20000 cells.
 struct CgStepArgs {
     double tol;
     int64_t max_iter;

@@ -249,3 +249,49 @@ def test_cg_on_both_sides_of_the_route(vtx, nx, ny):
     rhs = (F1 - F0) - (F1 - F0).mean(0)  # -(d2E/dX dlambda) d, exact up to rounding
     assert float((T.hvp(X, P, w) - rhs).norm() / rhs.norm()) < 1e-8
     assert abs(float(dC) - float((b * w).sum())) <= 1e-12 * float((b * w).abs().sum())
+
+
+@pytest.mark.parametrize("rest", [0.0, 1e-9])
+@pytest.mark.parametrize("n", [30, 34])
+def test_cg_where_one_step_cuts_the_residual_sharply(vtx, oracle, n, rest):
+    """On a perfect hexagonal tiling an eigenvector of H is solved for in one
+    step, which cuts the residual to rounding, or to the 1e-9 of it that is
+    spread over all others; the one-launch step (34 x 34 cells) has the next
+    squared residual from a difference that cancels there.  The number of
+    steps is the oracle's within a tenth, the gradient its to the tolerance
+    times the condition number (below 1e4 here)."""
+    V = vtx
+    t = _hex(n, n, 0.0)
+    m = oracle.Mesh.from_tissue(t)
+    p = g.uniform_params(t, KA=0.02, P0=0.5, lam=1.0)
+    # plane waves of one wave vector on the two vertices of a unit cell span
+    # an invariant space: eight real dimensions
+    k = 2.0 * np.pi * np.array([2.0 / t.Lx, 0.0])
+    wave = [np.cos(t.X @ k), np.sin(t.X @ k)]
+    cols = []
+    # a vertex's sublattice: whether its vertical edge points up
+    dy = (t.X[t.he[:, g.HE_TGT], 1] + t.he[:, g.HE_OY] * t.Ly - t.X[t.he[:, g.HE_SRC], 1])
+    even = np.zeros(t.n_vert, bool)
+    even[t.he[dy > 0.9 * dy.max(), g.HE_SRC]] = True
+    assert even.sum() == t.n_cell
+    for sub in (even, ~even):
+        for w in wave:
+            for comp in range(2):
+                v = np.zeros_like(t.X)
+                v[sub, comp] = w[sub]
+                cols.append(v.ravel())
+    Q, _ = np.linalg.qr(np.array(cols).T)
+    HQ = np.stack([oracle.hvp(m, t.X, p, q.reshape(-1, 2)).ravel() for q in Q.T], 1)
+    assert np.abs(HQ - Q @ (Q.T @ HQ)).max() < 1e-9  # invariant
+    lam, U = np.linalg.eigh(Q.T @ HQ)
+    b = (Q @ U[:, -1]).reshape(-1, 2)
+    rng = np.random.default_rng(n)
+    b = b / np.linalg.norm(b)
+    noise = rng.normal(size=b.shape)
+    b = b + rest * noise / np.linalg.norm(noise)
+    T, P = V.Tissue.from_tissue(t), V.Params(KA=0.02, A0=1.0, KP=1.0, P0=0.5, lam=1.0)
+    ref, io = oracle.adjoint_grad(m, t.X, p, b, theta="lambda", tol=1e-13)
+    got, info = T.param_grad(_dev(t.X), P, dC_dX=_dev(b), theta="lambda", cg_tol=1e-13)
+    assert info["status"] == V.CONVERGED and io["status"] == 0
+    assert abs(info["cg_iters"] - io["iters"]) <= 0.1 * io["iters"] + 1, (info, io)
+    assert np.abs(got.cpu().numpy() - ref).max() < 1e-9 * np.abs(ref).max()
