@@ -295,3 +295,36 @@ def test_cg_where_one_step_cuts_the_residual_sharply(vtx, oracle, n, rest):
     assert info["status"] == V.CONVERGED and io["status"] == 0
     assert abs(info["cg_iters"] - io["iters"]) <= 0.1 * io["iters"] + 1, (info, io)
     assert np.abs(got.cpu().numpy() - ref).max() < 1e-9 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("mode", ["f32", "mixed", "f64"])
+@pytest.mark.parametrize("n_cell", [20, 32, 33, 64, 129, 255, 257, 513, 1000, 1024])
+def test_one_workgroup_relaxation_in_every_mode(vtx, oracle, mode, n_cell):
+    """Tissue.relax in one workgroup, in the reduced modes as well, with
+    exchanges: one step has the oracle's topology and counts from the same
+    stored positions (exchanges are decided in FP64 in every mode), and 80
+    steps have the iterates, counts and topology of the general batched kernel
+    (1024 threads) bit for bit, on a mesh whose forces are the oracle's."""
+    V = vtx
+    dt = V.pos_dtype(mode)
+    t = g.random_tissue(n_cell, seed=600 + n_cell)
+    p = g.uniform_params(t, P0=3.7, lam=0.1)
+    P = V.Params(KA=1.0, A0=1.0, KP=1.0, P0=3.7, lam=0.1)
+    kw = dict(eta=3e-3, tol=0.0, t1_enable=True, l_min=0.05)
+    T, X = V.Tissue.from_tissue(t), _dev(t.X, dt)
+    m, Xo = oracle.Mesh.from_tissue(t), X.double().cpu().numpy()
+    r, ro = T.relax(X, P, mode=mode, max_iter=1, **kw), oracle.relax(m, Xo, p, max_iter=1, **kw)
+    assert (r["n_t1"], r["n_stretch"]) == (ro["n_t1"], ro["n_stretch"]) and r["n_stretch"] > 0
+    assert np.array_equal(T.topology(), m.he)
+    T2, X2 = V.Tissue.from_tissue(t), _dev(t.X, dt)
+    T2.relax(X2, P, mode=mode, max_iter=1, **kw)
+    ra = T.relax(X, P, mode=mode, max_iter=80, **kw)
+    rb = V.Batch([T2]).relax([X2], [P], mode=mode, block_threads=1024, max_iter=80, **kw)[0]
+    keys = ("iters", "n_t1", "n_stretch", "status", "max_f")
+    assert [ra[k] for k in keys] == [rb[k] for k in keys]
+    assert torch.equal(X, X2) and np.array_equal(T.topology(), T2.topology())
+    F = T.energy_forces(X, P, mode=mode)[1].double().cpu().numpy()
+    m.he[:] = T.topology()
+    Fo = oracle.energy_forces(m, X.double().cpu().numpy(), p)[1]
+    assert np.abs(F - Fo).max() / np.abs(Fo).max() < (1e-10 if mode == "f64" else 1e-5)
+    assert V.Tissue.from_tissue(g.Tissue(m.he, Xo, t.Lx, t.Ly)).n_edge == t.n_edge  # a valid table
