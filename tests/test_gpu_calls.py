@@ -328,3 +328,128 @@ def test_one_workgroup_relaxation_in_every_mode(vtx, oracle, mode, n_cell):
     Fo = oracle.energy_forces(m, X.double().cpu().numpy(), p)[1]
     assert np.abs(F - Fo).max() / np.abs(Fo).max() < (1e-10 if mode == "f64" else 1e-5)
     assert V.Tissue.from_tissue(g.Tissue(m.he, Xo, t.Lx, t.Ly)).n_edge == t.n_edge  # a valid table
+
+
+def _routes(V, t, mode="f64"):
+    """Calls that relax tissue t, by name: each takes (X, params, options)."""
+    T = V.Tissue.from_tissue(t)
+    B = V.Batch([T])
+
+    def batch(threads):
+        return lambda X, P, **kw: B.relax([X], [P], mode=mode, block_threads=threads, **kw)[0]
+    return T, {"single": lambda X, P, **kw: T.relax(X, P, mode=mode, **kw),
+               "batch0": batch(0), "batch256": batch(256), "batch1024": batch(1024)}
+
+
+@pytest.mark.parametrize("mode", ["f32", "mixed", "f64"])
+@pytest.mark.parametrize("n_cell", [300, 1000, 1100, 4200])
+@pytest.mark.parametrize("t1", [False, True])
+def test_forces_that_are_not_finite_end_every_loop(vtx, mode, n_cell, t1):
+    """A step of 1e30, and a NaN in the positions: every loop (one workgroup
+    from LDS, one launch per step, the general batched kernel with positions in
+    LDS and in global memory) ends with VTX_E_NONFINITE at the positions whose
+    forces are not finite, the same in all; the tissue is usable afterwards."""
+    V = vtx
+    dt = V.pos_dtype(mode)
+    t = g.random_tissue(n_cell, seed=n_cell)
+    P = V.Params(KA=1.0, A0=1.0, KP=1.0, P0=3.7, lam=0.1)
+    T, routes = _routes(V, t, mode)
+    for bad in ("step", "nan"):
+        X0 = t.X.copy()
+        if bad == "nan":
+            X0[n_cell // 2, 1] = np.nan
+        ends = []
+        for name, relax in routes.items():
+            X = _dev(X0, dt)
+            with pytest.raises(V.VtxError) as err:
+                relax(X, P, eta=1e30 if bad == "step" else 1e-3, tol=0.0, max_iter=500,
+                      t1_enable=t1, l_min=0.001)
+            assert err.value.code == V.E_NONFINITE, name
+            ends.append(X.cpu().numpy())
+            T.set_topology(t.he)
+        assert all(np.array_equal(ends[0], e, equal_nan=True) for e in ends)
+        if bad == "nan" and not t1:  # (a T1 pass comes before the forces)
+            assert np.array_equal(ends[0], _dev(X0, dt).cpu().numpy(), equal_nan=True)
+    out = []
+    for relax in routes.values():
+        X = _dev(t.X, dt)
+        relax(X, P, eta=1e-3, tol=0.0, max_iter=20)
+        out.append(X)
+    assert all(torch.equal(out[0], x) for x in out)
+
+
+def _crowd(nx, ny):
+    """A hexagonal tiling with short edges, no two near each other and all
+    numbered before the rest, each of whose stretches shortens the four edges
+    at its ends: (tissue, l_min, l_new, edges that wait for their turn)."""
+    t = g.hex_lattice(nx, ny, float(np.sqrt(2.0 / (3.0 * np.sqrt(3.0)))))
+    side = float(np.sqrt(2.0 / (3.0 * np.sqrt(3.0))))
+    he = t.he
+    assert np.array_equal(he[0::2, g.HE_TWIN], np.arange(1, len(he), 2))
+    box = np.array([t.Lx, t.Ly])
+    src, tgt = he[0::2, g.HE_SRC], he[0::2, g.HE_TGT]
+    vec = t.X[tgt] + he[0::2, g.HE_OX:g.HE_OY + 1] * box - t.X[src]
+    near = [set() for _ in range(t.n_vert)]
+    for a, b in zip(src, tgt):
+        near[a].add(b)
+        near[b].add(a)
+    X, used, chosen = t.X.copy(), set(), []
+    for e in range(t.n_edge):
+        a, b = src[e], tgt[e]
+        zone = near[a] | near[b]
+        if zone & used:
+            continue
+        used |= zone
+        chosen.append(e)
+        X[a] += 0.35 * vec[e]
+        X[b] -= 0.35 * vec[e]
+    order = np.array(chosen + [e for e in range(t.n_edge) if e not in set(chosen)])
+    new = np.empty(t.n_edge, np.int64)
+    new[order] = np.arange(t.n_edge)
+    out = he.copy()
+    for col in (g.HE_PREV, g.HE_NEXT, g.HE_TWIN):
+        out[:, col] = 2 * new[he[:, col] // 2] + he[:, col] % 2
+    out = out.reshape(-1, 2, 8)[order].reshape(-1, 8)
+    return (g.Tissue(np.ascontiguousarray(out, np.int32), X, t.Lx, t.Ly), 0.95 * side, 2.0 * side,
+            4 * len(chosen))
+
+
+@pytest.mark.parametrize("mode", ["f32", "f64"])
+@pytest.mark.parametrize("nx,ny", [(20, 20), (36, 32), (66, 66)])
+def test_a_t1_pass_with_too_many_edges_waiting(vtx, oracle, mode, nx, ny):
+    """More than 256 edges that became short wait for their turn in one T1 pass:
+    VTX_E_CAPACITY from every loop and from the pass alone, and the tissue is
+    as good as new after set_topology."""
+    V = vtx
+    dt = V.pos_dtype(mode)
+    t, l_min, l_new, waiting = _crowd(nx, ny)
+    assert waiting > 256
+    # each short edge is stretched, not exchanged, and its four neighbours end short
+    kw = dict(KA=1e-3, A0=1.0, KP=1e-3, P0=3.7, lam=1.0)
+    m, Xo = oracle.Mesh.from_tissue(t), t.X.copy()
+    before = oracle.edge_lengths(m, Xo) < l_min
+    assert before.sum() == waiting // 4 and before[:waiting // 4].all()
+    d = oracle.edge_lengths(m, Xo)
+    src, tgt = t.he[0::2, g.HE_SRC], t.he[0::2, g.HE_TGT]
+    vec = t.X[tgt] + t.he[0::2, g.HE_OX:g.HE_OY + 1] * np.array([t.Lx, t.Ly]) - t.X[src]
+    for e in range(waiting // 4):
+        Xo[src[e]] -= 0.5 * (l_new - d[e]) * vec[e] / d[e]
+        Xo[tgt[e]] += 0.5 * (l_new - d[e]) * vec[e] / d[e]
+    assert (oracle.edge_lengths(m, Xo) < l_min).sum() == waiting
+    P = V.Params(**kw)
+    T, routes = _routes(V, t, mode)
+    routes["pass"] = lambda X, P, l_min, l_new, **_: T.t1(X, P, l_min, l_new, mode=mode)
+    for name, relax in routes.items():
+        with pytest.raises(V.VtxError) as err:
+            relax(_dev(t.X, dt), P, eta=1e-6, tol=0.0, max_iter=3, t1_enable=True, l_min=l_min,
+                  l_new=l_new)
+        assert err.value.code == V.E_CAPACITY, name
+        T.set_topology(t.he)
+    out = []
+    fresh = V.Tissue.from_tissue(t)
+    for relax in [lambda X, P, **o: fresh.relax(X, P, mode=mode, **o)] + \
+            [r for n, r in routes.items() if n != "pass"]:
+        X = _dev(t.X, dt)
+        relax(X, P, eta=1e-3, tol=0.0, max_iter=10, t1_enable=True, l_min=0.2 * l_min)
+        out.append(X)
+    assert all(torch.equal(out[0], x) for x in out)
