@@ -756,14 +756,16 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_lds(const GradItem *__r
     // by their own thread, off the step's chain: they stay in global memory.
     double2 *xg = (double2 *)G.cg;
     for (int v = tid; v < nv; v += bd) xg[v] = double2{0.0, 0.0};
-    const bool solve = krylov_iterates(rr0);
-    int status = rr0 == 0.0 ? VTX_CONVERGED : VTX_CG_MAXITER;
+    // (a status of its own, not a flag kept through the loops: their registers
+    // are full, and one more live value cost 3 %)
+    constexpr int kNotSolved = -1;
+    int status = rr0 == 0.0 ? VTX_CONVERGED : krylov_iterates(rr0) ? VTX_CG_MAXITER : kNotSolved;
     int64_t it = 0;
     double rel_res = 0.0;
     double hx[KV], hy[KV];
     if (!MINRES) {
         const double stop = o.tol * sqrt(rr0);
-        while (solve && status == VTX_CG_MAXITER && it < o.max_iter) {
+        while (status == VTX_CG_MAXITER && it < o.max_iter) {
             if (__builtin_amdgcn_readfirstlane(sqrt(rr) <= stop ? 1 : 0)) {
                 status = VTX_CONVERGED;
                 break;
@@ -795,7 +797,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_lds(const GradItem *__r
                 }
             }
         }
-        if (solve && status == VTX_CG_MAXITER && sqrt(rr) <= stop) status = VTX_CONVERGED;
+        if (status == VTX_CG_MAXITER && sqrt(rr) <= stop) status = VTX_CONVERGED;
         rel_res = rr0 == 0.0 ? 0.0 : sqrt(rr / rr0);
     } else {
         // the recurrences of k_batch_cg; `ql` holds the current Lanczos
@@ -812,7 +814,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_lds(const GradItem *__r
             bx[j] = by[j] = 0.0;
         }
         double beta = 0.0, c1 = 1.0, s1 = 0.0, c2 = 1.0, s2 = 0.0, phibar = beta1;
-        while (solve && status == VTX_CG_MAXITER && it < o.max_iter) {
+        while (status == VTX_CG_MAXITER && it < o.max_iter) {
             const double alpha = solve_sum(hess(hx, hy), sh_a);
             double zz = 0.0;
 #pragma unroll
@@ -878,7 +880,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_lds(const GradItem *__r
         vtx_grad_result gr{};
         gr.cg_iters = it;
         gr.cg_rel_res = rel_res;
-        gr.status = status;
+        gr.status = status == kNotSolved ? VTX_CG_MAXITER : status;
         res[idx] = gr;
     }
     if (!G.g) return;
