@@ -89,7 +89,7 @@ extern "C" {
 /* Schedules of vtx_batch_relax. */
 #define VTX_SCHED_AUTO (-1)     /* choose by timed trials (vtx_batch_autotune)       */
 #define VTX_SCHED_PERSISTENT 0  /* one persistent launch, one workgroup per tissue   */
-#define VTX_SCHED_GRID 1        /* each tissue in turn on the whole GPU (vtx_relax)  */
+#define VTX_SCHED_GRID 1        /* each tissue in turn through vtx_relax             */
 #define VTX_SCHED_SPLIT 2       /* each tissue over several cooperating workgroups   */
 
 #define VTX_GRAD_ADJOINT 0     /* implicit differentiation, adjoint form, CG */
@@ -345,9 +345,10 @@ int vtx_batch_destroy(vtx_batch b);
  *                         vertex stars in registers, T1 passes included, on
  *                         as many waves as its largest tissue needs (512
  *                         threads at most); 0 takes 1024 threads otherwise;
- *   VTX_SCHED_GRID        each tissue in turn through vtx_relax (all
- *                         workgroups of the GPU on one tissue; suits a few
- *                         large tissues); block_threads is ignored;
+ *   VTX_SCHED_GRID        each tissue in turn through vtx_relax (the whole
+ *                         GPU on one tissue, or one workgroup where it fits;
+ *                         suits a few large tissues); block_threads is
+ *                         ignored;
  *   VTX_SCHED_SPLIT       T1 off only: each tissue split over K = block_threads
  *                         (1, 2, 4 or 8; 0 chooses) cooperating 512-thread
  *                         workgroups of one cooperative launch, each owning a

@@ -1068,7 +1068,7 @@ static_assert(kRelaxLdsThreads <= 512, "block_allsum2 holds the sums of eight wa
 // Against a form with five barriers, a branch per corner, the library's
 // sqrt and division and always eight waves, a step of 100 FP64 cells with T1
 // takes 2.8 us instead of 4.5, of 100 tissues of 100 MIXED cells 3.3 instead
-// of 4.8, and of 128 nudged FP64 relaxations of 1000 cells 8.0 instead of
+// of 4.8, and of 128 nudged FP64 relaxations of 1000 cells 7.1 instead of
 // 9.7; through one launch per pass (Tissue.relax before) the first took
 // 15.4 us.
 // KV: vertices per thread, 4 or, for tissues of up to a workgroup's threads, 1

@@ -763,14 +763,15 @@ constexpr int kQuad0 = 0x00, kQuad1 = 0x55, kQuad2 = 0xAA;
 // positions, and take the step again in the launch after, from the
 // coefficients this launch stored and the pass changed.  Kernel boundaries
 // give the ordering that device-scope arrivals or k_finish gave before (two
-// or three launches an iteration: 19.0 us at 10000 cells in MIXED with T1,
-// now 7.2; 5.3 at 3000 cells in FP64 without).  A launch is bound by its
+// or three launches an iteration: 19.0 us a step of the call at 10000 cells in
+// MIXED with T1, now 7.2; 5.1 at 3000 cells in FP64 without, 4.7 the launch).  A launch is bound by its
 // start, two rounds of loads from beyond the L2 and the chain of one cell's
 // geometry, not by the chip's rates: 5 waves a CU at 10000 cells.
 // A lane's topology is a table entry, one coalesced load of 48 bytes, where
 // star, row and corners are three loads that wait for each other; a launch
-// that finds the table out of date reads those and writes it.  (3000 cells,
-// FP64: 5.3 -> 4.9 us a launch; 10000, MIXED with T1: 7.6 -> 7.2.)
+// that finds the table out of date reads those and writes it.  (Per launch, by
+// the table alone: 5.3 -> 4.9 us at 3000 cells in FP64, 7.6 -> 7.2 at 10000 in
+// MIXED with T1.)
 // (Three waves per SIMD: the T1 pass, which one wave runs, would take all 512
 // registers and leave the step one wave per SIMD.)
 template <typename PosT, typename M, bool T1>

@@ -421,7 +421,7 @@ class Batch:
         """schedule: SCHED_PERSISTENT (one workgroup of `block_threads` per
         tissue: 256, 512 or 1024, or 0 to let the library choose, which takes
         the LDS-resident kernel when every tissue fits it), SCHED_GRID (each
-        tissue in turn on the whole GPU), SCHED_SPLIT (T1 off: each tissue
+        tissue in turn through Tissue.relax), SCHED_SPLIT (T1 off: each tissue
         over `block_threads` = 1, 2, 4 or 8 cooperating workgroups, 0
         chooses) or SCHED_AUTO (timed trials pick one)."""
         m = _mode(mode)
